@@ -172,7 +172,8 @@ int bat_reliability_range_ex(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *               kept, 64-bit FNV-1a hashes of the arc list and of p's
  *               bytes), the part count, the launch (arc order kind,
  *               work-item size and chain length as bat_last_launch reports
- *               them), the parts done, the count, then R and the per-arc T1
+ *               them; for sub-cube sweeps the levels and bits of an item and
+ *               a hash of the arcs' counter bits), the parts done, the count, then R and the per-arc T1
  *               and T0 as hexadecimal floating-point pairs (hi lo).
  *               The caller owns the file; it is kept after the sweep
  *               ends.
@@ -432,6 +433,18 @@ int bat_ms_reliability_range(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *                      each in this process when first launched).  The
  *                      code objects are those of an in-process compile:
  *                      the helper uses this process's hiprtc library
+ *   "BAT_CUBES"        whole sweeps by sub-cubes: cubes of state vectors that
+ *                      all connect, or that all do not, are decided by two
+ *                      bit-sliced closures (every arc free in the cube up,
+ *                      every one down) and added as one, the undecided ones
+ *                      are split further, down to single vectors.  -1
+ *                      (default) = where it applies, unless one of the
+ *                      options above that shape the plain sweep's launch
+ *                      is set; 0 = never; 1 = wherever it can run.  R
+ *                      agrees to rounding, counts exactly
+ *   "BAT_CUBE_LEVELS"  words of 5 arcs a sub-cube sweep's work item splits
+ *                      (1..3; 0 = by size)
+ *   "BAT_CUBE_SPLIT"   wavefronts that share such a work item (0 = by size)
  *   "BAT_JIT_FLUSH"    setting it to a nonzero value unloads every
  *                      graph-specialised kernel this process compiled or
  *                      loaded (after the current device finishes its work;
@@ -469,7 +482,9 @@ int bat_autotune(int32_t n_nodes, int32_t n_arcs, const bat_arc *arcs, const dou
 /*
  * Description of the last launch on the calling thread, for benchmarks:
  * kernel time in milliseconds (HIP events around the enumeration kernel on
- * its own stream), the number of state vectors it covered, which kernel ran
+ * its own stream, or for sub-cube sweeps the device clock at its first
+ * block's start and at the reduction's start or its only block's end), the
+ * number of state vectors it covered, which kernel ran
  * and the launch choices it ran with.  Returns BAT_EINVAL if nothing ran yet.
  */
 typedef struct {
@@ -483,7 +498,8 @@ typedef struct {
     int32_t relaxations;   /* arc relaxations per sweep after pruning */
     uint64_t kernel_id;    /* 64-bit hash naming the exact kernel code that ran (the specialised
                               kernel's code object, or the ahead-of-time kernel sources and instance) */
-    int32_t perm;          /* arc-to-counter-bit order (as "BAT_PERM"; 4 = forward BAT order; -1 batched) */
+    int32_t perm;          /* arc-to-counter-bit order (as "BAT_PERM"; 4 = forward BAT order; 5 = by influence, the
+                              sub-cube sweep's; -1 batched) */
     int32_t chain_log2;    /* warm-start chain length used, 0 = none */
     int32_t check_every;   /* convergence-test cadence */
     int32_t item_order;    /* 0 = consecutive work items, 1 = spread */

@@ -1,0 +1,435 @@
+// bat_cube.hpp -- device code of the sub-cube sweep: whole sweeps of the
+// 2^m state vectors in which a cube of vectors that all connect, or that
+// all do not, is decided and added as one.
+//
+// Included by bat_cube.hip and, as text after bat_device.hpp, by the
+// graph-specialised kernels compiled at run time; includes no header.
+//
+// The counter's M bits (the arcs on some s-t path, most often pivotal arc
+// most significant) are split, for `levels` = 1 to 3, into
+//     item | lane (up to 6 bits) | word of level levels-1 | ... | word 0
+// with words of 5 bits.  A wavefront takes an item.  A lane holds one
+// prefix; its word of level l > 0 stands for the 32 cubes that the 5 bits
+// below the prefix make, each still free in the 5 l bits under it.  Reach
+// only grows when an arc comes up, so two bit-sliced closures decide such a
+// word: with every free arc down, the cubes connected for certain (S: added
+// whole, 2^(5 l) vectors each); with every free arc up, those that can
+// connect at all (P).  The cubes of P & ~S become prefixes of the next
+// level: the wavefront queues them and takes 64 at a time, one per lane, so
+// every lane works however unevenly the undecided cubes lie.  Word 0 has
+// nothing free under it: one closure decides its 32 vectors.  Every vector
+// thus gets the verdict the plain sweep gives it, from its own word 0 or
+// from the cube that holds it.
+//
+// A closure removes the nodes other than s and t one by one: straight-line
+// AND-ORs on the working masks of the arcs and of the node pairs a removed
+// node joins (see bat_cube_plan.hpp), exact in one pass.
+//
+// What bounds it: the issue of those AND-ORs, and the scalar instructions
+// that index their registers when the graph is read at run time.  The sums
+// are per word: F(V) from the byte tables of the level (see bat_device.hpp),
+// times the prefix's probability, a product of one table entry per level.
+
+namespace bat {
+
+constexpr int kCubeGroup = 5;                     // bits of a word
+constexpr int kCubeLevels = 3;
+constexpr int kCubeProgs = 2 * kCubeLevels - 1;   // closures: word 0, then (up, down) per level
+constexpr int kCubeSlots = 64;                    // words of a closure (ahead-of-time kernels)
+constexpr int kCubeSteps = 640;                   // steps of all closures, padded
+constexpr int kCubeQueue = 1024;                  // prefixes queued at a time (a level can make 2048)
+constexpr int kCubeWaves = 4;                     // wavefronts per block
+
+struct alignas(16) double2_t {
+    double x, y;
+};
+
+struct CubeProg {
+    u32 first;    // its first step in step[]
+    u32 octets;   // steps in groups of 8, padded
+    u32 result;   // slot of the verdict; kCubeNever, kCubeAlways
+    u32 word;     // counter bit of the word's first arc
+};
+constexpr u32 kCubeNever = 254u, kCubeAlways = 255u;
+
+// Kernel argument (under 4 KiB): the plan travels with the launch, so a call
+// makes no copy of it.
+struct CubeParams {
+    u64 n_items;              // work items of this launch
+    u64 item_mul, item_mask;  // work item w is block item_base + ((w item_mul) & item_mask)
+    u64 item_base;
+    u32 m, M;                 // arcs, arcs enumerated (counter bits)
+    u32 levels, lane_bits;
+    u32 split;                // wavefronts sharing an item (each takes every split-th round of 64 prefixes)
+    u32 fused;                // one block: it writes the results itself
+    double2_t *part;          // [blocks] double-double partials
+    u64 *pcount;              // [blocks]
+    const double *p_dev;      // [m] on the device, or null: p below
+    // results: dd and count, or R (with the check of p_dev); null where not wanted
+    double *res, *R;
+    u64 *count;
+    int *status;
+    u64 *diag;                // host, or null: [start, swept, done] device clocks and seq, written last
+    u64 seq;
+    CubeProg prog[kCubeProgs];
+    unsigned char arc_of_bit[64];
+    double p[kMaxArcs];
+    // a | b << 8 | d << 16, slot d = a & b; bit 31: added to what d holds.
+    // (read 16 bytes past the last step)
+    u32 step[kCubeSteps + 4];
+};
+
+typedef const __attribute__((address_space(4))) CubeParams CubeArgs;
+
+struct CubeTables {
+    double tb[kCubeLevels][256];  // per level: sums over bits 0..2 of the word's index
+    double a4[kCubeLevels][4];    // bits 3..4
+    double q5[kCubeLevels][32];   // all five
+    double ql[kWave];             // lane bits
+    double pr[64];                // working probability of the arc at counter bit cb
+};
+struct CubeWave {
+    unsigned short queue[2][kCubeQueue];
+    unsigned short from[kWave];  // level 1 prefixes (lane << 5 | word 2 index, or the lane) of the final rounds
+    double qp[2][kWave];         // their probabilities
+};
+
+// LDS written by some lanes of a wavefront and read by others: the LDS
+// operations of one wavefront complete in order, so only the compiler must
+// keep them so.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ double cube_q(const CubeTables &T, u32 M, u32 cb, u32 x)
+{
+    if (cb >= M) return x ? 0.0 : 1.0;  // a bit past the last arc: never set
+    const double p = T.pr[cb];
+    return x ? p : 1.0 - p;
+}
+
+// The block's probability tables (all threads).
+__device__ __forceinline__ void cube_tables(CubeArgs *P, CubeTables &T)
+{
+    const u32 tid = threadIdx.x, nt = blockDim.x, M = P->M, levels = P->levels;
+    if (tid < M) {
+        const u32 a = P->arc_of_bit[tid];
+        T.pr[tid] = P->p_dev ? P->p_dev[a] : P->p[a];
+    }
+    __syncthreads();
+    for (u32 i = tid; i < levels * 256u; i += nt) {
+        const u32 l = i >> 8, y = i & 255u, c0 = kCubeGroup * l;
+        double b[2][3];
+#pragma unroll
+        for (u32 k = 0; k < 3; ++k) {
+            b[0][k] = cube_q(T, M, c0 + k, 0u);
+            b[1][k] = cube_q(T, M, c0 + k, 1u);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) s += ((y >> k) & 1u) ? b[k & 1u][0] * b[(k >> 1) & 1u][1] * b[k >> 2][2] : 0.0;
+        T.tb[l][y] = s;
+    }
+    for (u32 i = tid; i < levels * 32u; i += nt) {
+        const u32 l = i >> 5, j = i & 31u;
+        const double hi = cube_q(T, M, kCubeGroup * l + 3, (j >> 3) & 1u) * cube_q(T, M, kCubeGroup * l + 4, j >> 4);
+        double q = 1.0;
+        for (u32 k = 0; k < 3; ++k) q *= cube_q(T, M, kCubeGroup * l + k, (j >> k) & 1u);
+        T.q5[l][j] = q * hi;
+        if ((j & 7u) == 0u) T.a4[l][j >> 3] = hi;
+    }
+    if (tid < (u32)kWave) {
+        double q = 1.0;
+        for (u32 b = 0; b < P->lane_bits; ++b) q *= cube_q(T, M, kCubeGroup * levels + b, (tid >> b) & 1u);
+        T.ql[tid] = q;
+    }
+    __syncthreads();
+}
+
+// Number of set bits of x in the lanes below this one, and in all lanes.
+__device__ __forceinline__ u32 wave_excl_popc(u32 x, u32 &total)
+{
+    const u32 c = (u32)__popc(x);
+    u32 e = 0u, t = 0u;
+#pragma unroll
+    for (u32 b = 0; b < 6; ++b) {
+        const u64 m = __ballot((c >> b) & 1u);
+        e += __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u)) << b;
+        t += (u32)__popcll(m) << b;
+    }
+    total = t;
+    return e;
+}
+
+// Entries [w0, w0 + kCubeQueue) of the wavefront's set bits, in lane order:
+// lane << 5 | bit.  e: set bits in the lanes below.
+__device__ __forceinline__ void cube_enqueue(unsigned short *q, u32 U, u32 e, u32 w0, u32 lane)
+{
+    u32 pos = e - w0;
+    while (__ballot(U != 0u) != 0ull) {
+        if (U) {
+            if (pos < (u32)kCubeQueue) q[pos] = (unsigned short)(lane << 5 | (u32)__builtin_ctz(U));
+            ++pos;
+            U &= U - 1u;
+        }
+    }
+    wave_lds_sync();
+}
+
+// Graph read at run time, at most 32 counter bits: the words live in v64 to
+// v127 and the steps, read with scalar loads (four each, the next four ahead
+// of use), name them through the VGPR-index mode.  Hand-written because
+// compiled code leaves and enters that mode around each access: 9
+// instructions per step here against about 17.
+#define BAT_CUBE_STEP(w)                      \
+    "s_set_gpr_idx_on " w ", 0x1\n\t"         \
+    "v_mov_b32 %[x], v64\n\t"                 \
+    "s_lshr_b32 s72, " w ", 8\n\t"            \
+    "s_set_gpr_idx_on s72, 0x1\n\t"           \
+    "v_and_b32 %[x], v64, %[x]\n\t"           \
+    "s_lshr_b32 s72, " w ", 16\n\t"           \
+    "s_ashr_i32 s73, " w ", 31\n\t"           \
+    "s_set_gpr_idx_on s72, 0x9\n\t"           \
+    "v_and_or_b32 v64, v64, s73, %[x]\n\t"
+#define BAT_CUBE_MASK(v, cb) "v_bfe_i32 " v ", %[c], " cb ", 1\n\t"
+
+struct CubeDyn {
+    CubeArgs *P;
+
+    // c: the prefix's counter bits (free arcs' bits: set when up, as a
+    // digraph's closures use them)
+    __device__ __forceinline__ u32 close(u32 pi, u32 c, u32, bool live) const
+    {
+        const u32 result = P->prog[pi].result;
+        if (result >= (u32)kCubeSlots) return live && result == kCubeAlways ? ~0u : 0u;
+        const __attribute__((address_space(4))) u32 *steps = P->step;
+        u32 off = P->prog[pi].first * 4u, n = P->prog[pi].octets, x, out;
+        asm volatile(
+            "s_mov_b32 s74, m0\n\t"
+            "s_load_dwordx4 s[64:67], %[p], %[o]\n\t"
+            BAT_CUBE_MASK("v64", "0") BAT_CUBE_MASK("v65", "1") BAT_CUBE_MASK("v66", "2") BAT_CUBE_MASK("v67", "3")
+            BAT_CUBE_MASK("v68", "4") BAT_CUBE_MASK("v69", "5") BAT_CUBE_MASK("v70", "6") BAT_CUBE_MASK("v71", "7")
+            BAT_CUBE_MASK("v72", "8") BAT_CUBE_MASK("v73", "9") BAT_CUBE_MASK("v74", "10") BAT_CUBE_MASK("v75", "11")
+            BAT_CUBE_MASK("v76", "12") BAT_CUBE_MASK("v77", "13") BAT_CUBE_MASK("v78", "14") BAT_CUBE_MASK("v79", "15")
+            BAT_CUBE_MASK("v80", "16") BAT_CUBE_MASK("v81", "17") BAT_CUBE_MASK("v82", "18") BAT_CUBE_MASK("v83", "19")
+            BAT_CUBE_MASK("v84", "20") BAT_CUBE_MASK("v85", "21") BAT_CUBE_MASK("v86", "22") BAT_CUBE_MASK("v87", "23")
+            BAT_CUBE_MASK("v88", "24") BAT_CUBE_MASK("v89", "25") BAT_CUBE_MASK("v90", "26") BAT_CUBE_MASK("v91", "27")
+            BAT_CUBE_MASK("v92", "28") BAT_CUBE_MASK("v93", "29") BAT_CUBE_MASK("v94", "30") BAT_CUBE_MASK("v95", "31")
+            "s_set_gpr_idx_on %[w], 0x8\n\t"
+            "v_mov_b32 v64, 0xaaaaaaaa\n\t"
+            "v_mov_b32 v65, 0xcccccccc\n\t"
+            "v_mov_b32 v66, 0xf0f0f0f0\n\t"
+            "v_mov_b32 v67, 0xff00ff00\n\t"
+            "v_mov_b32 v68, 0xffff0000\n\t"
+            "s_waitcnt lgkmcnt(0)\n"
+            "1:\n\t"
+            "s_load_dwordx4 s[68:71], %[p], %[o] offset:0x10\n\t"
+            BAT_CUBE_STEP("s64") BAT_CUBE_STEP("s65") BAT_CUBE_STEP("s66") BAT_CUBE_STEP("s67")
+            "s_waitcnt lgkmcnt(0)\n\t"
+            "s_load_dwordx4 s[64:67], %[p], %[o] offset:0x20\n\t"
+            BAT_CUBE_STEP("s68") BAT_CUBE_STEP("s69") BAT_CUBE_STEP("s70") BAT_CUBE_STEP("s71")
+            "s_add_u32 %[o], %[o], 32\n\t"
+            "s_sub_u32 %[n], %[n], 1\n\t"
+            "s_cmp_lg_u32 %[n], 0\n\t"
+            "s_waitcnt lgkmcnt(0)\n\t"
+            "s_cbranch_scc1 1b\n\t"
+            "s_set_gpr_idx_on %[r], 0x1\n\t"
+            "v_mov_b32 %[out], v64\n\t"
+            "s_set_gpr_idx_off\n\t"
+            "s_mov_b32 m0, s74"
+            : [o] "+s"(off), [n] "+s"(n), [x] "=&v"(x), [out] "=&v"(out)
+            : [p] "s"(steps), [c] "v"(c), [w] "s"(P->prog[pi].word), [r] "s"(result)
+            : "scc", "memory", "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "v64", "v65",
+              "v66", "v67", "v68", "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80",
+              "v81", "v82", "v83", "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95",
+              "v96", "v97", "v98", "v99", "v100", "v101", "v102", "v103", "v104", "v105", "v106", "v107", "v108",
+              "v109", "v110", "v111", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121",
+              "v122", "v123", "v124", "v125", "v126", "v127");
+        return live ? out : 0u;
+    }
+};
+#undef BAT_CUBE_STEP
+#undef BAT_CUBE_MASK
+
+// One wavefront's share of the sweep.
+template <class Clo>
+struct CubeSweep {
+    CubeArgs *P;
+    const CubeTables &T;
+    CubeWave &W;
+    Clo clo;
+    u32 lane;
+    u64 base;          // the item's counter bits
+    double hi, lo;     // sum of the probabilities
+    u64 cnt;
+
+    __device__ __forceinline__ void add(u32 level, double q, u32 V)
+    {
+        cnt += (u64)__popc(V) << (kCubeGroup * level);
+        if (__ballot(V != 0u) == 0ull) return;
+        const double *tb = T.tb[level], *a4 = T.a4[level];
+        double F = a4[0] * tb[V & 255u];
+        F = __builtin_fma(a4[1], tb[(V >> 8) & 255u], F);
+        F = __builtin_fma(a4[2], tb[(V >> 16) & 255u], F);
+        F = __builtin_fma(a4[3], tb[V >> 24], F);
+        double s, e;
+        two_sum(hi, q * F, s, e);
+        hi = s;
+        lo += e;
+    }
+
+    __device__ __forceinline__ u32 close(u32 pi, u32 rel, u32 fill, bool live)
+    {
+        const u64 c = base | rel | fill;
+        return clo.close(pi, (u32)c, (u32)(c >> 32), live);
+    }
+
+    // The cubes of the prefix's word: added where they connect for certain
+    // (when `mine`), returned where they are undecided.
+    __device__ __forceinline__ u32 classify(u32 level, u32 rel, double q, bool live, bool mine)
+    {
+        const u32 up = close(2u * level - 1u, rel, (1u << (kCubeGroup * level)) - 1u, live);
+        if (__ballot(up != 0u) == 0ull) return 0u;
+        const u32 down = close(2u * level, rel, 0u, live && up != 0u);
+        if (mine) add(level, q, down);
+        return up & ~down;
+    }
+
+    // The vectors under the undecided cubes U of level 1 prefixes (one per
+    // lane: `from`, probability q), every `step`-th round from `first`.
+    __device__ __forceinline__ void finals(u32 U, u32 from, double q, u32 first, u32 step)
+    {
+        u32 total;
+        const u32 e = wave_excl_popc(U, total);
+        if (total == 0u) return;
+        W.from[lane] = (unsigned short)from;
+        W.qp[1][lane] = q;
+        u32 round = first;
+        for (u32 w0 = 0; w0 < total; w0 += kCubeQueue) {
+            cube_enqueue(W.queue[1], U, e, w0, lane);
+            const u32 end = min(total, w0 + (u32)kCubeQueue);
+            for (; (u32)kWave * round < end; round += step) {
+                const u32 i = (u32)kWave * round + lane;
+                const bool live = i < end;
+                const u32 x = W.queue[1][(live ? i : end - 1u) - w0], own = x >> 5;
+                const u32 rel = (u32)W.from[own] << (2 * kCubeGroup) | (x & 31u) << kCubeGroup;
+                const u32 V = close(0u, rel, 0u, live);
+                add(0u, W.qp[1][own] * T.q5[1][x & 31u], V);
+            }
+            wave_lds_sync();
+        }
+    }
+
+    __device__ __forceinline__ void item(u64 block, u32 sub)
+    {
+        const u32 levels = P->levels, lane_bits = P->lane_bits, split = P->split, M = P->M;
+        const u32 rb = kCubeGroup * levels + lane_bits;
+        base = block << rb;
+        const bool live = (lane >> lane_bits) == 0u;
+        // the item's probability: one factor per lane, multiplied across
+        double q = lane + rb < M ? cube_q(T, M, rb + lane, (u32)(block >> lane) & 1u) : 1.0;
+#pragma unroll
+        for (int off = kWave / 2; off >= 1; off >>= 1) q *= shfl_xor_d(q, off);
+        q *= T.ql[lane];
+        if (levels == 1u) {
+            u32 V = close(0u, lane << kCubeGroup, 0u, live);
+            if (M < 5u) V &= (1u << (1u << M)) - 1u;  // bits past the last arc
+            add(0u, q, V);
+            return;
+        }
+        const u32 U = classify(levels - 1u, lane << (kCubeGroup * levels), q, live, sub == 0u);
+        if (levels == 2u) {
+            finals(U, lane, q, sub, split);
+            return;
+        }
+        u32 total;
+        const u32 e = wave_excl_popc(U, total);
+        if (total == 0u) return;
+        W.qp[0][lane] = q;
+        u32 round = sub;
+        for (u32 w0 = 0; w0 < total; w0 += kCubeQueue) {
+            cube_enqueue(W.queue[0], U, e, w0, lane);
+            const u32 end = min(total, w0 + (u32)kCubeQueue);
+            for (; (u32)kWave * round < end; round += split) {
+                const u32 i = (u32)kWave * round + lane;
+                const bool on = i < end;
+                const u32 x = W.queue[0][(on ? i : end - 1u) - w0];
+                const double q1 = W.qp[0][x >> 5] * T.q5[2][x & 31u];
+                const u32 U1 = classify(1u, x << (2 * kCubeGroup), q1, on, true);
+                finals(U1, x, q1, 0u, 1u);
+            }
+            wave_lds_sync();
+        }
+    }
+};
+
+__device__ __forceinline__ void cube_clock(CubeArgs *P, u32 k)
+{
+    if (P->diag) P->diag[k] = wall_clock64();
+}
+
+// Results from the sums (one thread): as a double-double and the count, or
+// as R and the count with the check of p (NaN and -1 when a p is no
+// probability).
+__device__ __forceinline__ void cube_results(CubeArgs *P, double hi, double lo, u64 cnt)
+{
+    cnt <<= P->m - P->M;
+    int st = 0;
+    if (P->p_dev)
+        for (u32 i = 0; i < P->m; ++i)
+            if (!(P->p_dev[i] >= 0.0 && P->p_dev[i] <= 1.0)) st = -1;
+    if (P->res) {
+        P->res[0] = hi;
+        P->res[1] = lo;
+    }
+    if (P->R) *P->R = st ? __builtin_nan("") : hi + lo;
+    if (P->count) *P->count = st ? 0ull : cnt;
+    if (P->status) *P->status = st;
+    cube_clock(P, 2);
+    if (P->diag) __hip_atomic_store(P->diag + 3, P->seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <class Clo>
+__device__ __forceinline__ void cube_kernel(CubeArgs *P, CubeTables &T, CubeWave *Ws, Clo clo)
+{
+    __shared__ double sh[kCubeWaves][2];
+    __shared__ u64 sc[kCubeWaves];
+    if (blockIdx.x == 0 && threadIdx.x == 0) cube_clock(P, 0);
+    cube_tables(P, T);
+    const u32 lane = threadIdx.x & (kWave - 1);
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 waves = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
+    CubeSweep<Clo> S{P, T, Ws[wave], clo, lane, 0ull, 0.0, 0.0, 0ull};
+    const u64 w = (u64)blockIdx.x * waves + wave;
+    const u32 split = P->split;
+    const u64 it = w / split;
+    if (it < P->n_items) S.item(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
+    wave_sum_dd(S.hi, S.lo);
+    const u64 c = wave_sum_u64(S.cnt);
+    if (lane == 0) {
+        sh[wave][0] = S.hi;
+        sh[wave][1] = S.lo;
+        sc[wave] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double h = 0.0, l = 0.0;
+        u64 n = 0;
+        for (u32 k = 0; k < waves; ++k) {
+            dd_add(h, l, sh[k][0], sh[k][1]);
+            n += sc[k];
+        }
+        if (P->fused) {
+            cube_clock(P, 1);
+            cube_results(P, h, l, n);
+        } else {
+            P->part[blockIdx.x] = {h, l};
+            P->pcount[blockIdx.x] = n;
+        }
+    }
+}
+
+}  // namespace bat

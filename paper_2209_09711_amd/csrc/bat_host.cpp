@@ -39,6 +39,7 @@
 
 #include "bat.h"
 #include "bat_launch.hpp"
+#include "bat_cube_plan.hpp"
 
 using bat::u32;
 using bat::u64;
@@ -76,7 +77,8 @@ int fail(int code, const char *fmt, ...)
 struct Options {
     std::atomic<int64_t> jit{2}, chunk_log2{0}, seg_log2{6}, check_every{1}, autotune{1}, perm{-1}, chain_log2{-1}, item_order{-1},
         window_test{1}, block_waves{-1}, super_restart{-1}, simd_waves{-1}, keep_bottom{-1}, series{1},
-        grad_keep_bottom{2}, ms_run{0}, jit_procs{16}, batch_jit_arcs{-1}, batch_streams{-1}, ms_bits{1}, batch_acc{1}, jit_flush_req{0};
+        grad_keep_bottom{2}, ms_run{0}, jit_procs{16}, batch_jit_arcs{-1}, batch_streams{-1}, ms_bits{1}, batch_acc{1}, jit_flush_req{0},
+        cubes{-1}, cube_levels{0}, cube_split{0};
     Options()
     {
         auto rd = [](const char *k, std::atomic<int64_t> &v) {
@@ -104,6 +106,9 @@ struct Options {
         rd("BAT_BATCH_STREAMS", batch_streams);
         rd("BAT_MS_BITS", ms_bits);
         rd("BAT_BATCH_ACC", batch_acc);
+        rd("BAT_CUBES", cubes);
+        rd("BAT_CUBE_LEVELS", cube_levels);
+        rd("BAT_CUBE_SPLIT", cube_split);
     }
     std::atomic<int64_t> *find(const char *k)
     {
@@ -130,7 +135,17 @@ struct Options {
         if (!strcmp(k, "BAT_MS_BITS")) return &ms_bits;
         if (!strcmp(k, "BAT_BATCH_ACC")) return &batch_acc;
         if (!strcmp(k, "BAT_JIT_FLUSH")) return &jit_flush_req;
+        if (!strcmp(k, "BAT_CUBES")) return &cubes;
+        if (!strcmp(k, "BAT_CUBE_LEVELS")) return &cube_levels;
+        if (!strcmp(k, "BAT_CUBE_SPLIT")) return &cube_split;
         return nullptr;
+    }
+    // whether every knob of the plain sweep's launch is at its default
+    bool plain_shape_default() const
+    {
+        return jit == 2 && perm < 0 && chain_log2 < 0 && chunk_log2 <= 0 && seg_log2 == 6 && check_every == 1 &&
+               item_order < 0 && window_test == 1 && block_waves < 0 && super_restart < 0 && simd_waves < 0 &&
+               keep_bottom < 0 && series == 1 && grad_keep_bottom == 2;
     }
 };
 Options &opts()
@@ -236,6 +251,7 @@ struct Plan {
 constexpr int kPermKinds = 4;
 constexpr int kDefaultPerm = 3;  // untuned whole sweeps
 constexpr int kPermForward = 4;  // the forward BAT order (ranges only; never tuned)
+constexpr int kPermInfluence = 5;  // the sub-cube sweep's order (bat_cube_plan.hpp); no sweep of the plain kernels
 constexpr int kGradThreeWaveNodes = 28;  // gradient sweeps of graphs up to this size run 3 waves/SIMD
 constexpr int kSuperMaxNodes = 28;       // forward sweeps keep super-block bottoms in LDS up to this size
 
@@ -356,15 +372,9 @@ void contract_series(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32
     P.jT = id[t];
 }
 
-void make_plan(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, Plan &P, int perm_kind = 0,
-               bool directed = false)
+// rel[i]: arc i may lie on a simple s-t path (exactly, for undirected arcs).
+std::vector<char> relevance(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed)
 {
-    P.n = n;
-    P.m = m;
-    P.s = s;
-    P.t = t;
-    P.perm = perm_kind;
-    P.directed = directed;
     Bcc B;
     B.n = n;
     B.m = m;
@@ -408,6 +418,19 @@ void make_plan(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, 
             B.rel[i] = u != v && v != s && u != t && from_s[u] && to_t[v];
         }
     }
+    return B.rel;
+}
+
+void make_plan(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, Plan &P, int perm_kind = 0,
+               bool directed = false)
+{
+    P.n = n;
+    P.m = m;
+    P.s = s;
+    P.t = t;
+    P.perm = perm_kind;
+    P.directed = directed;
+    const std::vector<char> Brel = relevance(n, m, arcs, s, t, directed);
 
     // BFS from s over relevant arcs: node numbering and sweep order
     std::vector<int> id(n, -1), order, rel_bfs, disc_flag;
@@ -418,7 +441,7 @@ void make_plan(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, 
     for (size_t h = 0; h < order.size(); ++h) {
         int u = order[h];
         for (int i = 0; i < m; ++i) {
-            if (!B.rel[i] || listed[i]) continue;
+            if (!Brel[i] || listed[i]) continue;
             int a = arcs[i].u, b = arcs[i].v;
             if (directed ? a != u : (a != u && b != u)) continue;  // directed: leave by the tail
             int w = (a == u) ? b : a;
@@ -512,6 +535,7 @@ void chain_codes(const Plan &P, u32 out[6])
 struct DeviceInfo {
     int id = -1;
     int cus = 0;
+    int clock_khz = 0;  // of the device clock kernels read (wall_clock64)
     std::string arch;
 };
 
@@ -530,6 +554,7 @@ int current_device(DeviceInfo &D)
         d.id = dev;
         d.cus = prop.multiProcessorCount;
         d.arch = prop.gcnArchName;
+        HIPCHK(hipDeviceGetAttribute(&d.clock_khz, hipDeviceAttributeWallClockRate, dev));
         it = cache.emplace(dev, d).first;
     }
     D = it->second;
@@ -560,8 +585,18 @@ struct SideStreams {
     hipEvent_t join[kSideStreams] = {};
 };
 
+// Where a thread's sub-cube sweeps report to (pinned host memory, never
+// freed): the device clocks and sequence number of its last kDiagSlots
+// launches, [start, swept, done, seq] each.
+constexpr u64 kDiagSlots = 16;
+struct Diag {
+    u64 *slots = nullptr;
+    u64 seq = 0;
+};
+
 struct ResourcePool {
     std::mutex mu;
+    std::vector<Diag> diag;
     std::multimap<int, hipStream_t> streams;
     std::multimap<int, Scratch> scratch;
     std::vector<std::vector<hipEvent_t>> events;
@@ -578,7 +613,10 @@ struct ThreadState {
     std::map<int, SideStreams> side;
     std::map<int, Scratch> scratch;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    Diag diag;
     bool have_launch = false;
+    u64 cube_seq = 0;  // the last launch was this sub-cube sweep (0: another kernel)
+    int cube_dev = 0, cube_khz = 0;
     bat_launch_info info{};
     ~ThreadState()
     {
@@ -589,6 +627,7 @@ struct ThreadState {
         for (auto &kv : scratch)
             if (kv.second.dev || kv.second.host) P.scratch.emplace(kv.first, kv.second);
         if (ev[0]) P.events.emplace_back(ev, ev + 4);
+        if (diag.slots) P.diag.push_back(diag);
     }
 };
 thread_local ThreadState t_state;
@@ -698,6 +737,36 @@ int events_ready()
     }
     return BAT_OK;
 }
+
+// The next launch's report slot (null: `stream` is being captured and the
+// thread has no slots yet, which cannot be allocated then).
+int diag_next(hipStream_t stream, u64 *&slot, u64 &seq)
+{
+    Diag &G = t_state.diag;
+    if (!G.slots) {
+        ResourcePool &P = pool();
+        std::lock_guard<std::mutex> g(P.mu);
+        if (!P.diag.empty()) {
+            G = P.diag.back();
+            P.diag.pop_back();
+        }
+    }
+    if (!G.slots) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (stream) HIPCHK(hipStreamIsCapturing(stream, &cs));
+        slot = nullptr;
+        if (cs != hipStreamCaptureStatusNone) return BAT_OK;
+        void *h = nullptr;
+        HIPCHK(hipHostMalloc(&h, sizeof(u64) * 4 * kDiagSlots, hipHostMallocDefault));
+        memset(h, 0, sizeof(u64) * 4 * kDiagSlots);
+        G.slots = (u64 *)h;
+    }
+    seq = ++G.seq;
+    slot = G.slots + 4 * (seq % kDiagSlots);
+    return BAT_OK;
+}
+
+bool diag_done(const u64 *slot, u64 seq) { return __atomic_load_n(slot + 3, __ATOMIC_ACQUIRE) == seq; }
 
 // ------------------------------------------------- fixed device scratch
 // The workspace of bat_reliability_noalloc: a fixed array in device memory,
@@ -1595,6 +1664,7 @@ int queue_sweep(const Request &rq, const Plan &P, const DeviceInfo &D, const Tun
 
     bat_launch_info &I = t_state.info;
     memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
     I.jit_ms = jit_ms;
     I.vectors = std::min<u64>(rq.c_hi - rq.c_lo, K.n_chunks * K.chunk_iters << bat::kWordBits);
     I.specialised = use_jit ? 1 : 0;
@@ -1614,6 +1684,221 @@ int queue_sweep(const Request &rq, const Plan &P, const DeviceInfo &D, const Tun
     I.simd_waves = (use_jit && !(rq.grad && P.jN > kGradThreeWaveNodes)) ? shape.simd_waves : 0;
     t_state.have_launch = true;
     return BAT_OK;
+}
+
+// ------------------------------------------------------- sub-cube sweeps
+// Whole sweeps in the form of bat_cube.hpp.  Option BAT_CUBES: -1 (default)
+// takes it unless a knob of the plain sweep's launch has been set (those
+// describe the plain kernels), 0 never, 1 always where it can run.
+bool cubes_wanted(bool grad)
+{
+    const int64_t want = opts().cubes.load();
+    if (want == 0 || grad) return false;
+    return want == 1 || opts().plain_shape_default();
+}
+
+// Levels by size.  One level decides every word of 32 vectors by itself: one
+// closure deep, so the shortest while the device holds its 2^(M - 11)
+// wavefronts (24 arcs: 16 us against 12 us with two levels; 22 arcs: 8 us
+// against 10 us).  Three levels decide less (30 arcs: 42 us against 34 us)
+// but run longer chains of closures per wavefront; they win from 32 arcs on
+// (0.60 ms against 0.56 ms there).
+void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed, batcube::CubePlan &C,
+                int levels = 0)
+{
+    std::vector<char> rel = relevance(n, m, arcs, s, t, directed);
+    for (int32_t i = 0; i < m; ++i)
+        if (arcs[i].u == arcs[i].v) rel[i] = 0;
+    if (levels <= 0) levels = (int)opts().cube_levels.load();
+    int M = 0;
+    for (int32_t i = 0; i < m; ++i) M += rel[i] ? 1 : 0;
+    if (levels <= 0) levels = M <= 23 ? 1 : M <= 31 ? 2 : 3;
+    batcube::make_cube_plan(n, m, arcs, rel, s, t, directed, levels, C);
+}
+
+// The launch of a cube plan: everything but the result and partial pointers.
+// part j of `parts` (a power of two, at most the items): the items that are
+// j modulo parts.
+u64 cube_items(const batcube::CubePlan &C) { return 1ull << std::max(0, C.M - C.rel_bits()); }
+
+int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
+                bat::CubeParams &K, unsigned &blocks, int &waves, u64 parts = 1, u64 part = 0)
+{
+    memset(&K, 0, sizeof K);
+    K.m = (u32)C.m;
+    K.M = (u32)C.M;
+    K.levels = (u32)C.levels;
+    K.lane_bits = (u32)C.lane_bits;
+    K.n_items = cube_items(C) / parts;
+    K.item_mul = 0x9E3779B97F4A7C15ull * parts;  // odd times parts: consecutive items lie apart
+    K.item_mask = cube_items(C) - 1;
+    K.item_base = part;
+    // a few wavefronts share an item while the items alone would leave the
+    // device partly empty (24 arcs, 256 items: 12.4 us shared by 4, 15.3 us
+    // alone; 28 arcs, 4096 items: 55 us shared by 4, 62 us alone)
+    u64 split = 1;
+    if (opts().cube_split.load() > 0) split = (u64)opts().cube_split.load();
+    else
+        while (C.levels > 1 && split < 16 && K.n_items * split < (u64)D.cus * 16) split *= 2;
+    if (C.levels == 1) split = 1;
+    K.split = (u32)split;
+    const u64 w = K.n_items * split;
+    waves = (int)std::min<u64>(w, bat::kCubeWaves);
+    const u64 nb = (w + waves - 1) / waves;
+    if (nb > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)w);
+    blocks = (unsigned)nb;
+    K.fused = nb == 1 ? 1u : 0u;
+    K.p_dev = p_dev;
+    if (p_host) memcpy(K.p, p_host, sizeof(double) * C.m);
+    for (int c = 0; c < C.M; ++c) K.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
+    u32 at = 0;
+    for (int k = 0; k < 2 * C.levels - 1; ++k) {
+        const batcube::Program &pr = C.prog[k];
+        bat::CubeProg &q = K.prog[k];
+        q.first = at;
+        q.octets = (u32)std::max<size_t>(1, (pr.step.size() + 7) / 8);
+        q.result = pr.result == -1 ? bat::kCubeNever : pr.result == -2 ? bat::kCubeAlways : (u32)pr.result;
+        q.word = (u32)(bat::kCubeGroup * ((k + 1) / 2));
+        if (at + 8 * q.octets > (u32)bat::kCubeSteps) return fail(BAT_EDEVICE, "sub-cube closures of too many steps");
+        for (u32 i = 0; i < 8 * q.octets; ++i) {
+            if (i < pr.step.size()) {
+                const batcube::Step &x = pr.step[i];
+                K.step[at + i] = (u32)x.a | (u32)x.b << 8 | (u32)x.d << 16 | (x.assign ? 0u : 1u << 31);
+            } else {
+                K.step[at + i] = 1u << 31;  // slot 0 |= itself
+            }
+        }
+        at += 8 * q.octets;
+    }
+    return BAT_OK;
+}
+
+// Whether the ahead-of-time kernel can run the plan.
+bool cube_fits(const batcube::CubePlan &C)
+{
+    return C.M <= batk::kCubeMaxBits && C.slots <= bat::kCubeSlots && C.steps + 8 * bat::kCubeProgs <= bat::kCubeSteps;
+}
+
+// The blocks' partials (none when one block writes the results).
+size_t cube_part_bytes(const bat::CubeParams &K, unsigned blocks) { return K.fused ? 0 : 24 * (size_t)blocks; }
+void cube_parts(bat::CubeParams &K, unsigned blocks, char *ws)
+{
+    if (K.fused) return;
+    K.part = (bat::double2_t *)ws;
+    K.pcount = (u64 *)(ws + 16 * (size_t)blocks);
+}
+
+void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int waves)
+{
+    bat_launch_info &I = t_state.info;
+    memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
+    I.vectors = (1ull << C.m) / (cube_items(C) / K.n_items);
+    I.chunk_log2 = std::max(0, C.rel_bits() + (C.m - C.M) - bat::kWordBits);
+    I.n_chunks = (int32_t)std::min<u64>(K.n_items, 0x7fffffff);
+    I.relaxations = C.M;
+    I.kernel_id = aot_kernel_id("k_cube_fwd", 0, false);
+    I.perm = kPermInfluence;
+    I.check_every = 1;
+    I.item_order = 1;
+    I.block_waves = waves;
+    t_state.have_launch = true;
+}
+
+// Queue the sweep (and its reduction) on `stream`; K's result pointers set.
+// No event is recorded: the kernels report their clocks themselves (four
+// event records took a third of a small call's time).
+int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, const DeviceInfo &D,
+               hipStream_t stream)
+{
+    u64 *slot = nullptr;
+    int rc = diag_next(stream, slot, K.seq);
+    if (rc) return rc;
+    K.diag = slot;
+    HIPCHK(batk::cube_sweep(stream, blocks, waves, K));
+    if (!K.fused) HIPCHK(batk::cube_finish(stream, blocks, K));
+    cube_launch_info(C, K, waves);
+    t_state.have_launch = slot != nullptr;
+    t_state.cube_seq = K.seq;
+    t_state.cube_dev = D.id;
+    t_state.cube_khz = D.clock_khz;
+    return BAT_OK;
+}
+
+// Wait for a launch on the thread's stream: a short call's results are
+// there some microseconds before the stream counts as idle, so its report
+// is polled first.
+int cube_wait(const bat::CubeParams &K, hipStream_t stream)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 0; !diag_done(K.diag, K.seq); ++k) {
+        __builtin_ia32_pause();
+        if ((k & 63) == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) {
+            HIPCHK(hipStreamSynchronize(stream));
+            if (!diag_done(K.diag, K.seq)) return fail(BAT_EDEVICE, "a sweep ended without its results");
+        }
+    }
+    return BAT_OK;
+}
+
+// A whole sweep over host probabilities (validated): R as a double-double
+// and the count, written by the device into the pinned staging buffer.
+int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, double *R_hl, u64 &count,
+              u64 parts = 1, u64 part = 0)
+{
+    hipStream_t stream;
+    int rc = thread_stream(D.id, stream);
+    if (rc) return rc;
+    bat::CubeParams K;
+    unsigned blocks = 0;
+    int waves = 0;
+    rc = cube_params(C, p, nullptr, D, K, blocks, waves, parts, part);
+    if (rc) return rc;
+    Scratch *S = nullptr;
+    rc = scratch_reserve(D.id, stream, cube_part_bytes(K, blocks), 64, S);
+    if (rc) return rc;
+    cube_parts(K, blocks, S->dev);
+    K.res = (double *)S->host;
+    K.count = (u64 *)(S->host + 16);
+    rc = cube_queue(C, K, blocks, waves, D, stream);
+    if (!rc) rc = cube_wait(K, stream);
+    if (rc) {
+        (void)hipStreamSynchronize(stream);
+        return rc;
+    }
+    memcpy(R_hl, S->host, 16);
+    memcpy(&count, S->host + 16, 8);
+    return BAT_OK;
+}
+
+// The same on `stream` over device probabilities, results to device memory.
+// ws: a workspace of ws_bytes, or null to take one from the stream's pool.
+int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo &D, hipStream_t stream, double *R,
+               u64 *count, int *status, char *ws, size_t ws_bytes)
+{
+    bat::CubeParams K;
+    unsigned blocks = 0;
+    int waves = 0;
+    int rc = cube_params(C, nullptr, p_dev, D, K, blocks, waves);
+    if (rc) return rc;
+    const size_t need = cube_part_bytes(K, blocks);
+    void *own = nullptr;
+    if (!ws && need) {
+        HIPCHK(hipMallocAsync(&own, need, stream));
+        ws = (char *)own;
+    } else if (ws && need > ws_bytes) {
+        return fail(BAT_ETOOBIG, "needs %zu bytes of fixed scratch; it holds %zu", need, ws_bytes);
+    }
+    cube_parts(K, blocks, ws);
+    K.R = R;
+    K.count = count;
+    K.status = status;
+    rc = cube_queue(C, K, blocks, waves, D, stream);
+    if (own) {
+        const hipError_t e = hipFreeAsync(own, stream);
+        if (!rc) HIPCHK(e);
+    }
+    return rc;
 }
 
 struct Prepared {
@@ -1650,6 +1935,17 @@ int run_sync(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
     TuneChoice tc;
     const bool full = c_lo == 0 && c_hi == (1ull << m);
     if (!p && m > 0) return fail(BAT_EINVAL, "p is NULL");
+    if (full && !tmpl && cubes_wanted(grad)) {
+        int rc = validate(n, m, arcs, p, s, t);
+        if (!rc) rc = current_device(X.D);
+        if (rc) return rc;
+        batcube::CubePlan C;
+        make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C);
+        if (cube_fits(C)) {
+            res.assign(2, 0.0);
+            return cube_sync(C, p, X.D, res.data(), count);
+        }
+    }
     // any arc order for a whole sweep; a partial range is in the paper's
     // order unless the caller (the autotuner timing a sample) forces one
     const bool allow_perm = full || (tmpl && tmpl->force_perm >= 0);
@@ -1750,6 +2046,9 @@ struct RunningSums {
     // the launch every chunk repeats (-1: no chunk run yet): arc-to-bit
     // order kind, work-item size (log2 iterations), chain length
     int order = -1, items = -1, chain = -1;
+    // order kPermInfluence (sub-cube sweeps): items is 32 levels + the bits
+    // of an item, bits a hash of the arcs' counter bits
+    uint64_t bits = 0;
     u64 parts = 0;  // chunks: parts of the whole sweep's work items
     u64 done = 0;
     u64 count = 0;
@@ -1817,20 +2116,31 @@ int checkpoint_read(const char *path, const std::string &problem, bool grad, int
         return fail(BAT_EINVAL, "checkpoint %s belongs to another problem (%s; this call: %s)", path,
                     lines[1].c_str(), problem.c_str());
     if (lines.size() < (grad ? 9u : 7u)) return fail(BAT_EIO, "checkpoint %s: truncated", path);
-    unsigned long long parts = 0, done = 0, cnt = 0;
+    unsigned long long parts = 0, done = 0, cnt = 0, bits = 0;
     int order = -1, items = -1, chain = -1;
     char tail;
+    const int got_launch = sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d bits=%llx %c", &order, &items,
+                                  &chain, &bits, &tail);
+    const bool cubes = order == kPermInfluence;
+    const bool launch_ok =
+        cubes ? got_launch == 4
+              : sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d %c", &order, &items, &chain, &tail) == 3;
     if (sscanf(lines[2].c_str(), "parts %llu %c", &parts, &tail) != 1 ||
-        sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d %c", &order, &items, &chain, &tail) != 3 ||
+        !launch_ok ||
         sscanf(lines[4].c_str(), "done %llu %c", &done, &tail) != 1 ||
         sscanf(lines[5].c_str(), "count %llu %c", &cnt, &tail) != 1)
         return fail(BAT_EIO, "checkpoint %s: malformed header", path);
     const int ubits = m > bat::kWordBits ? m - bat::kWordBits : 0;
     const bool fwd = (flags & BAT_FORWARD_ORDER) != 0;
-    if (fwd ? order != kPermForward : (order < 0 || order >= kPermKinds))
+    if (cubes) {
+        const int levels = items / 32, rel = items % 32;
+        if (fwd || levels < 1 || levels > bat::kCubeLevels || rel < bat::kCubeGroup * levels || chain != 0 ||
+            parts == 0 || (parts & (parts - 1)) != 0 || parts > (1ull << std::max(m - rel, 0)) || done > parts)
+            return fail(BAT_EIO, "checkpoint %s: bad launch or part counts", path);
+    } else if (fwd ? order != kPermForward : (order < 0 || order >= kPermKinds))
         return fail(BAT_EIO, "checkpoint %s: bad arc order %d", path, order);
-    if (items < 0 || items > 20 || (chain != 0 && (chain < 3 || chain > 6)) || parts == 0 ||
-        (parts & (parts - 1)) != 0 || parts > (1ull << std::max(ubits - items, 0)) || done > parts)
+    if (!cubes && (items < 0 || items > 20 || (chain != 0 && (chain < 3 || chain > 6)) || parts == 0 ||
+        (parts & (parts - 1)) != 0 || parts > (1ull << std::max(ubits - items, 0)) || done > parts))
         return fail(BAT_EIO, "checkpoint %s: bad launch or part counts", path);
     // "<tag> hi lo [hi lo ...]" with hexadecimal floats (exact round trip)
     auto doubles = [&](const std::string &ln, const char *tag, size_t want, double *out) {
@@ -1850,6 +2160,7 @@ int checkpoint_read(const char *path, const std::string &problem, bool grad, int
     R.order = order;
     R.items = items;
     R.chain = chain;
+    R.bits = bits;
     R.parts = parts;
     R.done = done;
     R.count = cnt;
@@ -1869,9 +2180,11 @@ int checkpoint_read(const char *path, const std::string &problem, bool grad, int
 int checkpoint_write(const char *path, const std::string &problem, bool grad, const RunningSums &S)
 {
     std::string text = std::string(kCheckpointMagic) + "\n" + problem + "\n";
-    char buf[128];
-    snprintf(buf, sizeof buf, "parts %llu\nlaunch order=%d items=%d chain=%d\ndone %llu\ncount %llu\nR %a %a\n",
-             (unsigned long long)S.parts, S.order, S.items, S.chain, (unsigned long long)S.done,
+    char buf[256];
+    char bits[32] = "";
+    if (S.order == kPermInfluence) snprintf(bits, sizeof bits, " bits=%016llx", (unsigned long long)S.bits);
+    snprintf(buf, sizeof buf, "parts %llu\nlaunch order=%d items=%d chain=%d%s\ndone %llu\ncount %llu\nR %a %a\n",
+             (unsigned long long)S.parts, S.order, S.items, S.chain, bits, (unsigned long long)S.done,
              (unsigned long long)S.count, S.R[0], S.R[1]);
     text += buf;
     if (grad) {
@@ -1909,6 +2222,31 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
 {
     Request rq{};
     const bool first = S.order < 0;
+    if (first ? cubes_wanted(grad) && !(flags & BAT_FORWARD_ORDER) : S.order == kPermInfluence) {
+        // the sub-cube sweep's items
+        DeviceInfo D;
+        int rc = current_device(D);
+        if (rc) return rc;
+        batcube::CubePlan C;
+        make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C, first ? 0 : S.items / 32);
+        uint64_t bits = fnv_bytes(1469598103934665603ull, C.arc_of_bit.data(), sizeof(int) * C.arc_of_bit.size());
+        if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) || grad ||
+                       !cube_fits(C)))
+            return fail(BAT_EIO, "the checkpoint's work items are not the ones this library cuts");
+        if (cube_fits(C)) {
+            if (first) {
+                S.order = kPermInfluence;
+                S.items = 32 * C.levels + C.rel_bits();
+                S.chain = 0;
+                S.bits = bits;
+                S.parts = std::min<u64>(parts_wanted, cube_items(C));
+            }
+            u64 c = 0;
+            rc = cube_sync(C, p, D, R_hl, c, S.parts, S.done);
+            *count = c;
+            return rc;
+        }
+    }
     if (first) {
         int rc = whole_sweep_order(n, m, arcs, s, t, flags, grad, rq.force_perm);
         if (rc) return rc;
@@ -2150,6 +2488,7 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     HIPCHK(hipStreamSynchronize(st));
     bat_launch_info &I = t_state.info;
     memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
     I.vectors = c_hi - c_lo;
     I.n_chunks = (int32_t)std::min<u64>(n_items, 0x7fffffff);
     I.chunk_log2 = -1;
@@ -2314,6 +2653,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     HIPCHK(hipStreamSynchronize(st));
     bat_launch_info &I = t_state.info;
     memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
     I.vectors = span;
     I.n_chunks = (int32_t)std::min<u64>(K.n_items, 0x7fffffff);
     I.chunk_log2 = -1;
@@ -2483,9 +2823,19 @@ static int async_common(int32_t n, int32_t m, const bat_arc *arcs, const double 
     if (m > 0 && !p_dev) return fail(BAT_EINVAL, "p_dev is NULL");
     Prepared X;
     TuneChoice tc;
-    int rc = prepare(n, m, arcs, nullptr, s, t, grad, true, nullptr, X, tc);
-    if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
+    int rc;
+    if (cubes_wanted(grad)) {
+        rc = validate(n, m, arcs, nullptr, s, t);
+        if (!rc) rc = current_device(X.D);
+        if (rc) return rc;
+        batcube::CubePlan C;
+        make_cubes(n, m, arcs, s, t, false, C);
+        if (cube_fits(C))
+            return cube_async(C, p_dev, X.D, st, R_dev, (u64 *)count_dev, status_dev, nullptr, 0);
+    }
+    rc = prepare(n, m, arcs, nullptr, s, t, grad, true, nullptr, X, tc);
+    if (rc) return rc;
     Request rq{};
     rq.n = n; rq.m = m; rq.s = s; rq.t = t; rq.arcs = arcs; rq.p_dev = p_dev;
     rq.c_lo = 0; rq.c_hi = 1ull << m; rq.grad = grad;
@@ -2531,6 +2881,12 @@ int bat_reliability_noalloc(int32_t n, int32_t m, const bat_arc *arcs, const dou
     rc = noalloc_scratch(X.D.id, ws);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
+    if (cubes_wanted(false)) {
+        batcube::CubePlan C;
+        make_cubes(n, m, arcs, s, t, false, C);
+        if (cube_fits(C))
+            return cube_async(C, p_dev, X.D, st, R_dev, (u64 *)count_dev, status_dev, ws, kNoAllocScratchBytes);
+    }
     Request rq{};
     rq.n = n; rq.m = m; rq.s = s; rq.t = t; rq.arcs = arcs; rq.p_dev = p_dev;
     rq.c_lo = 0; rq.c_hi = 1ull << m; rq.grad = false;
@@ -2615,6 +2971,23 @@ int bat_last_launch(bat_launch_info *info)
 {
     if (!info) return fail(BAT_EINVAL, "NULL info");
     if (!t_state.have_launch) return fail(BAT_EINVAL, "no launch on this thread yet");
+    if (t_state.cube_seq) {
+        const u64 *d = t_state.diag.slots + 4 * (t_state.cube_seq % kDiagSlots);
+        if (!diag_done(d, t_state.cube_seq)) {
+            int dev = 0;
+            HIPCHK(hipGetDevice(&dev));
+            HIPCHK(hipSetDevice(t_state.cube_dev));
+            const hipError_t e = hipDeviceSynchronize();
+            (void)hipSetDevice(dev);
+            HIPCHK(e);
+            if (!diag_done(d, t_state.cube_seq)) return fail(BAT_EDEVICE, "the last launch has not run");
+        }
+        const double khz = std::max(t_state.cube_khz, 1);
+        t_state.info.kernel_ms = (double)(d[1] - d[0]) / khz;
+        t_state.info.total_ms = (double)(d[2] - d[0]) / khz;
+        *info = t_state.info;
+        return BAT_OK;
+    }
     HIPCHK(hipEventSynchronize(t_state.ev[3]));
     float k = 0.f, tot = 0.f;
     HIPCHK(hipEventElapsedTime(&k, t_state.ev[1], t_state.ev[2]));
@@ -3211,6 +3584,7 @@ int batched_impl(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_of
     HIPCHK(hipStreamSynchronize(st));
     bat_launch_info &I = t_state.info;
     memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
     I.vectors = vectors;
     I.specialised = n_gen < ents.size() ? 1 : 0;
     I.jit_ms = spec_jit_ms;

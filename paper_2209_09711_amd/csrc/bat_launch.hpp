@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bat_device.hpp"
+#include "bat_cube.hpp"
 
 namespace batk {
 
@@ -96,5 +97,10 @@ hipError_t valu_peak(hipStream_t st, unsigned blocks, bat::u32 iters, bat::u32 *
 hipError_t finalize(hipStream_t st, const double *res, const bat::u64 *count, const int *status,
                     const unsigned char *cb_of_arc, bat::u32 m, bool grad, double *R, bat::u64 *cnt, double *dRdp,
                     double *T1, double *T0, int *status_out);
+
+// ---- sub-cube sweeps (bat_cube.hip): blocks of `waves` wavefronts
+constexpr int kCubeMaxBits = 32;  // counter bits of the ahead-of-time kernels
+hipError_t cube_sweep(hipStream_t st, unsigned blocks, int waves, const bat::CubeParams &P);
+hipError_t cube_finish(hipStream_t st, unsigned blocks, const bat::CubeParams &P);
 
 }  // namespace batk

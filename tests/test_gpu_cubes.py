@@ -1,0 +1,120 @@
+"""The sub-cube sweep (whole sweeps that decide and add connected cubes of
+vectors as one) against the oracle and the frontier DP, at the sizes where
+its split changes: fewer arcs than a word, one lane, one and several work
+items, each number of levels, items shared by several wavefronts.  Counts
+are exact; R within 2e-15 relative (products of at most 30 factors and
+compensated sums: about 30 roundings of 1.1e-16, met by the frontier DP's
+own plain sums).
+"""
+import contextlib
+
+import numpy as np
+import pytest
+
+import bat_workloads as W
+import oracle
+from oracle import frontier_dp
+
+pytestmark = pytest.mark.gpu
+
+REL = 4e-15
+
+
+def _B():
+    import paper_2209_09711_amd as B
+    return B
+
+
+@contextlib.contextmanager
+def options(**kw):
+    B = _B()
+    old = {k: B.bat_get_option(k) for k in kw}
+    try:
+        for k, v in kw.items():
+            B.bat_set_option(k, v)
+        yield
+    finally:
+        for k, v in old.items():
+            B.bat_set_option(k, v)
+
+
+def _digraph(n, m, seed):
+    rng = np.random.default_rng(seed)
+    arcs = [tuple(int(x) for x in rng.choice(n, 2, replace=False)) for _ in range(m)]
+    return W.Network(f"di{n}_{m}", n, arcs, 0, n - 1, rng.uniform(0.3, 0.95, m))
+
+
+def _nets():
+    out = [(W.bridge(0.9), False), (W.figure1(), False), (W.parallel(3, [0.2, 0.5, 0.7]), False),
+           (W.grid(2, 4, p=np.linspace(0.5, 0.95, 10)), False), (W.grid(3, 4, p=np.linspace(0.4, 0.98, 17)), False)]
+    for n, m in [(2, 1), (4, 4), (6, 10), (7, 11), (7, 12), (8, 15), (9, 16), (10, 17), (11, 21), (12, 22)]:
+        out.append((W.random_connected(n, m, seed=40 + m, p_lo=0.2, p_hi=0.99), False))
+    for k in range(3):
+        out.append((W.random_multigraph(5, 11 + k, seed=60 + k), False))
+        out.append((_digraph(8, 14 + 2 * k, 70 + k), True))
+    return out
+
+
+@pytest.mark.parametrize("levels", [1, 2, 3])
+@pytest.mark.parametrize("split", [1, 3, 16])
+def test_cubes_vs_oracle(levels, split):
+    B = _B()
+    with options(BAT_CUBES=1, BAT_CUBE_LEVELS=levels, BAT_CUBE_SPLIT=split):
+        for net, directed in _nets():
+            print("cubes", levels, split, net.name, net.n, net.m, flush=True)
+            R, cnt = B.bat_reliability_ex(net.n, net.arcs, net.p, net.s, net.t, directed=directed)
+            li = B.bat_last_launch()
+            o = oracle.reliability(net.n, net.arcs, net.p, net.s, net.t, directed=directed)
+            assert li.perm == 5 and 0.0 < li.kernel_ms <= li.total_ms
+            assert cnt == o.count, net.name
+            assert abs(R - o.sum) <= REL * o.sum, (net.name, R, o.sum)
+
+
+@pytest.mark.parametrize("n,m,seed", [(13, 26, 3), (14, 27, 4), (16, 29, 5), (11, 30, 6), (18, 31, 7)])
+def test_cubes_larger_vs_frontier_dp(n, m, seed):
+    """The default launch (two levels from 24 relevant arcs on, several work
+    items per block), twice with the same bits."""
+    B = _B()
+    net = W.random_connected(n, m, seed=seed, p_lo=0.5, p_hi=0.99)
+    print("cubes", net.name, flush=True)
+    R, cnt = B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
+    assert B.bat_last_launch().perm == 5
+    assert (R, cnt) == B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
+    Rd, cd = frontier_dp.reliability(net.n, net.arcs, net.p, net.s, net.t)
+    assert cnt == cd and abs(R - Rd) <= REL * Rd
+
+
+def test_cubes_exact_probabilities():
+    """p = 1/2 gives count 2^-m to the bit; p of 0 and 1 stay exact."""
+    B = _B()
+    net = W.random_connected(13, 25, seed=9)
+    with options(BAT_CUBES=1, BAT_CUBE_LEVELS=3):
+        R, cnt = B.bat_reliability(net.n, net.arcs, np.full(net.m, 0.5), net.s, net.t)
+        assert R == cnt * 2.0 ** -net.m
+        assert B.bat_reliability(net.n, net.arcs, np.ones(net.m), net.s, net.t) == (1.0, cnt)
+        assert B.bat_reliability(net.n, net.arcs, np.zeros(net.m), net.s, net.t) == (0.0, cnt)
+
+
+def test_cubes_checkpointed(tmp_path):
+    """A sub-cube sweep in parts: resumed bitwise the uninterrupted one, and
+    a file whose work items this library does not cut is refused."""
+    B = _B()
+    net = W.random_connected(12, 24, seed=21, p_lo=0.4, p_hi=0.99)
+    o = oracle.net_reliability(net)
+    with options(BAT_CUBES=1, BAT_CUBE_LEVELS=2):
+        args = (net.n, net.arcs, net.p, net.s, net.t, net.m - 3)
+        whole = B.bat_reliability_checkpointed(*args, None)
+        f = str(tmp_path / "c.ckpt")
+        assert B.bat_reliability_checkpointed(*args, f, max_chunks=3) is None
+        lines = open(f).read().splitlines()
+        assert lines[2] == "parts 8" and lines[3].startswith("launch order=5 ") and lines[4] == "done 3"
+        bad = str(tmp_path / "bad.ckpt")
+        for launch in (lines[3][:-1] + ("0" if lines[3][-1] != "0" else "1"), "launch order=5 items=80 chain=0",
+                       "launch order=5 items=7 chain=0 bits=0"):
+            open(bad, "w").write("\n".join(lines[:3] + [launch] + lines[4:]) + "\n")
+            with pytest.raises(B.BatError) as e:
+                B.bat_reliability_checkpointed(*args, bad)
+            assert e.value.code == B.BAT_EIO
+    # the file's launch holds when the options have changed since
+    assert B.bat_reliability_checkpointed(*args, f) == whole
+    assert whole[1] == o.count and abs(whole[0] - o.sum) <= REL * o.sum
