@@ -1,7 +1,8 @@
 """Build the HIP library in-tree: ``paper_2209_09711_amd/libbat_hip.so``.
 
-Steps: embed ``csrc/bat_device.hpp`` as a string literal (the source the
-library hands to hiprtc for graph-specialised kernels) with a digest of the
+Steps: embed ``csrc/bat_device.hpp`` and ``csrc/bat_cube.hpp`` as string
+literals (the source the library hands to hiprtc for graph-specialised
+kernels) with a digest of the
 ahead-of-time kernel sources, then compile the
 ahead-of-time kernels and the C ABI with hipcc for gfx950, and the compile
 helper ``bat_jitc`` (a host program the library runs to compile several
@@ -28,9 +29,11 @@ HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 
 def embed_device_source() -> str:
     import hashlib
-    src = open(os.path.join(CSRC, "bat_device.hpp")).read()
     delim = "BATDEV"
-    assert f"){delim}\"" not in src
+    srcs = {}
+    for f in ("bat_device.hpp", "bat_cube.hpp"):
+        srcs[f] = open(os.path.join(CSRC, f)).read()
+        assert f"){delim}\"" not in srcs[f]
     # digest of everything the ahead-of-time kernels are compiled from,
     # reported in each launch's kernel identity
     h = hashlib.sha256()
@@ -38,9 +41,11 @@ def embed_device_source() -> str:
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     out = os.path.join(CSRC, "bat_device_embed.inc")
-    text = ("// Generated by build.py from bat_device.hpp: the device template as text,\n"
-            "// compiled at run time by hiprtc for graph-specialised kernels.\n"
-            f"static const char kDeviceSource[] = R\"{delim}(\n{src}\n){delim}\";\n"
+    text = ("// Generated by build.py from bat_device.hpp and bat_cube.hpp: the device\n"
+            "// templates as text, compiled at run time by hiprtc for graph-specialised\n"
+            "// kernels.\n"
+            f"static const char kDeviceSource[] = R\"{delim}(\n{srcs['bat_device.hpp']}\n){delim}\";\n"
+            f"static const char kCubeSource[] = R\"{delim}(\n{srcs['bat_cube.hpp']}\n){delim}\";\n"
             f"static const char kAotKernelDigest[] = \"{h.hexdigest()[:32]}\";\n")
     if not os.path.exists(out) or open(out).read() != text:
         with open(out, "w") as f:

@@ -24,7 +24,7 @@ __global__ void __launch_bounds__(bat::kCubeWaves *bat::kWave) k_cube_fwd(bat::C
     __shared__ bat::CubeTables T;
     __shared__ bat::CubeWave W[bat::kCubeWaves];
     bat::CubeArgs *P = cube_args();
-    bat::cube_kernel(P, T, W, bat::CubeDyn{P});
+    bat::cube_kernel(P, T, W, bat::CubeDyn{P, 0u});
 }
 
 constexpr int kFinishThreads = 1024;

@@ -39,6 +39,7 @@ constexpr int kCubeSlots = 64;                    // words of a closure (ahead-o
 constexpr int kCubeSteps = 640;                   // steps of all closures, padded
 constexpr int kCubeQueue = 1024;                  // prefixes queued at a time (a level can make 2048)
 constexpr int kCubeWaves = 4;                     // wavefronts per block
+constexpr int kCubeUnits = 64;                    // most units of work a block takes
 
 struct alignas(16) double2_t {
     double x, y;
@@ -60,7 +61,8 @@ struct CubeParams {
     u64 item_base;
     u32 m, M;                 // arcs, arcs enumerated (counter bits)
     u32 levels, lane_bits;
-    u32 split;                // wavefronts sharing an item (each takes every split-th round of 64 prefixes)
+    u32 split;                // units an item is split into (each takes every split-th round of 64 prefixes)
+    u32 units;                // units per block
     u32 fused;                // one block: it writes the results itself
     double2_t *part;          // [blocks] double-double partials
     u64 *pcount;              // [blocks]
@@ -198,11 +200,18 @@ __device__ __forceinline__ void cube_enqueue(unsigned short *q, u32 U, u32 e, u3
 
 struct CubeDyn {
     CubeArgs *P;
+    u32 base;  // the item's counter bits
 
-    // c: the prefix's counter bits (free arcs' bits: set when up, as a
-    // digraph's closures use them)
-    __device__ __forceinline__ u32 close(u32 pi, u32 c, u32, bool live) const
+    __device__ __forceinline__ u32 levels() const { return P->levels; }
+    __device__ __forceinline__ u32 lane_bits() const { return P->lane_bits; }
+    __device__ __forceinline__ u32 arcs() const { return P->M; }
+    __device__ __forceinline__ void item(u64 block) { base = (u32)(block << (kCubeGroup * P->levels + P->lane_bits)); }
+
+    // rel: the prefix's counter bits within the item
+    __device__ __forceinline__ u32 close(u32 pi, u32 rel, bool live) const
     {
+        // free arcs' bits: set when up, as a digraph's closures use them
+        const u32 c = base | rel | ((pi & 1u) ? (1u << (kCubeGroup * ((pi + 1u) >> 1))) - 1u : 0u);
         const u32 result = P->prog[pi].result;
         if (result >= (u32)kCubeSlots) return live && result == kCubeAlways ? ~0u : 0u;
         const __attribute__((address_space(4))) u32 *steps = P->step;
@@ -254,6 +263,61 @@ struct CubeDyn {
 #undef BAT_CUBE_STEP
 #undef BAT_CUBE_MASK
 
+// Graph known at compile time (hiprtc): G holds the plan's sizes and, as
+// G::run<k>(r), the steps of closure k on an array that becomes registers.
+// The masks of the item's arcs are uniform and stay scalar.
+template <class G>
+struct CubeStatic {
+    u32 um[G::M > G::REL ? G::M - G::REL : 1];  // masks of the item's arcs
+
+    __device__ __forceinline__ u32 levels() const { return G::LEVELS; }
+    __device__ __forceinline__ u32 lane_bits() const { return G::LANE_BITS; }
+    __device__ __forceinline__ u32 arcs() const { return G::M; }
+    __device__ __forceinline__ void item(u64 block)
+    {
+#pragma unroll
+        for (int k = 0; k < G::M - G::REL; ++k) {
+            um[k] = 0u - ((u32)(block >> k) & 1u);
+            // opaque: a mask seen as all or nothing would turn each AND-OR
+            // into a select and an OR
+            asm volatile("" : "+s"(um[k]));
+        }
+    }
+
+    template <u32 K>
+    __device__ __forceinline__ u32 run(u32 rel, bool live) const
+    {
+        constexpr int word = kCubeGroup * (int)((K + 1u) / 2u);
+        if constexpr (K >= 2u * G::LEVELS - 1u || G::RESULT[K] == kCubeNever) {
+            return 0u;
+        } else if constexpr (G::RESULT[K] == kCubeAlways) {
+            return live ? ~0u : 0u;
+        } else {
+            u32 r[G::SLOTS];
+#pragma unroll
+            for (int c = 0; c < G::M; ++c) {
+                if (c < word) r[c] = (K & 1u) ? ~0u : 0u;
+                else if (c < word + kCubeGroup) r[c] = slice_pattern(c - word);
+                else if (c < G::REL) {
+                    r[c] = (u32)__builtin_amdgcn_sbfe((int)rel, c, 1);
+                    asm volatile("" : "+v"(r[c]));
+                } else r[c] = um[c - G::REL];
+            }
+            G::template steps<K>(r);
+            return live ? r[G::RESULT[K]] : 0u;
+        }
+    }
+
+    __device__ __forceinline__ u32 close(u32 pi, u32 rel, bool live) const
+    {
+        return pi == 0u   ? run<0>(rel, live)
+               : pi == 1u ? run<1>(rel, live)
+               : pi == 2u ? run<2>(rel, live)
+               : pi == 3u ? run<3>(rel, live)
+                          : run<4>(rel, live);
+    }
+};
+
 // One wavefront's share of the sweep.
 template <class Clo>
 struct CubeSweep {
@@ -262,7 +326,6 @@ struct CubeSweep {
     CubeWave &W;
     Clo clo;
     u32 lane;
-    u64 base;          // the item's counter bits
     double hi, lo;     // sum of the probabilities
     u64 cnt;
 
@@ -281,19 +344,13 @@ struct CubeSweep {
         lo += e;
     }
 
-    __device__ __forceinline__ u32 close(u32 pi, u32 rel, u32 fill, bool live)
-    {
-        const u64 c = base | rel | fill;
-        return clo.close(pi, (u32)c, (u32)(c >> 32), live);
-    }
-
     // The cubes of the prefix's word: added where they connect for certain
     // (when `mine`), returned where they are undecided.
     __device__ __forceinline__ u32 classify(u32 level, u32 rel, double q, bool live, bool mine)
     {
-        const u32 up = close(2u * level - 1u, rel, (1u << (kCubeGroup * level)) - 1u, live);
+        const u32 up = clo.close(2u * level - 1u, rel, live);
         if (__ballot(up != 0u) == 0ull) return 0u;
-        const u32 down = close(2u * level, rel, 0u, live && up != 0u);
+        const u32 down = clo.close(2u * level, rel, live && up != 0u);
         if (mine) add(level, q, down);
         return up & ~down;
     }
@@ -316,7 +373,7 @@ struct CubeSweep {
                 const bool live = i < end;
                 const u32 x = W.queue[1][(live ? i : end - 1u) - w0], own = x >> 5;
                 const u32 rel = (u32)W.from[own] << (2 * kCubeGroup) | (x & 31u) << kCubeGroup;
-                const u32 V = close(0u, rel, 0u, live);
+                const u32 V = clo.close(0u, rel, live);
                 add(0u, W.qp[1][own] * T.q5[1][x & 31u], V);
             }
             wave_lds_sync();
@@ -325,9 +382,9 @@ struct CubeSweep {
 
     __device__ __forceinline__ void item(u64 block, u32 sub)
     {
-        const u32 levels = P->levels, lane_bits = P->lane_bits, split = P->split, M = P->M;
+        const u32 levels = clo.levels(), lane_bits = clo.lane_bits(), split = P->split, M = clo.arcs();
         const u32 rb = kCubeGroup * levels + lane_bits;
-        base = block << rb;
+        clo.item(block);
         const bool live = (lane >> lane_bits) == 0u;
         // the item's probability: one factor per lane, multiplied across
         double q = lane + rb < M ? cube_q(T, M, rb + lane, (u32)(block >> lane) & 1u) : 1.0;
@@ -335,7 +392,7 @@ struct CubeSweep {
         for (int off = kWave / 2; off >= 1; off >>= 1) q *= shfl_xor_d(q, off);
         q *= T.ql[lane];
         if (levels == 1u) {
-            u32 V = close(0u, lane << kCubeGroup, 0u, live);
+            u32 V = clo.close(0u, lane << kCubeGroup, live);
             if (M < 5u) V &= (1u << (1u << M)) - 1u;  // bits past the last arc
             add(0u, q, V);
             return;
@@ -392,34 +449,52 @@ __device__ __forceinline__ void cube_results(CubeArgs *P, double hi, double lo, 
     if (P->diag) __hip_atomic_store(P->diag + 3, P->seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A block takes `units` consecutive units; its wavefronts take the next one
+// from the block's own counter, so that one wavefront's long unit does not
+// leave the others waiting at the end (units differ widely: with a fixed
+// unit per wavefront 70% of the resident wavefront cycles of the 5x5 grid
+// were spent waiting, and it took 17.9 ms against 12.0 ms with 32 units per
+// block; later 8.65 ms with 32, 7.9 ms with 64, 8.6 ms with 128, whose
+// blocks are too few for an even end; 8 and 16 wavefronts per block: 8.7
+// and 9.7 ms).  Each unit's sum has its own place and they
+// are added in unit order, whichever wavefront formed them.
 template <class Clo>
 __device__ __forceinline__ void cube_kernel(CubeArgs *P, CubeTables &T, CubeWave *Ws, Clo clo)
 {
-    __shared__ double sh[kCubeWaves][2];
-    __shared__ u64 sc[kCubeWaves];
+    __shared__ double2_t su[kCubeUnits];
+    __shared__ u64 sc[kCubeUnits];
+    __shared__ u32 next;
     if (blockIdx.x == 0 && threadIdx.x == 0) cube_clock(P, 0);
+    if (threadIdx.x == 0) next = 0u;
     cube_tables(P, T);
     const u32 lane = threadIdx.x & (kWave - 1);
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const u32 waves = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
-    CubeSweep<Clo> S{P, T, Ws[wave], clo, lane, 0ull, 0.0, 0.0, 0ull};
-    const u64 w = (u64)blockIdx.x * waves + wave;
-    const u32 split = P->split;
-    const u64 it = w / split;
-    if (it < P->n_items) S.item(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
-    wave_sum_dd(S.hi, S.lo);
-    const u64 c = wave_sum_u64(S.cnt);
-    if (lane == 0) {
-        sh[wave][0] = S.hi;
-        sh[wave][1] = S.lo;
-        sc[wave] = c;
+    const u32 split = P->split, units = P->units;
+    const u64 first = (u64)blockIdx.x * units, all = P->n_items * split;
+    for (;;) {
+        // Every lane adds 1 (compiled to one add of 64): under an "if lane 0"
+        // the compiler joined this branch to the one that ends the loop
+        // body, sent the other lanes round the loop past the atomic and
+        // never ended it.
+        __builtin_amdgcn_wave_barrier();
+        const u32 k = __builtin_amdgcn_readfirstlane(atomicAdd(&next, 1u)) / kWave;
+        if (k >= units) break;
+        CubeSweep<Clo> S{P, T, Ws[wave], clo, lane, 0.0, 0.0, 0ull};
+        const u64 w = first + k, it = w / split;
+        if (w < all) S.item(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
+        wave_sum_dd(S.hi, S.lo);
+        const u64 c = wave_sum_u64(S.cnt);
+        if (lane == 0) {
+            su[k] = {S.hi, S.lo};
+            sc[k] = c;
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double h = 0.0, l = 0.0;
         u64 n = 0;
-        for (u32 k = 0; k < waves; ++k) {
-            dd_add(h, l, sh[k][0], sh[k][1]);
+        for (u32 k = 0; k < units; ++k) {
+            dd_add(h, l, su[k].x, su[k].y);
             n += sc[k];
         }
         if (P->fused) {

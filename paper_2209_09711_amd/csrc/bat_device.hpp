@@ -69,6 +69,16 @@ constexpr int kQLOM = kQLM + 6 * 64;         // [8][256] Q_lo without g bit b
 constexpr int kTablesFwd = kTBG;             // doubles the forward kernel needs
 constexpr int kTables = kQLOM + 8 * 256;     // whole block
 
+#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC_RTC__)
+// (a & b) | c.  v_bitop3_b32 issues at the full rate (1.7 wave64
+// instructions per CU and clock measured), v_and_or_b32, which the compiler
+// picks for the plain expression, at half of it (0.95).
+__device__ __forceinline__ u32 and_or(u32 a, u32 b, u32 c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA);
+}
+#endif
+
 // The 32-bit word in which slice arc cb works: bit j set iff bit cb of j.
 __host__ __device__ constexpr u32 slice_pattern(int cb)
 {

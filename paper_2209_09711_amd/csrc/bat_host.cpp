@@ -1701,8 +1701,9 @@ bool cubes_wanted(bool grad)
 // closure deep, so the shortest while the device holds its 2^(M - 11)
 // wavefronts (24 arcs: 16 us against 12 us with two levels; 22 arcs: 8 us
 // against 10 us).  Three levels decide less (30 arcs: 42 us against 34 us)
-// but run longer chains of closures per wavefront; they win from 32 arcs on
-// (0.60 ms against 0.56 ms there).
+// but run longer chains of closures per wavefront; they win from 33 arcs on
+// (specialised: 32 arcs 126 us against 94 us, 33 arcs 110 us against 131 us,
+// 35 arcs 0.14 ms against 0.39 ms).
 void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed, batcube::CubePlan &C,
                 int levels = 0)
 {
@@ -1712,7 +1713,7 @@ void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t,
     if (levels <= 0) levels = (int)opts().cube_levels.load();
     int M = 0;
     for (int32_t i = 0; i < m; ++i) M += rel[i] ? 1 : 0;
-    if (levels <= 0) levels = M <= 23 ? 1 : M <= 31 ? 2 : 3;
+    if (levels <= 0) levels = M <= 23 ? 1 : M <= 32 ? 2 : 3;
     batcube::make_cube_plan(n, m, arcs, rel, s, t, directed, levels, C);
 }
 
@@ -1722,7 +1723,7 @@ void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t,
 u64 cube_items(const batcube::CubePlan &C) { return 1ull << std::max(0, C.M - C.rel_bits()); }
 
 int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
-                bat::CubeParams &K, unsigned &blocks, int &waves, u64 parts = 1, u64 part = 0)
+                bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, u64 parts = 1, u64 part = 0)
 {
     memset(&K, 0, sizeof K);
     K.m = (u32)C.m;
@@ -1733,18 +1734,27 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     K.item_mul = 0x9E3779B97F4A7C15ull * parts;  // odd times parts: consecutive items lie apart
     K.item_mask = cube_items(C) - 1;
     K.item_base = part;
-    // a few wavefronts share an item while the items alone would leave the
-    // device partly empty (24 arcs, 256 items: 12.4 us shared by 4, 15.3 us
-    // alone; 28 arcs, 4096 items: 55 us shared by 4, 62 us alone)
+    // Items are split into units while there are few: with two levels only
+    // to fill the device (24 arcs, 256 items: 12.4 us in 4 units each, 15.3
+    // us whole; 30 arcs, 16384 items: 43 us in 4, 33 us whole, as every unit
+    // decides the item's first word again); with three levels, where that
+    // is a small part, until the long items no longer set the end (36 arcs,
+    // 16384 items: 0.60 ms in 4, 1.02 ms whole; 40 arcs, 524288 items: 11.9
+    // ms in 4, 9.1 ms whole)
     u64 split = 1;
     if (opts().cube_split.load() > 0) split = (u64)opts().cube_split.load();
     else
-        while (C.levels > 1 && split < 16 && K.n_items * split < (u64)D.cus * 16) split *= 2;
+        while (C.levels > 1 && split < (C.levels == 2 ? 16 : 4) && K.n_items * split < (u64)D.cus * (C.levels == 2 ? 16 : 256))
+            split *= 2;
     if (C.levels == 1) split = 1;
     K.split = (u32)split;
     const u64 w = K.n_items * split;
     waves = (int)std::min<u64>(w, bat::kCubeWaves);
-    const u64 nb = (w + waves - 1) / waves;
+    // units per block: as many as leave every CU some 16 blocks
+    u64 units = (u64)waves;
+    while (units < bat::kCubeUnits && w / (2 * units) >= (u64)D.cus * 16) units *= 2;
+    K.units = (u32)units;
+    const u64 nb = (w + units - 1) / units;
     if (nb > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)w);
     blocks = (unsigned)nb;
     K.fused = nb == 1 ? 1u : 0u;
@@ -1752,7 +1762,7 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     if (p_host) memcpy(K.p, p_host, sizeof(double) * C.m);
     for (int c = 0; c < C.M; ++c) K.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
     u32 at = 0;
-    for (int k = 0; k < 2 * C.levels - 1; ++k) {
+    for (int k = 0; !jit && k < 2 * C.levels - 1; ++k) {
         const batcube::Program &pr = C.prog[k];
         bat::CubeProg &q = K.prog[k];
         q.first = at;
@@ -1773,9 +1783,18 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     return BAT_OK;
 }
 
-// Whether the ahead-of-time kernel can run the plan.
-bool cube_fits(const batcube::CubePlan &C)
+// Whether the plan runs as a graph-specialised kernel: by the rule of the
+// plain sweep (a compile takes about half a second, once per graph).
+bool cube_jit(const batcube::CubePlan &C)
 {
+    const int64_t jit = opts().jit.load();
+    return jit == 1 || (jit == 2 && C.m >= 32);
+}
+
+// Whether a kernel can run the plan (aot: the ahead-of-time one).
+bool cube_fits(const batcube::CubePlan &C, bool aot = false)
+{
+    if (!aot && cube_jit(C)) return true;
     return C.M <= batk::kCubeMaxBits && C.slots <= bat::kCubeSlots && C.steps + 8 * bat::kCubeProgs <= bat::kCubeSteps;
 }
 
@@ -1788,6 +1807,71 @@ void cube_parts(bat::CubeParams &K, unsigned blocks, char *ws)
     K.pcount = (u64 *)(ws + 16 * (size_t)blocks);
 }
 
+// The hiprtc source of the sweep specialised for a plan.  with_arcs: also
+// the arcs at the counter bits, in a comment (the code does not depend on
+// them).
+std::string cube_source(const batcube::CubePlan &C, bool with_arcs = false)
+{
+    std::string g = "\nnamespace bat {\nstruct JitCube {\n";
+    if (with_arcs) {
+        g += "  // arcs at counter bits 0, 1, ...:";
+        for (int a : C.arc_of_bit) g += " " + std::to_string(a);
+        g += "\n";
+    }
+    auto num = [&](const char *k, int v) { g += std::string("  static constexpr int ") + k + " = " + std::to_string(v) + ";\n"; };
+    num("M", C.M);
+    num("REL", C.rel_bits());
+    num("SLOTS", std::max(C.slots, 1));
+    g += "  static constexpr u32 LEVELS = " + std::to_string(C.levels) + "u, LANE_BITS = " + std::to_string(C.lane_bits) +
+         "u;\n  static constexpr u32 RESULT[5] = {";
+    for (int k = 0; k < bat::kCubeProgs; ++k) {
+        const int r = k < 2 * C.levels - 1 ? C.prog[k].result : -1;
+        g += (k ? ", " : "") + std::to_string(r == -1 ? bat::kCubeNever : r == -2 ? bat::kCubeAlways : (u32)r) + "u";
+    }
+    g += "};\n  template <u32 K> __device__ static __forceinline__ void steps(u32 *r) {\n";
+    for (int k = 0; k < 2 * C.levels - 1; ++k) {
+        g += "    if constexpr (K == " + std::to_string(k) + "u) {\n";
+        for (const batcube::Step &x : C.prog[k].step)
+            g += "      r[" + std::to_string(x.d) +
+                 (x.assign ? "] = r[" + std::to_string(x.a) + "] & r[" + std::to_string(x.b) + "];\n"
+                           : "] = and_or(r[" + std::to_string(x.a) + "], r[" + std::to_string(x.b) + "], r[" +
+                                 std::to_string(x.d) + "]);\n");
+        g += "    }\n";
+    }
+    g += "  }\n};\n}\n"
+         "extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) "
+         "bat_cube_jit(bat::CubeParams) {\n"
+         "  __shared__ bat::CubeTables T; __shared__ bat::CubeWave W[bat::kCubeWaves];\n"
+         "  bat::cube_kernel((bat::CubeArgs *)__builtin_amdgcn_kernarg_segment_ptr(), T, W, bat::CubeStatic<bat::JitCube>{});\n}\n";
+    return std::string(kDeviceSource) + kCubeSource + g;
+}
+
+// The specialised kernel of a plan, by the bytes its source is made from.
+int cube_jit_get(const batcube::CubePlan &C, const DeviceInfo &D, hipFunction_t &fn, double &jit_ms, uint64_t &id)
+{
+    std::string key = std::to_string(D.id) + " cube " + std::to_string(C.M) + " " + std::to_string(C.levels) + " " +
+                      std::to_string(C.lane_bits) + " " + std::to_string(C.slots) + ":";
+    for (int k = 0; k < 2 * C.levels - 1; ++k) {
+        key += " " + std::to_string(C.prog[k].result) + " ";
+        for (const batcube::Step &x : C.prog[k].step) {
+            const unsigned char b[4] = {(unsigned char)x.a, (unsigned char)x.b, (unsigned char)x.d,
+                                        (unsigned char)(x.assign ? 1 : 0)};
+            key.append((const char *)b, sizeof b);
+        }
+        key += ";";
+    }
+    {
+        std::lock_guard<std::mutex> lk(g_jit_mu);
+        auto it = g_jit.find(key);
+        if (it != g_jit.end()) {
+            fn = it->second.fn;
+            id = it->second.id;
+            return BAT_OK;
+        }
+    }
+    return jit_load(D, key, cube_source(C), "bat_cube_jit", fn, jit_ms, id);
+}
+
 void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int waves)
 {
     bat_launch_info &I = t_state.info;
@@ -1797,7 +1881,6 @@ void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int 
     I.chunk_log2 = std::max(0, C.rel_bits() + (C.m - C.M) - bat::kWordBits);
     I.n_chunks = (int32_t)std::min<u64>(K.n_items, 0x7fffffff);
     I.relaxations = C.M;
-    I.kernel_id = aot_kernel_id("k_cube_fwd", 0, false);
     I.perm = kPermInfluence;
     I.check_every = 1;
     I.item_order = 1;
@@ -1808,16 +1891,31 @@ void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int 
 // Queue the sweep (and its reduction) on `stream`; K's result pointers set.
 // No event is recorded: the kernels report their clocks themselves (four
 // event records took a third of a small call's time).
-int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, const DeviceInfo &D,
-               hipStream_t stream)
+int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, bool jit,
+               const DeviceInfo &D, hipStream_t stream)
 {
+    hipFunction_t fn = nullptr;
+    double jit_ms = 0.0;
+    uint64_t kid = aot_kernel_id("k_cube_fwd", 0, false);
+    if (jit) {
+        int rc = cube_jit_get(C, D, fn, jit_ms, kid);
+        if (rc) return rc;
+    }
     u64 *slot = nullptr;
     int rc = diag_next(stream, slot, K.seq);
     if (rc) return rc;
     K.diag = slot;
-    HIPCHK(batk::cube_sweep(stream, blocks, waves, K));
+    if (jit) {
+        void *args[] = {&K};
+        HIPCHK(hipModuleLaunchKernel(fn, blocks, 1, 1, (unsigned)(waves * bat::kWave), 1, 1, 0, stream, args, nullptr));
+    } else {
+        HIPCHK(batk::cube_sweep(stream, blocks, waves, K));
+    }
     if (!K.fused) HIPCHK(batk::cube_finish(stream, blocks, K));
     cube_launch_info(C, K, waves);
+    t_state.info.specialised = jit ? 1 : 0;
+    t_state.info.jit_ms = jit_ms;
+    t_state.info.kernel_id = kid;
     t_state.have_launch = slot != nullptr;
     t_state.cube_seq = K.seq;
     t_state.cube_dev = D.id;
@@ -1852,7 +1950,8 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     bat::CubeParams K;
     unsigned blocks = 0;
     int waves = 0;
-    rc = cube_params(C, p, nullptr, D, K, blocks, waves, parts, part);
+    const bool jit = cube_jit(C);
+    rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, parts, part);
     if (rc) return rc;
     Scratch *S = nullptr;
     rc = scratch_reserve(D.id, stream, cube_part_bytes(K, blocks), 64, S);
@@ -1860,7 +1959,7 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     cube_parts(K, blocks, S->dev);
     K.res = (double *)S->host;
     K.count = (u64 *)(S->host + 16);
-    rc = cube_queue(C, K, blocks, waves, D, stream);
+    rc = cube_queue(C, K, blocks, waves, jit, D, stream);
     if (!rc) rc = cube_wait(K, stream);
     if (rc) {
         (void)hipStreamSynchronize(stream);
@@ -1879,7 +1978,8 @@ int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo
     bat::CubeParams K;
     unsigned blocks = 0;
     int waves = 0;
-    int rc = cube_params(C, nullptr, p_dev, D, K, blocks, waves);
+    const bool jit = !ws && cube_jit(C);  // (a fixed workspace: no module is loaded)
+    int rc = cube_params(C, nullptr, p_dev, D, K, blocks, waves, jit);
     if (rc) return rc;
     const size_t need = cube_part_bytes(K, blocks);
     void *own = nullptr;
@@ -1893,7 +1993,7 @@ int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo
     K.R = R;
     K.count = count;
     K.status = status;
-    rc = cube_queue(C, K, blocks, waves, D, stream);
+    rc = cube_queue(C, K, blocks, waves, jit, D, stream);
     if (own) {
         const hipError_t e = hipFreeAsync(own, stream);
         if (!rc) HIPCHK(e);
@@ -2884,7 +2984,7 @@ int bat_reliability_noalloc(int32_t n, int32_t m, const bat_arc *arcs, const dou
     if (cubes_wanted(false)) {
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, false, C);
-        if (cube_fits(C))
+        if (cube_fits(C, true))
             return cube_async(C, p_dev, X.D, st, R_dev, (u64 *)count_dev, status_dev, ws, kNoAllocScratchBytes);
     }
     Request rq{};
@@ -3006,14 +3106,19 @@ int bat_jit_source(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t
     if (flags & ~(uint32_t)BAT_DIRECTED) return fail(BAT_EINVAL, "unknown flags 0x%x", flags);
     int rc = validate(n, m, arcs, nullptr, s, t);
     if (rc) return rc;
-    if (perm < 0 || perm >= kPermKinds) return fail(BAT_EINVAL, "perm %d outside [0, %d)", perm, kPermKinds);
+    if ((perm < 0 || perm >= kPermKinds) && perm != kPermInfluence)
+        return fail(BAT_EINVAL, "perm %d outside [0, %d)", perm, kPermKinds);
+    if (perm == kPermInfluence && grad != 0) return fail(BAT_EINVAL, "no such sub-cube sweep");
     if (grad < -batk::kBatchMaxP || grad > 1) return fail(BAT_EINVAL, "grad %d outside [-%d, 1]", grad, batk::kBatchMaxP);
     if (grad < 0 && (flags & BAT_DIRECTED)) return fail(BAT_EINVAL, "the batched sweep is undirected");
     Plan P;
-    make_plan(n, m, arcs, s, t, P, perm, (flags & BAT_DIRECTED) != 0);
+    batcube::CubePlan C;
+    if (perm == kPermInfluence) make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C);
+    else make_plan(n, m, arcs, s, t, P, perm, (flags & BAT_DIRECTED) != 0);
     Options &O = opts();
     const std::string src =
-        grad < 0 ? jit_source(P, false, jit_shape(false, 4, 0, 0, 1), -grad)
+        perm == kPermInfluence ? cube_source(C, true)
+        : grad < 0 ? jit_source(P, false, jit_shape(false, 4, 0, 0, 1), -grad)
                  : jit_source(P, grad != 0,
                               jit_shape(grad != 0, (int)O.block_waves.load(), (int)O.super_restart.load(),
                                         (int)O.simd_waves.load(), (int)O.keep_bottom.load()));

@@ -84,6 +84,35 @@ def test_cubes_larger_vs_frontier_dp(n, m, seed):
     assert cnt == cd and abs(R - Rd) <= REL * Rd
 
 
+@pytest.mark.parametrize("levels", [1, 2, 3])
+def test_cubes_specialised(levels):
+    """The graph-specialised build against the oracle, and as every other
+    launch: the same count, R within rounding."""
+    B = _B()
+    nets = [_nets()[k] for k in (0, 3, 4, 9, 12, 14, 16, 18)]
+    for net, directed in nets:
+        print("specialised cubes", levels, net.name, flush=True)
+        with options(BAT_CUBES=1, BAT_JIT=1, BAT_CUBE_LEVELS=levels):
+            R, cnt = B.bat_reliability_ex(net.n, net.arcs, net.p, net.s, net.t, directed=directed)
+            assert B.bat_last_launch().specialised == 1
+        o = oracle.reliability(net.n, net.arcs, net.p, net.s, net.t, directed=directed)
+        assert cnt == o.count and abs(R - o.sum) <= REL * o.sum, net.name
+
+
+@pytest.mark.parametrize("n,m", [(12, 32), (16, 33), (26, 38), (40, 44)])
+def test_cubes_specialised_larger(n, m):
+    """2^32 vectors and more (three levels from 33 relevant arcs on; more
+    than 32 counter bits; more nodes than a 32-bit node set)."""
+    B = _B()
+    net = W.random_connected(n, m, seed=m, p_lo=0.6, p_hi=0.99)
+    print("specialised cubes", net.name, flush=True)
+    R, cnt = B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
+    li = B.bat_last_launch()
+    assert li.specialised == 1 and li.perm == 5
+    Rd, cd = frontier_dp.reliability(net.n, net.arcs, net.p, net.s, net.t)
+    assert cnt == cd and abs(R - Rd) <= REL * Rd
+
+
 def test_cubes_exact_probabilities():
     """p = 1/2 gives count 2^-m to the bit; p of 0 and 1 stay exact."""
     B = _B()
