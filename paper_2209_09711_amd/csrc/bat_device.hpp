@@ -69,15 +69,17 @@ constexpr int kQLOM = kQLM + 6 * 64;         // [8][256] Q_lo without g bit b
 constexpr int kTablesFwd = kTBG;             // doubles the forward kernel needs
 constexpr int kTables = kQLOM + 8 * 256;     // whole block
 
-#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC_RTC__)
 // (a & b) | c.  v_bitop3_b32 issues at the full rate (1.7 wave64
 // instructions per CU and clock measured), v_and_or_b32, which the compiler
 // picks for the plain expression, at half of it (0.95).
 __device__ __forceinline__ u32 and_or(u32 a, u32 b, u32 c)
 {
+#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC_RTC__)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA);
-}
+#else
+    return (a & b) | c;  // hipcc's host pass, which parses this and has no such builtin
 #endif
+}
 
 // The 32-bit word in which slice arc cb works: bit j set iff bit cb of j.
 __host__ __device__ constexpr u32 slice_pattern(int cb)
@@ -172,8 +174,8 @@ __device__ __forceinline__ u32 edge_mask(u64 c_lo, u64 c_hi, u64 g, u32 lane)
 __device__ __forceinline__ void relax(u32 &ru, u32 &rv, u32 w)
 {
     u32 a = ru, b = rv;
-    rv = b | (a & w);
-    ru = a | (b & w);
+    rv = and_or(a, w, b);
+    ru = and_or(b, w, a);
 }
 
 // ----------------------------------------------------------- closures
@@ -368,8 +370,8 @@ struct StaticClosure {
     __device__ __forceinline__ void rel(int k)
     {
         if (G::RU[k] == G::S) r[G::RV[k]] |= W[k];
-        else if (one_way(k) == 1) r[G::RV[k]] |= r[G::RU[k]] & W[k];
-        else if (one_way(k) == 2) r[G::RU[k]] |= r[G::RV[k]] & W[k];
+        else if (one_way(k) == 1) r[G::RV[k]] = and_or(r[G::RU[k]], W[k], r[G::RV[k]]);
+        else if (one_way(k) == 2) r[G::RU[k]] = and_or(r[G::RV[k]], W[k], r[G::RU[k]]);
         else relax(r[G::RU[k]], r[G::RV[k]], W[k]);
     }
 
@@ -1434,16 +1436,16 @@ __device__ __forceinline__ void ms_closure(const u32 (&W)[G::M], u32 src, u32 ne
 #pragma unroll
         for (int j = 0; j < G::M; ++j) {
             if (j == E) continue;
-            r[G::NV[j]] |= r[G::NU[j]] & W[j];
-            if (!G::DIR) r[G::NU[j]] |= r[G::NV[j]] & W[j];
+            r[G::NV[j]] = and_or(r[G::NU[j]], W[j], r[G::NV[j]]);
+            if (!G::DIR) r[G::NU[j]] = and_or(r[G::NV[j]], W[j], r[G::NU[j]]);
         }
         // the slots run outward from s: a forward sweep often suffices
         if (__ballot((r[G::T] & need) != need) == 0ull) break;
 #pragma unroll
         for (int j = G::M - 1; j >= 0; --j) {
             if (j == E) continue;
-            r[G::NV[j]] |= r[G::NU[j]] & W[j];
-            if (!G::DIR) r[G::NU[j]] |= r[G::NV[j]] & W[j];
+            r[G::NV[j]] = and_or(r[G::NU[j]], W[j], r[G::NV[j]]);
+            if (!G::DIR) r[G::NU[j]] = and_or(r[G::NV[j]], W[j], r[G::NU[j]]);
         }
         if (__ballot((r[G::T] & need) != need) == 0ull) break;
         // reach only grows: an unchanged bit count is a fixed point
