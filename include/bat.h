@@ -532,8 +532,9 @@ int bat_valu_peak(double *lane_ops_per_s);
  * (grad = 0), the gradient sweep (grad = 1), or the batched sweep of -grad
  * probability vectors (grad = -1..-32; undirected only), with
  * arc-to-counter-bit order `perm` (0..3, as "BAT_PERM"; the batched form
- * always runs order 0), or with perm = 5 and grad = 0 the sub-cube sweep
- * (its closures' steps, and in a comment the arcs at its counter bits).
+ * always runs order 0), or with perm = 5 and grad = 0 or 1 the sub-cube
+ * sweep (its closures' steps, and in a comment the arcs at its counter
+ * bits).
  * Diagnostics only; needs no GPU.  The text is what hiprtc compiles: it
  * declares no headers.  buf (may be NULL) receives at most *len bytes
  * including the terminating NUL; *len is set to the size needed.

@@ -61,16 +61,21 @@ struct CubeParams {
     u64 item_base;
     u32 m, M;                 // arcs, arcs enumerated (counter bits)
     u32 levels, lane_bits;
-    u32 split;                // units an item is split into (each takes every split-th round of 64 prefixes)
-    u32 units;                // units per block
+    u32 split;                // units an item is split into (see cube_share)
+    u32 units;                // units per block (with gradients: chunks)
+    u32 chunk;                // with gradients: units per chunk
     u32 fused;                // one block: it writes the results itself
-    double2_t *part;          // [blocks] double-double partials
-    u64 *pcount;              // [blocks]
+    // partials: [blocks] double-doubles and counts; with gradients
+    // [1 + 2 M][blocks] (R, then bit cb down and up)
+    double2_t *part;
+    u64 *pcount;
+    u32 *done;                // with gradients: finished blocks of the reduction
     const double *p_dev;      // [m] on the device, or null: p below
     // results: dd and count, or R (with the check of p_dev); null where not wanted
     double *res, *R;
     u64 *count;
     int *status;
+    double *dRdp, *T1, *T0;   // [m] each
     u64 *diag;                // host, or null: [start, swept, done] device clocks and seq, written last
     u64 seq;
     CubeProg prog[kCubeProgs];
@@ -95,6 +100,31 @@ struct CubeWave {
     unsigned short from[kWave];  // level 1 prefixes (lane << 5 | word 2 index, or the lane) of the final rounds
     double qp[2][kWave];         // their probabilities
 };
+
+// x of another lane through the data-parallel primitives, 0 where there is
+// none or its row is masked.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_d(double x)
+{
+    const u64 b = (u64)__double_as_longlong(x);
+    const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)b, CTRL, ROWS, 0xf, false);
+    const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double((long long)((u64)hi << 32 | lo));
+}
+
+// The sum over the 64 lanes, in lane 63: row shifts by 1, 2, 4 and 8, then
+// the rows' last lanes broadcast.  (18 instructions; a butterfly of
+// double-doubles through LDS takes over 100, too many for 50 columns.)
+__device__ __forceinline__ double wave_sum_last(double x)
+{
+    x += dpp_d<0x111, 0xf>(x);
+    x += dpp_d<0x112, 0xf>(x);
+    x += dpp_d<0x114, 0xf>(x);
+    x += dpp_d<0x118, 0xf>(x);
+    x += dpp_d<0x142, 0xa>(x);
+    x += dpp_d<0x143, 0xc>(x);
+    return x;
+}
 
 // LDS written by some lanes of a wavefront and read by others: the LDS
 // operations of one wavefront complete in order, so only the compiler must
@@ -166,14 +196,28 @@ __device__ __forceinline__ u32 wave_excl_popc(u32 x, u32 &total)
     return e;
 }
 
-// Entries [w0, w0 + kCubeQueue) of the wavefront's set bits, in lane order:
+// The rounds of 64 prefixes a unit takes of its item's `total`: every
+// split-th from its own, or all of a few rounds for unit 0 and none for the
+// others, which end there (long items are what a launch waits for at its
+// end; short ones are not worth sharing).
+constexpr u32 kCubeShare = 2;
+__device__ __forceinline__ bool cube_share(u32 total, u32 sub, u32 split, u32 &first, u32 &step)
+{
+    const bool few = total <= kCubeShare * (u32)kWave;
+    first = few ? 0u : sub;
+    step = few ? 1u : split;
+    return total != 0u && (!few || sub == 0u);
+}
+
+// Entries [w0, w0 + QUEUE) of the wavefront's set bits, in lane order:
 // lane << 5 | bit.  e: set bits in the lanes below.
+template <u32 QUEUE>
 __device__ __forceinline__ void cube_enqueue(unsigned short *q, u32 U, u32 e, u32 w0, u32 lane)
 {
     u32 pos = e - w0;
     while (__ballot(U != 0u) != 0ull) {
         if (U) {
-            if (pos < (u32)kCubeQueue) q[pos] = (unsigned short)(lane << 5 | (u32)__builtin_ctz(U));
+            if (pos < QUEUE) q[pos] = (unsigned short)(lane << 5 | (u32)__builtin_ctz(U));
             ++pos;
             U &= U - 1u;
         }
@@ -275,9 +319,11 @@ struct CubeStatic {
     __device__ __forceinline__ u32 arcs() const { return G::M; }
     __device__ __forceinline__ void item(u64 block)
     {
+        const u32 b[2] = {(u32)__builtin_amdgcn_readfirstlane((u32)block),
+                          (u32)__builtin_amdgcn_readfirstlane((u32)(block >> 32))};
 #pragma unroll
         for (int k = 0; k < G::M - G::REL; ++k) {
-            um[k] = 0u - ((u32)(block >> k) & 1u);
+            um[k] = 0u - ((b[k >> 5] >> (k & 31)) & 1u);
             // opaque: a mask seen as all or nothing would turn each AND-OR
             // into a select and an OR
             asm volatile("" : "+s"(um[k]));
@@ -356,17 +402,16 @@ struct CubeSweep {
     }
 
     // The vectors under the undecided cubes U of level 1 prefixes (one per
-    // lane: `from`, probability q), every `step`-th round from `first`.
-    __device__ __forceinline__ void finals(u32 U, u32 from, double q, u32 first, u32 step)
+    // lane: `from`, probability q), the share of unit `sub` of `split`.
+    __device__ __forceinline__ void finals(u32 U, u32 from, double q, u32 sub, u32 split)
     {
-        u32 total;
+        u32 total, step, round;
         const u32 e = wave_excl_popc(U, total);
-        if (total == 0u) return;
+        if (!cube_share(total, sub, split, round, step)) return;
         W.from[lane] = (unsigned short)from;
         W.qp[1][lane] = q;
-        u32 round = first;
         for (u32 w0 = 0; w0 < total; w0 += kCubeQueue) {
-            cube_enqueue(W.queue[1], U, e, w0, lane);
+            cube_enqueue<kCubeQueue>(W.queue[1], U, e, w0, lane);
             const u32 end = min(total, w0 + (u32)kCubeQueue);
             for (; (u32)kWave * round < end; round += step) {
                 const u32 i = (u32)kWave * round + lane;
@@ -402,15 +447,14 @@ struct CubeSweep {
             finals(U, lane, q, sub, split);
             return;
         }
-        u32 total;
+        u32 total, step, round;
         const u32 e = wave_excl_popc(U, total);
-        if (total == 0u) return;
+        if (!cube_share(total, sub, split, round, step)) return;
         W.qp[0][lane] = q;
-        u32 round = sub;
         for (u32 w0 = 0; w0 < total; w0 += kCubeQueue) {
-            cube_enqueue(W.queue[0], U, e, w0, lane);
+            cube_enqueue<kCubeQueue>(W.queue[0], U, e, w0, lane);
             const u32 end = min(total, w0 + (u32)kCubeQueue);
-            for (; (u32)kWave * round < end; round += split) {
+            for (; (u32)kWave * round < end; round += step) {
                 const u32 i = (u32)kWave * round + lane;
                 const bool on = i < end;
                 const u32 x = W.queue[0][(on ? i : end - 1u) - w0];
@@ -428,25 +472,41 @@ __device__ __forceinline__ void cube_clock(CubeArgs *P, u32 k)
     if (P->diag) P->diag[k] = wall_clock64();
 }
 
-// Results from the sums (one thread): as a double-double and the count, or
-// as R and the count with the check of p (NaN and -1 when a p is no
-// probability).
-__device__ __forceinline__ void cube_results(CubeArgs *P, double hi, double lo, u64 cnt)
+// 0, or -1 when a p on the device is no probability.
+__device__ __forceinline__ int cube_status(CubeArgs *P)
 {
-    cnt <<= P->m - P->M;
     int st = 0;
     if (P->p_dev)
         for (u32 i = 0; i < P->m; ++i)
             if (!(P->p_dev[i] >= 0.0 && P->p_dev[i] <= 1.0)) st = -1;
+    return st;
+}
+
+// R and the count from the sums (one thread): as a double-double and the
+// count, or as R and the count with the status (NaN and -1).
+__device__ __forceinline__ void cube_store(CubeArgs *P, double hi, double lo, u64 cnt, int st)
+{
     if (P->res) {
         P->res[0] = hi;
         P->res[1] = lo;
     }
     if (P->R) *P->R = st ? __builtin_nan("") : hi + lo;
-    if (P->count) *P->count = st ? 0ull : cnt;
+    if (P->count) *P->count = st ? 0ull : cnt << (P->m - P->M);
     if (P->status) *P->status = st;
+}
+
+// The sequence number goes last: a host that sees it sees the results too,
+// so a synchronous call need not wait for the stream.
+__device__ __forceinline__ void cube_publish(CubeArgs *P)
+{
     cube_clock(P, 2);
     if (P->diag) __hip_atomic_store(P->diag + 3, P->seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ void cube_results(CubeArgs *P, double hi, double lo, u64 cnt)
+{
+    cube_store(P, hi, lo, cnt, cube_status(P));
+    cube_publish(P);
 }
 
 // A block takes `units` consecutive units; its wavefronts take the next one
@@ -504,6 +564,423 @@ __device__ __forceinline__ void cube_kernel(CubeArgs *P, CubeTables &T, CubeWave
             P->part[blockIdx.x] = {h, l};
             P->pcount[blockIdx.x] = n;
         }
+    }
+}
+
+// ------------------------------------------------------------- gradients
+// The same sweep with T1_i and T0_i of every arc.  Each decided word adds to
+// the arcs of its own bits, by the tables with one bit left out, and a cube
+// that connects whole also to the arcs free in it (its whole sum, for either
+// state).  What lies under a prefix goes up once: the sums of a round's
+// lanes are added per prefix of the level above (a segmented sum, as the
+// lanes lie in prefix order), so an arc above a word costs once per prefix,
+// not once per word under it.  A wavefront takes chunks of consecutive units
+// from the block's counter and folds its columns after each chunk (unless
+// nothing connected) into the chunk's own place in LDS, which the block adds
+// up in order, so that no sum depends on timing.  (Every n-th unit to a
+// wavefront and one fold each left the longest one running: 36 arcs, 3.5
+// ms.)  Nothing is divided by a probability: 0 and 1 are exact.
+//
+// What bounds it: besides the closures, the 64-byte records of the words'
+// bytes (16 LDS reads of 16 bytes per 64 words).
+
+struct CubeGradTables {
+    alignas(16) double tbx[256 * 8];  // word 0, per byte value: TB, then TB without bit a = 0..2 of state x = 0, 1
+    double a4m[8];                    // word 0: A without bit 3, without bit 4
+    double q5m[kCubeLevels - 1][5][32];  // words 1, 2: their probability without arc a
+    double qlm[kLaneBits][kWave];     // lane bits without one
+};
+
+__device__ __forceinline__ void cube_grad_tables(CubeArgs *P, const CubeTables &T, CubeGradTables &X)
+{
+    const u32 tid = threadIdx.x, nt = blockDim.x, M = P->M;
+    for (u32 y = tid; y < 256u; y += nt) {
+        double s = 0.0, sg[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, b[2][3];
+#pragma unroll
+        for (u32 k = 0; k < 3; ++k) {
+            b[0][k] = cube_q(T, M, k, 0u);
+            b[1][k] = cube_q(T, M, k, 1u);
+        }
+#pragma unroll
+        for (u32 i = 0; i < 8; ++i) {
+            const double on = (y >> i) & 1u ? 1.0 : 0.0;
+            const double q0 = b[i & 1u][0], q1 = b[(i >> 1) & 1u][1], q2 = b[i >> 2][2];
+            s += on * q0 * q1 * q2;
+            sg[i & 1u] += on * q1 * q2;
+            sg[2 + ((i >> 1) & 1u)] += on * q0 * q2;
+            sg[4 + (i >> 2)] += on * q0 * q1;
+        }
+        X.tbx[8 * y] = s;
+#pragma unroll
+        for (u32 k = 0; k < 6; ++k) X.tbx[8 * y + 1 + k] = sg[k];
+        X.tbx[8 * y + 7] = 0.0;
+    }
+    if (tid < 4u) {
+        X.a4m[tid] = cube_q(T, M, 4, tid >> 1);
+        X.a4m[4 + tid] = cube_q(T, M, 3, tid & 1u);
+    }
+    for (u32 i = tid; i < (P->levels - 1u) * 160u; i += nt) {
+        const u32 l = i / 160u, a = (i % 160u) >> 5, j = i & 31u;
+        double q = 1.0;
+        for (u32 b = 0; b < 5u; ++b)
+            if (b != a) q *= cube_q(T, M, kCubeGroup * (l + 1u) + b, (j >> b) & 1u);
+        X.q5m[l][a][j] = q;
+    }
+    for (u32 i = tid; i < P->lane_bits * (u32)kWave; i += nt) {
+        const u32 a = i >> 6, j = i & 63u;
+        double q = 1.0;
+        for (u32 b = 0; b < P->lane_bits; ++b)
+            if (b != a) q *= cube_q(T, M, kCubeGroup * P->levels + b, (j >> b) & 1u);
+        X.qlm[a][j] = q;
+    }
+    __syncthreads();
+}
+
+constexpr int kGradQueue = kCubeQueue / 2;
+struct CubeGradWave {
+    unsigned short queue[kCubeLevels - 1][kGradQueue];
+    unsigned short from[kWave];
+    // of the prefixes above words 0 and 1: probabilities, the sums under them
+    double qp[kCubeLevels - 1][kWave];
+    double val[kCubeLevels - 1][kWave];
+};
+
+template <class Clo>
+struct CubeGradSweep {
+    CubeArgs *P;
+    const CubeTables &T;
+    const CubeGradTables &X;
+    CubeGradWave &W;
+    Clo clo;
+    u32 lane;
+    double hi, lo;            // R
+    u64 cnt;
+    double g0[3][2], tb0[4];  // word 0: bits 0..2 by state; per byte for bits 3, 4
+    double g1[5][2], g2[5][2];  // words 1, 2
+    double free1, free2;      // cubes that connect whole, of words 1 and 2
+    double tl[kLaneBits];     // lane bits (of the lane's own state)
+    double sh[2], sl[2];      // item bit `lane`, by state
+
+    __device__ __forceinline__ void zero()
+    {
+        hi = lo = free1 = free2 = 0.0;
+        cnt = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) g0[a][0] = g0[a][1] = 0.0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) tb0[h] = 0.0;
+#pragma unroll
+        for (int a = 0; a < 5; ++a) g1[a][0] = g1[a][1] = g2[a][0] = g2[a][1] = 0.0;
+#pragma unroll
+        for (int b = 0; b < kLaneBits; ++b) tl[b] = 0.0;
+        sh[0] = sh[1] = sl[0] = sl[1] = 0.0;
+    }
+
+    __device__ __forceinline__ void addR(double x)
+    {
+        double s, e;
+        two_sum(hi, x, s, e);
+        hi = s;
+        lo += e;
+    }
+
+    // A final word under a prefix of probability q: R, the count and word
+    // 0's arcs; returns F(V).
+    __device__ __forceinline__ double word0(double q, u32 V)
+    {
+        cnt += (u64)__popc(V);
+        double F = 0.0, sg[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const Pair *rp = reinterpret_cast<const Pair *>(X.tbx + ((V >> (8 * h)) & 255u) * 8u);
+            const Pair v0 = rp[0], v1 = rp[1], v2 = rp[2], v3 = rp[3];
+            const double ah = T.a4[0][h];
+            tb0[h] = __builtin_fma(q, v0.x, tb0[h]);
+            F = __builtin_fma(ah, v0.x, F);
+            sg[0] = __builtin_fma(ah, v0.y, sg[0]);
+            sg[1] = __builtin_fma(ah, v1.x, sg[1]);
+            sg[2] = __builtin_fma(ah, v1.y, sg[2]);
+            sg[3] = __builtin_fma(ah, v2.x, sg[3]);
+            sg[4] = __builtin_fma(ah, v2.y, sg[4]);
+            sg[5] = __builtin_fma(ah, v3.x, sg[5]);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            g0[a][0] = __builtin_fma(q, sg[2 * a], g0[a][0]);
+            g0[a][1] = __builtin_fma(q, sg[2 * a + 1], g0[a][1]);
+        }
+        addR(q * F);
+        return F;
+    }
+
+    __device__ __forceinline__ double word_sum(u32 level, u32 V) const
+    {
+        const double *tb = T.tb[level], *a4 = T.a4[level];
+        double F = a4[0] * tb[V & 255u];
+        F = __builtin_fma(a4[1], tb[(V >> 8) & 255u], F);
+        F = __builtin_fma(a4[2], tb[(V >> 16) & 255u], F);
+        return __builtin_fma(a4[3], tb[V >> 24], F);
+    }
+
+    // The cubes S of a word of level 1 or 2 that connect whole: R, the count
+    // and the word's arcs g.  An arc's state x left out of the sum is the
+    // sum of the cubes of state x taken for both (its two probabilities add
+    // to 1).
+    __device__ __forceinline__ double cubes(u32 level, double q, u32 S, double (&g)[5][2], double &all)
+    {
+        cnt += (u64)__popc(S) << (kCubeGroup * level);
+        if (__ballot(S != 0u) == 0ull) return 0.0;
+#pragma unroll
+        for (int a = 0; a < 5; ++a) {
+            const u32 pat = slice_pattern(a), s1 = S & pat, s0 = S & ~pat;
+            g[a][1] = __builtin_fma(q, word_sum(level, s1 | s1 >> (1 << a)), g[a][1]);
+            g[a][0] = __builtin_fma(q, word_sum(level, s0 | s0 << (1 << a)), g[a][0]);
+        }
+        const double F = word_sum(level, S);
+        all = __builtin_fma(q, F, all);
+        addR(q * F);
+        return F;
+    }
+
+    // The sum v under cube j of a word of level 1 or 2 (q: the probability
+    // above the word): its arcs g.
+    __device__ __forceinline__ void under(u32 level, double q, u32 j, double v, double (&g)[5][2])
+    {
+        const double qv = q * v;
+#pragma unroll
+        for (int a = 0; a < 5; ++a) {
+            const double w = X.q5m[level - 1u][a][j] * qv;
+            const double up = (j >> a) & 1u ? 1.0 : 0.0, down = (j >> a) & 1u ? 0.0 : 1.0;
+            g[a][1] = __builtin_fma(w, up, g[a][1]);
+            g[a][0] = __builtin_fma(w, down, g[a][0]);
+        }
+    }
+
+    // The sums of x over the round's lanes of one prefix (own, contiguous)
+    // added to val; lanes that are not `on` belong to none.
+    __device__ __forceinline__ void to_prefix(double *val, u32 own, double x, bool on)
+    {
+        own = on ? own : (u32)kWave;
+        const u32 before = (u32)__shfl_up((int)own, 1, kWave);
+        const u64 heads = __ballot(lane == 0u || own != before);
+        const int start = 63 - __builtin_clzll(heads & (~0ull >> (63u - lane)));
+#pragma unroll
+        for (int off = 1; off <= 16; off <<= 1) {  // at most 32 lanes per prefix
+            const double y = __shfl_up(x, off, kWave);
+            x += (int)lane - off >= start ? y : 0.0;
+        }
+        if (on && (lane == 63u || ((heads >> (lane + 1u)) & 1ull))) val[own] += x;
+    }
+
+    // Decides a word: returns its undecided cubes; v: the sum of its
+    // connected ones (when `mine`).
+    __device__ __forceinline__ u32 classify(u32 level, u32 rel, double q, bool live, bool mine, double (&g)[5][2],
+                                            double &all, double &v)
+    {
+        v = 0.0;
+        const u32 up = clo.close(2u * level - 1u, rel, live);
+        if (__ballot(up != 0u) == 0ull) return 0u;
+        const u32 down = clo.close(2u * level, rel, live && up != 0u);
+        if (mine) v = cubes(level, q, down, g, all);
+        return up & ~down;
+    }
+
+    // The vectors under the undecided cubes U of level 1 words (one per
+    // lane: `from`, probability q above the word); returns their sums.
+    __device__ __forceinline__ double finals(u32 U, u32 from, double q, u32 sub, u32 split)
+    {
+        u32 total, step, round;
+        const u32 e = wave_excl_popc(U, total);
+        if (!cube_share(total, sub, split, round, step)) return 0.0;
+        W.from[lane] = (unsigned short)from;
+        W.qp[0][lane] = q;
+        W.val[0][lane] = 0.0;
+        for (u32 w0 = 0; w0 < total; w0 += kGradQueue) {
+            cube_enqueue<kGradQueue>(W.queue[0], U, e, w0, lane);
+            const u32 end = min(total, w0 + (u32)kGradQueue);
+            for (; (u32)kWave * round < end; round += step) {
+                const u32 i = (u32)kWave * round + lane;
+                const bool on = i < end;
+                const u32 x = W.queue[0][(on ? i : end - 1u) - w0], own = x >> 5, j = x & 31u;
+                const u32 V = clo.close(0u, (u32)W.from[own] << (2 * kCubeGroup) | j << kCubeGroup, on);
+                const double qo = W.qp[0][own], qj = T.q5[1][j];
+                const double F = word0(qo * qj, V);
+                under(1u, qo, j, F, g1);
+                to_prefix(W.val[0], own, qj * F, on);
+            }
+            wave_lds_sync();
+        }
+        return W.val[0][lane];
+    }
+
+    __device__ __forceinline__ void unit(u64 block, u32 sub)
+    {
+        const u32 levels = clo.levels(), lane_bits = clo.lane_bits(), split = P->split, M = clo.arcs();
+        const u32 rb = kCubeGroup * levels + lane_bits;
+        clo.item(block);
+        const bool live = (lane >> lane_bits) == 0u;
+        // the item's probability, and without the item bit `lane`
+        double qi = 1.0, qm = 1.0;
+#pragma unroll 4
+        for (u32 b = rb; b < M; ++b) {
+            const double f = cube_q(T, M, b, (u32)(block >> (b - rb)) & 1u);
+            qi *= f;
+            qm *= b - rb == lane ? 1.0 : f;
+        }
+        const double q = qi * T.ql[lane];
+        double v;  // the sum under the lane's prefix
+        if (levels == 1u) {
+            u32 V = clo.close(0u, lane << kCubeGroup, live);
+            if (M < 5u) V &= (1u << (1u << M)) - 1u;
+            v = word0(q, V);
+        } else if (levels == 2u) {
+            const u32 U = classify(1u, lane << (2 * kCubeGroup), q, live, sub == 0u, g1, free1, v);
+            v += finals(U, lane, q, sub, split);
+        } else {
+            const u32 U = classify(2u, lane << (3 * kCubeGroup), q, live, sub == 0u, g2, free2, v);
+            u32 total, step, round;
+            const u32 e = wave_excl_popc(U, total);
+            if (!cube_share(total, sub, split, round, step)) total = 0u;
+            W.qp[1][lane] = q;
+            W.val[1][lane] = 0.0;
+            for (u32 w0 = 0; w0 < total; w0 += kGradQueue) {
+                cube_enqueue<kGradQueue>(W.queue[1], U, e, w0, lane);
+                const u32 end = min(total, w0 + (u32)kGradQueue);
+                for (; (u32)kWave * round < end; round += step) {
+                    const u32 i = (u32)kWave * round + lane;
+                    const bool on = i < end;
+                    const u32 x = W.queue[1][(on ? i : end - 1u) - w0], own = x >> 5, j = x & 31u;
+                    const double qo = W.qp[1][own], qj = T.q5[2][j];
+                    double v1;
+                    const u32 U1 = classify(1u, x << (2 * kCubeGroup), qo * qj, on, true, g1, free1, v1);
+                    v1 += finals(U1, x, qo * qj, 0u, 1u);
+                    under(2u, qo, j, v1, g2);
+                    to_prefix(W.val[1], own, qj * v1, on);
+                }
+                wave_lds_sync();
+            }
+            v += W.val[1][lane];
+        }
+        wave_lds_sync();
+        v = live ? v : 0.0;
+        if (__ballot(v != 0.0) == 0ull) return;
+#pragma unroll
+        for (int b = 0; b < kLaneBits; ++b)
+            if ((u32)b < lane_bits) tl[b] = __builtin_fma(qi * X.qlm[b][lane], v, tl[b]);
+        if (rb < M) {
+            double h = T.ql[lane] * v, l = 0.0;
+            wave_sum_dd(h, l);
+            const u32 x = (u32)(block >> lane) & 1u;
+            if (lane + rb < M) {
+                if (x) dd_add(sh[1], sl[1], qm * h, qm * l);
+                else dd_add(sh[0], sl[0], qm * h, qm * l);
+            }
+        }
+    }
+
+    // Fold the wavefront's columns into the chunk's place (col: [1 + 2 M],
+    // R's low part last).
+    __device__ __forceinline__ u64 write(double *col)
+    {
+        const u64 c = wave_sum_u64(cnt);
+        if (c == 0ull) return 0ull;  // nothing connected: every sum is 0
+        const u32 levels = clo.levels(), lane_bits = clo.lane_bits(), M = clo.arcs();
+        const u32 rb = kCubeGroup * levels + lane_bits;
+        auto fold = [&](u32 cb, u32 x, double v) {
+            v = wave_sum_last(v);
+            if (lane == kWave - 1u && cb < M) col[1u + 2u * cb + x] = v;
+        };
+        wave_sum_dd(hi, lo);
+        if (lane == 0) {
+            col[0] = hi;
+            col[1u + 2u * M] = lo;
+        }
+        const double f0 = free1 + free2;
+#pragma unroll
+        for (u32 a = 0; a < 3; ++a) {
+            fold(a, 0u, g0[a][0] + f0);
+            fold(a, 1u, g0[a][1] + f0);
+        }
+        const double *am = X.a4m;
+        fold(3u, 0u, am[0] * tb0[0] + am[2] * tb0[2] + f0);
+        fold(3u, 1u, am[1] * tb0[1] + am[3] * tb0[3] + f0);
+        fold(4u, 0u, am[4] * tb0[0] + am[5] * tb0[1] + f0);
+        fold(4u, 1u, am[6] * tb0[2] + am[7] * tb0[3] + f0);
+        if (levels > 1u)
+#pragma unroll
+            for (u32 a = 0; a < 5; ++a) {
+                fold(kCubeGroup + a, 0u, g1[a][0] + free2);
+                fold(kCubeGroup + a, 1u, g1[a][1] + free2);
+            }
+        if (levels > 2u)
+#pragma unroll
+            for (u32 a = 0; a < 5; ++a) {
+                fold(2 * kCubeGroup + a, 0u, g2[a][0]);
+                fold(2 * kCubeGroup + a, 1u, g2[a][1]);
+            }
+#pragma unroll
+        for (u32 b = 0; b < (u32)kLaneBits; ++b)
+            if (b < lane_bits) {
+                const bool x = (lane >> b) & 1u;
+                fold(kCubeGroup * levels + b, 0u, x ? 0.0 : tl[b]);
+                fold(kCubeGroup * levels + b, 1u, x ? tl[b] : 0.0);
+            }
+        if (lane + rb < M) {
+            col[1u + 2u * (rb + lane)] = sh[0] + sl[0];
+            col[2u + 2u * (rb + lane)] = sh[1] + sl[1];
+        }
+        return c;
+    }
+};
+
+// cols: [kGradUnits][COLS], COLS >= 2 + 2 M.
+constexpr int kGradUnits = 8;  // most chunks of a block
+template <int COLS, class Clo>
+__device__ __forceinline__ void cube_grad_kernel(CubeArgs *P, CubeTables &T, CubeGradTables &X, CubeGradWave *Ws,
+                                                 double (&cols)[kGradUnits][COLS], Clo clo)
+{
+    __shared__ u32 next;
+    __shared__ u64 sc[kGradUnits];
+    if (threadIdx.x == 0) {
+        next = 0u;
+        if (blockIdx.x == 0) {
+            cube_clock(P, 0);
+            *P->done = 0u;
+        }
+    }
+    cube_tables(P, T);
+    cube_grad_tables(P, T, X);
+    const u32 lane = threadIdx.x & (kWave - 1);
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 split = P->split, units = P->units, per = P->chunk, M = clo.arcs();
+    const u64 all = P->n_items * split;
+    CubeGradSweep<Clo> S{P, T, X, Ws[wave], clo, lane};
+    for (;;) {
+        __builtin_amdgcn_wave_barrier();  // (see cube_kernel)
+        const u32 k = __builtin_amdgcn_readfirstlane(atomicAdd(&next, 1u)) / kWave;
+        if (k >= units) break;
+        S.zero();
+        for (u32 i = 0; i < per; ++i) {
+            const u64 w = ((u64)blockIdx.x * units + k) * per + i;
+            if (w >= all) break;
+            const u64 it = w / split;
+            S.unit(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
+        }
+        const u64 c = S.write(cols[k]);
+        if (lane == 0) sc[k] = c;
+    }
+    __syncthreads();
+    const u32 n = gridDim.x;
+    for (u32 i = threadIdx.x; i < 1u + 2u * M; i += blockDim.x) {
+        double h = 0.0, l = 0.0;
+        for (u32 k = 0; k < units; ++k)
+            if (sc[k]) dd_add(h, l, cols[k][i], i == 0u ? cols[k][1u + 2u * M] : 0.0);
+        P->part[(u64)i * n + blockIdx.x] = {h, l};
+    }
+    if (threadIdx.x == 0) {
+        u64 c = 0;
+        for (u32 k = 0; k < units; ++k) c += sc[k];
+        P->pcount[blockIdx.x] = c;
     }
 }
 

@@ -1690,10 +1690,10 @@ int queue_sweep(const Request &rq, const Plan &P, const DeviceInfo &D, const Tun
 // Whole sweeps in the form of bat_cube.hpp.  Option BAT_CUBES: -1 (default)
 // takes it unless a knob of the plain sweep's launch has been set (those
 // describe the plain kernels), 0 never, 1 always where it can run.
-bool cubes_wanted(bool grad)
+bool cubes_wanted()
 {
     const int64_t want = opts().cubes.load();
-    if (want == 0 || grad) return false;
+    if (want == 0) return false;
     return want == 1 || opts().plain_shape_default();
 }
 
@@ -1704,8 +1704,8 @@ bool cubes_wanted(bool grad)
 // but run longer chains of closures per wavefront; they win from 33 arcs on
 // (specialised: 32 arcs 126 us against 94 us, 33 arcs 110 us against 131 us,
 // 35 arcs 0.14 ms against 0.39 ms).
-void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed, batcube::CubePlan &C,
-                int levels = 0)
+void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed,
+                batcube::CubePlan &C, int levels = 0)
 {
     std::vector<char> rel = relevance(n, m, arcs, s, t, directed);
     for (int32_t i = 0; i < m; ++i)
@@ -1722,8 +1722,12 @@ void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t,
 // j modulo parts.
 u64 cube_items(const batcube::CubePlan &C) { return 1ull << std::max(0, C.M - C.rel_bits()); }
 
+// Most chunks of units a gradient sweep is cut into, while a block takes no
+// more than kGradUnits of them.
+constexpr u64 kGradChunks = 65536;
+
 int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
-                bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, u64 parts = 1, u64 part = 0)
+                bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, bool grad, u64 parts = 1, u64 part = 0)
 {
     memset(&K, 0, sizeof K);
     K.m = (u32)C.m;
@@ -1734,30 +1738,49 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     K.item_mul = 0x9E3779B97F4A7C15ull * parts;  // odd times parts: consecutive items lie apart
     K.item_mask = cube_items(C) - 1;
     K.item_base = part;
-    // Items are split into units while there are few: with two levels only
-    // to fill the device (24 arcs, 256 items: 12.4 us in 4 units each, 15.3
-    // us whole; 30 arcs, 16384 items: 43 us in 4, 33 us whole, as every unit
-    // decides the item's first word again); with three levels, where that
-    // is a small part, until the long items no longer set the end (36 arcs,
-    // 16384 items: 0.60 ms in 4, 1.02 ms whole; 40 arcs, 524288 items: 11.9
-    // ms in 4, 9.1 ms whole)
+    // Items are split into up to 4 units while there are few.  With two
+    // levels only to fill the device: 24 arcs, 256 items: 11.0 us in 4 units
+    // each, 15.3 us whole; 27 arcs, 2048 items: 37 us in 2, 47 us whole; with
+    // gradients, whose units also fold 50 sums, 24 arcs 32 us in 4 and 74 us
+    // in 16, 27 arcs 91 us whole and 119 us in 2.  With three levels, where
+    // deciding the item's first word again is a small part, until the long
+    // items no longer set the end: 36 arcs, 16384 items: 0.57 ms in 4, 1.02
+    // ms whole, with gradients 1.6 and 2.6 ms; 40 arcs, 524288 items: 11.9 ms
+    // in 4, 9.1 ms whole.
     u64 split = 1;
+    const u64 enough = (u64)D.cus * (C.levels == 3 ? 1024 : grad ? 4 : 16);
     if (opts().cube_split.load() > 0) split = (u64)opts().cube_split.load();
     else
-        while (C.levels > 1 && split < (C.levels == 2 ? 16 : 4) && K.n_items * split < (u64)D.cus * (C.levels == 2 ? 16 : 256))
-            split *= 2;
+        while (split < 4 && K.n_items * split < enough) split *= 2;
     if (C.levels == 1) split = 1;
     K.split = (u32)split;
     const u64 w = K.n_items * split;
     waves = (int)std::min<u64>(w, bat::kCubeWaves);
-    // units per block: as many as leave every CU some 16 blocks
     u64 units = (u64)waves;
+    if (grad) {
+        // a chunk's fold of some 50 columns takes as long as several rounds:
+        // chunks of several units once they are many (36 arcs, 65536 units:
+        // 1.6 ms one by one, 2.6 ms in chunks of 8 of a block of 64; 40 arcs,
+        // 524288 units: 20.4 ms in eights, 26 ms in twos)
+        u64 per = 1;
+        while (w / per > kGradChunks) per *= 2;
+        const u64 chunks = (w + per - 1) / per;
+        u64 cb = (u64)waves;
+        while (cb < bat::kGradUnits && chunks / (2 * cb) >= (u64)D.cus * 4) cb *= 2;
+        K.chunk = (u32)per;
+        K.units = (u32)cb;
+        blocks = (unsigned)((chunks + cb - 1) / cb);
+        K.fused = 0u;
+    }
+    // units per block: as many as leave every CU some 16 blocks
     while (units < bat::kCubeUnits && w / (2 * units) >= (u64)D.cus * 16) units *= 2;
-    K.units = (u32)units;
-    const u64 nb = (w + units - 1) / units;
-    if (nb > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)w);
-    blocks = (unsigned)nb;
-    K.fused = nb == 1 ? 1u : 0u;
+    if (!grad) {
+        K.units = (u32)units;
+        const u64 nb = (w + units - 1) / units;
+        if (nb > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)w);
+        blocks = (unsigned)nb;
+        K.fused = nb == 1 ? 1u : 0u;
+    }
     K.p_dev = p_dev;
     if (p_host) memcpy(K.p, p_host, sizeof(double) * C.m);
     for (int c = 0; c < C.M; ++c) K.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
@@ -1798,19 +1821,29 @@ bool cube_fits(const batcube::CubePlan &C, bool aot = false)
     return C.M <= batk::kCubeMaxBits && C.slots <= bat::kCubeSlots && C.steps + 8 * bat::kCubeProgs <= bat::kCubeSteps;
 }
 
-// The blocks' partials (none when one block writes the results).
-size_t cube_part_bytes(const bat::CubeParams &K, unsigned blocks) { return K.fused ? 0 : 24 * (size_t)blocks; }
-void cube_parts(bat::CubeParams &K, unsigned blocks, char *ws)
+// The partials (none when one block writes the results): per block, or with
+// gradients per block and column, and the reduction's block counter.
+size_t cube_part_bytes(const bat::CubeParams &K, unsigned blocks, bool grad)
 {
-    if (K.fused) return;
-    K.part = (bat::double2_t *)ws;
-    K.pcount = (u64 *)(ws + 16 * (size_t)blocks);
+    if (grad) return 256 + (16 * (1 + 2 * (size_t)K.M) + 8) * blocks;
+    return K.fused ? 0 : 24 * (size_t)blocks;
+}
+void cube_parts(bat::CubeParams &K, unsigned blocks, bool grad, char *ws)
+{
+    if (grad) {
+        K.done = (u32 *)ws;
+        K.part = (bat::double2_t *)(ws + 256);
+        K.pcount = (u64 *)(ws + 256 + 16 * (1 + 2 * (size_t)K.M) * blocks);
+    } else if (!K.fused) {
+        K.part = (bat::double2_t *)ws;
+        K.pcount = (u64 *)(ws + 16 * (size_t)blocks);
+    }
 }
 
 // The hiprtc source of the sweep specialised for a plan.  with_arcs: also
 // the arcs at the counter bits, in a comment (the code does not depend on
 // them).
-std::string cube_source(const batcube::CubePlan &C, bool with_arcs = false)
+std::string cube_source(const batcube::CubePlan &C, bool grad, bool with_arcs = false)
 {
     std::string g = "\nnamespace bat {\nstruct JitCube {\n";
     if (with_arcs) {
@@ -1838,18 +1871,28 @@ std::string cube_source(const batcube::CubePlan &C, bool with_arcs = false)
                                  std::to_string(x.d) + "]);\n");
         g += "    }\n";
     }
-    g += "  }\n};\n}\n"
-         "extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) "
-         "bat_cube_jit(bat::CubeParams) {\n"
-         "  __shared__ bat::CubeTables T; __shared__ bat::CubeWave W[bat::kCubeWaves];\n"
-         "  bat::cube_kernel((bat::CubeArgs *)__builtin_amdgcn_kernarg_segment_ptr(), T, W, bat::CubeStatic<bat::JitCube>{});\n}\n";
+    g += "  }\n};\n}\n";
+    if (grad)
+        g += "extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) "
+             "bat_cube_grad_jit(bat::CubeParams) {\n"
+             "  __shared__ bat::CubeTables T; __shared__ bat::CubeGradTables X;\n"
+             "  __shared__ bat::CubeGradWave W[bat::kCubeWaves];\n"
+             "  __shared__ double cols[bat::kGradUnits][2 + 2 * bat::JitCube::M];\n"
+             "  bat::cube_grad_kernel((bat::CubeArgs *)__builtin_amdgcn_kernarg_segment_ptr(), T, X, W, cols, "
+             "bat::CubeStatic<bat::JitCube>{});\n}\n";
+    else
+        g += "extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) "
+             "bat_cube_jit(bat::CubeParams) {\n"
+             "  __shared__ bat::CubeTables T; __shared__ bat::CubeWave W[bat::kCubeWaves];\n"
+             "  bat::cube_kernel((bat::CubeArgs *)__builtin_amdgcn_kernarg_segment_ptr(), T, W, "
+             "bat::CubeStatic<bat::JitCube>{});\n}\n";
     return std::string(kDeviceSource) + kCubeSource + g;
 }
 
 // The specialised kernel of a plan, by the bytes its source is made from.
-int cube_jit_get(const batcube::CubePlan &C, const DeviceInfo &D, hipFunction_t &fn, double &jit_ms, uint64_t &id)
+int cube_jit_get(const batcube::CubePlan &C, const DeviceInfo &D, bool grad, hipFunction_t &fn, double &jit_ms, uint64_t &id)
 {
-    std::string key = std::to_string(D.id) + " cube " + std::to_string(C.M) + " " + std::to_string(C.levels) + " " +
+    std::string key = std::to_string(D.id) + (grad ? " cubeg " : " cube ") + std::to_string(C.M) + " " + std::to_string(C.levels) + " " +
                       std::to_string(C.lane_bits) + " " + std::to_string(C.slots) + ":";
     for (int k = 0; k < 2 * C.levels - 1; ++k) {
         key += " " + std::to_string(C.prog[k].result) + " ";
@@ -1869,7 +1912,7 @@ int cube_jit_get(const batcube::CubePlan &C, const DeviceInfo &D, hipFunction_t 
             return BAT_OK;
         }
     }
-    return jit_load(D, key, cube_source(C), "bat_cube_jit", fn, jit_ms, id);
+    return jit_load(D, key, cube_source(C, grad), grad ? "bat_cube_grad_jit" : "bat_cube_jit", fn, jit_ms, id);
 }
 
 void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int waves)
@@ -1891,14 +1934,14 @@ void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int 
 // Queue the sweep (and its reduction) on `stream`; K's result pointers set.
 // No event is recorded: the kernels report their clocks themselves (four
 // event records took a third of a small call's time).
-int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, bool jit,
+int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, bool jit, bool grad,
                const DeviceInfo &D, hipStream_t stream)
 {
     hipFunction_t fn = nullptr;
     double jit_ms = 0.0;
-    uint64_t kid = aot_kernel_id("k_cube_fwd", 0, false);
+    uint64_t kid = aot_kernel_id(grad ? "k_cube_grad" : "k_cube_fwd", 0, false);
     if (jit) {
-        int rc = cube_jit_get(C, D, fn, jit_ms, kid);
+        int rc = cube_jit_get(C, D, grad, fn, jit_ms, kid);
         if (rc) return rc;
     }
     u64 *slot = nullptr;
@@ -1908,10 +1951,13 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
     if (jit) {
         void *args[] = {&K};
         HIPCHK(hipModuleLaunchKernel(fn, blocks, 1, 1, (unsigned)(waves * bat::kWave), 1, 1, 0, stream, args, nullptr));
+    } else if (grad) {
+        HIPCHK(batk::cube_grad(stream, blocks, waves, K));
     } else {
         HIPCHK(batk::cube_sweep(stream, blocks, waves, K));
     }
-    if (!K.fused) HIPCHK(batk::cube_finish(stream, blocks, K));
+    if (grad) HIPCHK(batk::cube_grad_finish(stream, blocks, K));
+    else if (!K.fused) HIPCHK(batk::cube_finish(stream, blocks, K));
     cube_launch_info(C, K, waves);
     t_state.info.specialised = jit ? 1 : 0;
     t_state.info.jit_ms = jit_ms;
@@ -1939,10 +1985,11 @@ int cube_wait(const bat::CubeParams &K, hipStream_t stream)
     return BAT_OK;
 }
 
-// A whole sweep over host probabilities (validated): R as a double-double
-// and the count, written by the device into the pinned staging buffer.
-int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, double *R_hl, u64 &count,
-              u64 parts = 1, u64 part = 0)
+// A whole sweep over host probabilities (validated); res: R as a
+// double-double, with gradients followed by T0 and T1 of each arc, written
+// by the device into the pinned staging buffer.
+int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, bool grad, std::vector<double> &res,
+              u64 &count, u64 parts = 1, u64 part = 0)
 {
     hipStream_t stream;
     int rc = thread_stream(D.id, stream);
@@ -1951,37 +1998,38 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     unsigned blocks = 0;
     int waves = 0;
     const bool jit = cube_jit(C);
-    rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, parts, part);
+    rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, grad, parts, part);
     if (rc) return rc;
     Scratch *S = nullptr;
-    rc = scratch_reserve(D.id, stream, cube_part_bytes(K, blocks), 64, S);
+    const size_t n = grad ? 2 + 4 * (size_t)C.m : 2;
+    rc = scratch_reserve(D.id, stream, cube_part_bytes(K, blocks, grad), 8 * (n + 1), S);
     if (rc) return rc;
-    cube_parts(K, blocks, S->dev);
+    cube_parts(K, blocks, grad, S->dev);
     K.res = (double *)S->host;
-    K.count = (u64 *)(S->host + 16);
-    rc = cube_queue(C, K, blocks, waves, jit, D, stream);
+    K.count = (u64 *)(S->host + 8 * n);
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream);
     if (!rc) rc = cube_wait(K, stream);
     if (rc) {
         (void)hipStreamSynchronize(stream);
         return rc;
     }
-    memcpy(R_hl, S->host, 16);
-    memcpy(&count, S->host + 16, 8);
+    res.assign((const double *)S->host, (const double *)S->host + n);
+    memcpy(&count, S->host + 8 * n, 8);
     return BAT_OK;
 }
 
 // The same on `stream` over device probabilities, results to device memory.
 // ws: a workspace of ws_bytes, or null to take one from the stream's pool.
-int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo &D, hipStream_t stream, double *R,
-               u64 *count, int *status, char *ws, size_t ws_bytes)
+int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo &D, hipStream_t stream, bool grad,
+               double *R, u64 *count, double *dRdp, double *T1, double *T0, int *status, char *ws, size_t ws_bytes)
 {
     bat::CubeParams K;
     unsigned blocks = 0;
     int waves = 0;
     const bool jit = !ws && cube_jit(C);  // (a fixed workspace: no module is loaded)
-    int rc = cube_params(C, nullptr, p_dev, D, K, blocks, waves, jit);
+    int rc = cube_params(C, nullptr, p_dev, D, K, blocks, waves, jit, grad);
     if (rc) return rc;
-    const size_t need = cube_part_bytes(K, blocks);
+    const size_t need = cube_part_bytes(K, blocks, grad);
     void *own = nullptr;
     if (!ws && need) {
         HIPCHK(hipMallocAsync(&own, need, stream));
@@ -1989,11 +2037,14 @@ int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo
     } else if (ws && need > ws_bytes) {
         return fail(BAT_ETOOBIG, "needs %zu bytes of fixed scratch; it holds %zu", need, ws_bytes);
     }
-    cube_parts(K, blocks, ws);
+    cube_parts(K, blocks, grad, ws);
     K.R = R;
     K.count = count;
     K.status = status;
-    rc = cube_queue(C, K, blocks, waves, jit, D, stream);
+    K.dRdp = dRdp;
+    K.T1 = T1;
+    K.T0 = T0;
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream);
     if (own) {
         const hipError_t e = hipFreeAsync(own, stream);
         if (!rc) HIPCHK(e);
@@ -2035,15 +2086,18 @@ int run_sync(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
     TuneChoice tc;
     const bool full = c_lo == 0 && c_hi == (1ull << m);
     if (!p && m > 0) return fail(BAT_EINVAL, "p is NULL");
-    if (full && !tmpl && cubes_wanted(grad)) {
+    if (full && !tmpl && cubes_wanted()) {
         int rc = validate(n, m, arcs, p, s, t);
         if (!rc) rc = current_device(X.D);
         if (rc) return rc;
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C);
         if (cube_fits(C)) {
-            res.assign(2, 0.0);
-            return cube_sync(C, p, X.D, res.data(), count);
+            if (cb_of_arc) {  // (the columns are in arc order)
+                cb_of_arc->resize(m);
+                for (int32_t a = 0; a < m; ++a) (*cb_of_arc)[a] = a;
+            }
+            return cube_sync(C, p, X.D, grad, res, count);
         }
     }
     // any arc order for a whole sweep; a partial range is in the paper's
@@ -2322,7 +2376,7 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
 {
     Request rq{};
     const bool first = S.order < 0;
-    if (first ? cubes_wanted(grad) && !(flags & BAT_FORWARD_ORDER) : S.order == kPermInfluence) {
+    if (first ? cubes_wanted() && !(flags & BAT_FORWARD_ORDER) : S.order == kPermInfluence) {
         // the sub-cube sweep's items
         DeviceInfo D;
         int rc = current_device(D);
@@ -2330,8 +2384,7 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C, first ? 0 : S.items / 32);
         uint64_t bits = fnv_bytes(1469598103934665603ull, C.arc_of_bit.data(), sizeof(int) * C.arc_of_bit.size());
-        if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) || grad ||
-                       !cube_fits(C)))
+        if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) || !cube_fits(C)))
             return fail(BAT_EIO, "the checkpoint's work items are not the ones this library cuts");
         if (cube_fits(C)) {
             if (first) {
@@ -2342,9 +2395,18 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
                 S.parts = std::min<u64>(parts_wanted, cube_items(C));
             }
             u64 c = 0;
-            rc = cube_sync(C, p, D, R_hl, c, S.parts, S.done);
+            std::vector<double> res;
+            rc = cube_sync(C, p, D, grad, res, c, S.parts, S.done);
+            if (rc) return rc;
             *count = c;
-            return rc;
+            R_hl[0] = res[0];
+            R_hl[1] = res[1];
+            if (grad) {
+                std::vector<int> arc(m);
+                for (int32_t a = 0; a < m; ++a) arc[a] = a;
+                split_grad(res, arc, m, nullptr, T1, T0);
+            }
+            return BAT_OK;
         }
     }
     if (first) {
@@ -2925,14 +2987,15 @@ static int async_common(int32_t n, int32_t m, const bat_arc *arcs, const double 
     TuneChoice tc;
     hipStream_t st = (hipStream_t)stream;
     int rc;
-    if (cubes_wanted(grad)) {
+    if (cubes_wanted()) {
         rc = validate(n, m, arcs, nullptr, s, t);
         if (!rc) rc = current_device(X.D);
         if (rc) return rc;
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, false, C);
         if (cube_fits(C))
-            return cube_async(C, p_dev, X.D, st, R_dev, (u64 *)count_dev, status_dev, nullptr, 0);
+            return cube_async(C, p_dev, X.D, st, grad, R_dev, (u64 *)count_dev, dRdp_dev, T1_dev, T0_dev,
+                              (int *)status_dev, nullptr, 0);
     }
     rc = prepare(n, m, arcs, nullptr, s, t, grad, true, nullptr, X, tc);
     if (rc) return rc;
@@ -2981,11 +3044,12 @@ int bat_reliability_noalloc(int32_t n, int32_t m, const bat_arc *arcs, const dou
     rc = noalloc_scratch(X.D.id, ws);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if (cubes_wanted(false)) {
+    if (cubes_wanted()) {
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, false, C);
         if (cube_fits(C, true))
-            return cube_async(C, p_dev, X.D, st, R_dev, (u64 *)count_dev, status_dev, ws, kNoAllocScratchBytes);
+            return cube_async(C, p_dev, X.D, st, false, R_dev, (u64 *)count_dev, nullptr, nullptr, nullptr,
+                              (int *)status_dev, ws, kNoAllocScratchBytes);
     }
     Request rq{};
     rq.n = n; rq.m = m; rq.s = s; rq.t = t; rq.arcs = arcs; rq.p_dev = p_dev;
@@ -3108,7 +3172,7 @@ int bat_jit_source(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t
     if (rc) return rc;
     if ((perm < 0 || perm >= kPermKinds) && perm != kPermInfluence)
         return fail(BAT_EINVAL, "perm %d outside [0, %d)", perm, kPermKinds);
-    if (perm == kPermInfluence && grad != 0) return fail(BAT_EINVAL, "no such sub-cube sweep");
+    if (perm == kPermInfluence && grad < 0) return fail(BAT_EINVAL, "no batched sub-cube sweep of one graph");
     if (grad < -batk::kBatchMaxP || grad > 1) return fail(BAT_EINVAL, "grad %d outside [-%d, 1]", grad, batk::kBatchMaxP);
     if (grad < 0 && (flags & BAT_DIRECTED)) return fail(BAT_EINVAL, "the batched sweep is undirected");
     Plan P;
@@ -3117,7 +3181,7 @@ int bat_jit_source(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t
     else make_plan(n, m, arcs, s, t, P, perm, (flags & BAT_DIRECTED) != 0);
     Options &O = opts();
     const std::string src =
-        perm == kPermInfluence ? cube_source(C, true)
+        perm == kPermInfluence ? cube_source(C, grad != 0, true)
         : grad < 0 ? jit_source(P, false, jit_shape(false, 4, 0, 0, 1), -grad)
                  : jit_source(P, grad != 0,
                               jit_shape(grad != 0, (int)O.block_waves.load(), (int)O.super_restart.load(),

@@ -102,5 +102,7 @@ hipError_t finalize(hipStream_t st, const double *res, const bat::u64 *count, co
 constexpr int kCubeMaxBits = 32;  // counter bits of the ahead-of-time kernels
 hipError_t cube_sweep(hipStream_t st, unsigned blocks, int waves, const bat::CubeParams &P);
 hipError_t cube_finish(hipStream_t st, unsigned blocks, const bat::CubeParams &P);
+hipError_t cube_grad(hipStream_t st, unsigned blocks, int waves, const bat::CubeParams &P);
+hipError_t cube_grad_finish(hipStream_t st, unsigned blocks, const bat::CubeParams &P);
 
 }  // namespace batk

@@ -135,3 +135,31 @@ def test_cube_levels_count_every_vector_once(name, net, directed, levels):
     got = sum(count(P["LEVELS"] - 1, x << top) for x in range(1 << max(0, P["M"] - top)))
     o = oracle.reliability(net.n, net.arcs, net.p, net.s, net.t, directed=directed)
     assert got << (len(net.arcs) - P["M"]) == o.count
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("name,net,directed,levels",
+                         [("grid5x5", W.grid(5, 5), False, 3), ("rand12", W.random_connected(8, 12, 1), False, 2),
+                          ("rand62", W.random_connected(30, 62, 4), False, 3), ("di0", *_cases()[-2][1:], 1)],
+                         ids=["grid5x5", "rand12", "rand62", "di0"])
+def test_cube_source_compiles(tmp_path, name, net, directed, levels, grad):
+    """The specialised kernels through the hiprtc that the library loads (it
+    ends the process where it cannot place a value in a scalar register)."""
+    import subprocess
+    B = _B()
+    rtc = [x.split()[-1] for x in open("/proc/self/maps") if "libhiprtc.so" in x]
+    if not rtc:
+        pytest.skip("no hiprtc library loaded")
+    old = B.bat_get_option("BAT_CUBE_LEVELS")
+    try:
+        B.bat_set_option("BAT_CUBE_LEVELS", levels)
+        src = B.bat_jit_source(net.n, net.arcs, net.s, net.t, grad=grad, perm=5, directed=directed)
+    finally:
+        B.bat_set_option("BAT_CUBE_LEVELS", old)
+    text, out = tmp_path / "k.hip.txt", tmp_path / "k.co"
+    text.write_text(src)
+    import os
+    helper = os.path.join(os.path.dirname(B.__file__), "bat_jitc")
+    subprocess.run([helper, rtc[0], str(text), str(out), "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang",
+                    "-target-feature", "-Xclang", "-packed-fp32-ops"], check=True, capture_output=True)
+    assert out.stat().st_size > 0

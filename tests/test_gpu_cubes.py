@@ -147,3 +147,77 @@ def test_cubes_checkpointed(tmp_path):
     # the file's launch holds when the options have changed since
     assert B.bat_reliability_checkpointed(*args, f) == whole
     assert whole[1] == o.count and abs(whole[0] - o.sum) <= REL * o.sum
+
+
+# T1 and T0: a lane adds its words' terms, all of one sign, by plain fused
+# additions, at most some 2^9 of them between folds at these sizes: 2^9
+# roundings of 1.1e-16 at worst.
+REL_GRAD = 6e-14
+
+
+def _rel(a, b):
+    a, b = np.asarray(a), np.asarray(b)
+    assert np.all(a[b == 0.0] == 0.0)
+    return float(np.max(np.abs(a - b)[b != 0.0] / b[b != 0.0], initial=0.0))
+
+
+@pytest.mark.parametrize("levels", [1, 2, 3])
+@pytest.mark.parametrize("split,jit", [(1, 0), (3, 0), (16, 0), (2, 1)])
+def test_cube_gradients_vs_oracle(levels, split, jit):
+    B = _B()
+    nets = _nets()
+    nets.append((W.bridge(0.9).with_p([1.0, 0.0, 0.7, 1.0, 0.0]), False))
+    nets.append((W.Network("loops", 4, [(0, 1), (1, 1), (1, 3), (2, 2), (0, 2)], 0, 3,
+                           np.array([.9, .5, .8, .3, .7])), False))
+    if jit:
+        nets = [nets[k] for k in (0, 4, 9, 12, 14, 16, 18, len(nets) - 2)]
+    with options(BAT_CUBES=1, BAT_JIT=jit, BAT_CUBE_LEVELS=levels, BAT_CUBE_SPLIT=split):
+        for net, directed in nets:
+            print("cube gradients", levels, split, jit, net.name, net.n, net.m, flush=True)
+            g = B.bat_reliability_ex(net.n, net.arcs, net.p, net.s, net.t, directed=directed, grad=True)
+            li = B.bat_last_launch()
+            assert li.perm == 5 and li.specialised == jit
+            o = oracle.reliability(net.n, net.arcs, net.p, net.s, net.t, grad=True, directed=directed)
+            assert g.count == o.count, net.name
+            assert abs(g.R - o.sum) <= REL * o.sum, net.name
+            assert _rel(g.T1, o.T1) <= REL_GRAD and _rel(g.T0, o.T0) <= REL_GRAD, net.name
+
+
+@pytest.mark.parametrize("n,m", [(13, 25), (14, 27), (20, 30), (12, 32), (16, 34)])
+def test_cube_gradients_larger(n, m):
+    """The default launch at the sizes where levels, splits and the
+    specialised build begin; the same bits twice and through device
+    pointers."""
+    import torch
+    from paper_2209_09711_amd.torch_fn import reliability
+    B = _B()
+    net = W.random_connected(n, m, seed=m, p_lo=0.5, p_hi=0.99)
+    print("cube gradients", net.name, flush=True)
+    g = B.bat_reliability_grad(net.n, net.arcs, net.p, net.s, net.t)
+    assert B.bat_last_launch().perm == 5
+    h = B.bat_reliability_grad(net.n, net.arcs, net.p, net.s, net.t)
+    assert (g.R, g.count) == (h.R, h.count) and np.array_equal(g.T1, h.T1) and np.array_equal(g.T0, h.T0)
+    Rd, cd = frontier_dp.reliability(net.n, net.arcs, net.p, net.s, net.t)
+    T1, T0 = frontier_dp.gradient(net.n, net.arcs, net.p, net.s, net.t)
+    assert g.count == cd and abs(g.R - Rd) <= REL * Rd
+    assert _rel(g.T1, T1) <= REL_GRAD and _rel(g.T0, T0) <= REL_GRAD
+    p = torch.tensor(net.p, dtype=torch.float64, device="cuda", requires_grad=True)
+    R, cnt = reliability(p, net.n, net.arcs, net.s, net.t)
+    assert int(cnt) == g.count
+    R.backward()
+    assert abs(R.item() - g.R) <= 2.3e-16 * g.R
+    np.testing.assert_allclose(p.grad.cpu().numpy(), g.T1 - g.T0, rtol=0, atol=REL_GRAD)
+
+
+def test_cube_gradients_checkpointed(tmp_path):
+    B = _B()
+    net = W.random_connected(12, 24, seed=22, p_lo=0.4, p_hi=0.99)
+    args = (net.n, net.arcs, net.p, net.s, net.t, net.m - 2)
+    whole = B.bat_reliability_checkpointed(*args, None, grad=True)
+    f = str(tmp_path / "g.ckpt")
+    assert B.bat_reliability_checkpointed(*args, f, grad=True, max_chunks=1) is None
+    assert open(f).read().splitlines()[3].startswith("launch order=5 ")
+    got = B.bat_reliability_checkpointed(*args, f, grad=True)
+    assert (got.R, got.count) == (whole.R, whole.count) and np.array_equal(got.dRdp, whole.dRdp)
+    o = oracle.net_reliability(net, grad=True)
+    assert got.count == o.count and _rel(got.T1, o.T1) <= REL_GRAD and _rel(got.T0, o.T0) <= REL_GRAD
