@@ -37,7 +37,8 @@ def embed_device_source() -> str:
     # digest of everything the ahead-of-time kernels are compiled from,
     # reported in each launch's kernel identity
     h = hashlib.sha256()
-    for f in ("bat_device.hpp", "bat_cube.hpp", "bat_kernels.hip", "bat_cube.hip", "bat_launch.hpp", "bat_ms.hip"):
+    for f in ("bat_device.hpp", "bat_cube.hpp", "bat_kernels.hip", "bat_cube.hip", "bat_cube_batch.hip",
+              "bat_launch.hpp", "bat_ms.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     out = os.path.join(CSRC, "bat_device_embed.inc")
@@ -58,7 +59,8 @@ def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + f".tmp{os.getpid()}"
     cmd = [hipcc, *HIP_FLAGS, "-shared", f"-I{INCLUDE}", f"-I{CSRC}",
-           *(os.path.join(CSRC, f) for f in ("bat_kernels.hip", "bat_cube.hip", "bat_ms.hip", "bat_host.cpp")),
+           *(os.path.join(CSRC, f) for f in ("bat_kernels.hip", "bat_cube.hip", "bat_cube_batch.hip", "bat_ms.hip",
+                                             "bat_host.cpp")),
            "-o", tmp, "-lhiprtc"]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -26,7 +26,7 @@ __global__ void __launch_bounds__(bat::kCubeWaves *bat::kWave) k_cube_fwd(bat::C
     __shared__ bat::CubeTables T;
     __shared__ bat::CubeWave W[bat::kCubeWaves];
     bat::CubeArgs *P = cube_args();
-    bat::cube_kernel(P, T, W, bat::CubeDyn{P, 0u});
+    bat::cube_kernel(P, T, W, bat::CubeDyn<bat::CubeArgs>{P, 0u});
 }
 
 __global__ void __launch_bounds__(bat::kCubeWaves *bat::kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -37,7 +37,7 @@ k_cube_grad(bat::CubeParams)
     __shared__ bat::CubeGradWave W[bat::kCubeWaves];
     __shared__ double cols[bat::kGradUnits][2 + 2 * batk::kCubeMaxBits];
     bat::CubeArgs *P = cube_args();
-    bat::cube_grad_kernel(P, T, X, W, cols, bat::CubeDyn{P, 0u});
+    bat::cube_grad_kernel(P, T, X, W, cols, bat::CubeDyn<bat::CubeArgs>{P, 0u});
 }
 
 constexpr int kFinishThreads = 1024;

@@ -143,14 +143,15 @@ __device__ __forceinline__ double cube_q(const CubeTables &T, u32 M, u32 cb, u32
     return x ? p : 1.0 - p;
 }
 
+__device__ __forceinline__ double cube_p(CubeArgs *P, u32 a) { return P->p_dev ? P->p_dev[a] : P->p[a]; }
+__device__ __forceinline__ const __attribute__((address_space(4))) u32 *cube_steps(CubeArgs *P) { return P->step; }
+
 // The block's probability tables (all threads).
-__device__ __forceinline__ void cube_tables(CubeArgs *P, CubeTables &T)
+template <class Args>
+__device__ __forceinline__ void cube_tables(Args *P, CubeTables &T)
 {
     const u32 tid = threadIdx.x, nt = blockDim.x, M = P->M, levels = P->levels;
-    if (tid < M) {
-        const u32 a = P->arc_of_bit[tid];
-        T.pr[tid] = P->p_dev ? P->p_dev[a] : P->p[a];
-    }
+    if (tid < M) T.pr[tid] = cube_p(P, P->arc_of_bit[tid]);
     __syncthreads();
     for (u32 i = tid; i < levels * 256u; i += nt) {
         const u32 l = i >> 8, y = i & 255u, c0 = kCubeGroup * l;
@@ -242,8 +243,9 @@ __device__ __forceinline__ void cube_enqueue(unsigned short *q, u32 U, u32 e, u3
     "v_and_or_b32 v64, v64, s73, %[x]\n\t"
 #define BAT_CUBE_MASK(v, cb) "v_bfe_i32 " v ", %[c], " cb ", 1\n\t"
 
+template <class Args>
 struct CubeDyn {
-    CubeArgs *P;
+    Args *P;
     u32 base;  // the item's counter bits
 
     __device__ __forceinline__ u32 levels() const { return P->levels; }
@@ -258,7 +260,7 @@ struct CubeDyn {
         const u32 c = base | rel | ((pi & 1u) ? (1u << (kCubeGroup * ((pi + 1u) >> 1))) - 1u : 0u);
         const u32 result = P->prog[pi].result;
         if (result >= (u32)kCubeSlots) return live && result == kCubeAlways ? ~0u : 0u;
-        const __attribute__((address_space(4))) u32 *steps = P->step;
+        const __attribute__((address_space(4))) u32 *steps = cube_steps(P);
         u32 off = P->prog[pi].first * 4u, n = P->prog[pi].octets, x, out;
         asm volatile(
             "s_mov_b32 s74, m0\n\t"
@@ -365,9 +367,9 @@ struct CubeStatic {
 };
 
 // One wavefront's share of the sweep.
-template <class Clo>
+template <class Clo, class Args = CubeArgs>
 struct CubeSweep {
-    CubeArgs *P;
+    Args *P;
     const CubeTables &T;
     CubeWave &W;
     Clo clo;

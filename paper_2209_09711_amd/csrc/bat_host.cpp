@@ -1704,12 +1704,18 @@ bool cubes_wanted()
 // but run longer chains of closures per wavefront; they win from 33 arcs on
 // (specialised: 32 arcs 126 us against 94 us, 33 arcs 110 us against 131 us,
 // 35 arcs 0.14 ms against 0.39 ms).
-void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed,
-                batcube::CubePlan &C, int levels = 0)
+std::vector<char> cube_arcs(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed)
 {
     std::vector<char> rel = relevance(n, m, arcs, s, t, directed);
     for (int32_t i = 0; i < m; ++i)
         if (arcs[i].u == arcs[i].v) rel[i] = 0;
+    return rel;
+}
+
+void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed,
+                batcube::CubePlan &C, int levels = 0)
+{
+    const std::vector<char> rel = cube_arcs(n, m, arcs, s, t, directed);
     if (levels <= 0) levels = (int)opts().cube_levels.load();
     int M = 0;
     for (int32_t i = 0; i < m; ++i) M += rel[i] ? 1 : 0;
@@ -1721,6 +1727,31 @@ void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t,
 // part j of `parts` (a power of two, at most the items): the items that are
 // j modulo parts.
 u64 cube_items(const batcube::CubePlan &C) { return 1ull << std::max(0, C.M - C.rel_bits()); }
+
+// The closures as the ahead-of-time kernels read them.
+bool cube_pack(const batcube::CubePlan &C, bat::CubeProg *prog, u32 *step)
+{
+    u32 at = 0;
+    for (int k = 0; k < 2 * C.levels - 1; ++k) {
+        const batcube::Program &pr = C.prog[k];
+        bat::CubeProg &q = prog[k];
+        q.first = at;
+        q.octets = (u32)std::max<size_t>(1, (pr.step.size() + 7) / 8);
+        q.result = pr.result == -1 ? bat::kCubeNever : pr.result == -2 ? bat::kCubeAlways : (u32)pr.result;
+        q.word = (u32)(bat::kCubeGroup * ((k + 1) / 2));
+        if (at + 8 * q.octets > (u32)bat::kCubeSteps) return false;
+        for (u32 i = 0; i < 8 * q.octets; ++i) {
+            if (i < pr.step.size()) {
+                const batcube::Step &x = pr.step[i];
+                step[at + i] = (u32)x.a | (u32)x.b << 8 | (u32)x.d << 16 | (x.assign ? 0u : 1u << 31);
+            } else {
+                step[at + i] = 1u << 31;  // slot 0 |= itself
+            }
+        }
+        at += 8 * q.octets;
+    }
+    return true;
+}
 
 // Most chunks of units a gradient sweep is cut into, while a block takes no
 // more than kGradUnits of them.
@@ -1784,25 +1815,7 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     K.p_dev = p_dev;
     if (p_host) memcpy(K.p, p_host, sizeof(double) * C.m);
     for (int c = 0; c < C.M; ++c) K.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
-    u32 at = 0;
-    for (int k = 0; !jit && k < 2 * C.levels - 1; ++k) {
-        const batcube::Program &pr = C.prog[k];
-        bat::CubeProg &q = K.prog[k];
-        q.first = at;
-        q.octets = (u32)std::max<size_t>(1, (pr.step.size() + 7) / 8);
-        q.result = pr.result == -1 ? bat::kCubeNever : pr.result == -2 ? bat::kCubeAlways : (u32)pr.result;
-        q.word = (u32)(bat::kCubeGroup * ((k + 1) / 2));
-        if (at + 8 * q.octets > (u32)bat::kCubeSteps) return fail(BAT_EDEVICE, "sub-cube closures of too many steps");
-        for (u32 i = 0; i < 8 * q.octets; ++i) {
-            if (i < pr.step.size()) {
-                const batcube::Step &x = pr.step[i];
-                K.step[at + i] = (u32)x.a | (u32)x.b << 8 | (u32)x.d << 16 | (x.assign ? 0u : 1u << 31);
-            } else {
-                K.step[at + i] = 1u << 31;  // slot 0 |= itself
-            }
-        }
-        at += 8 * q.octets;
-    }
+    if (!jit && !cube_pack(C, K.prog, K.step)) return fail(BAT_EDEVICE, "sub-cube closures of too many steps");
     return BAT_OK;
 }
 
@@ -3423,6 +3436,263 @@ int bat_autotune(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int
 
 }  // extern "C"
 
+// ------------------------------------------------ batched sub-cube sweeps
+// An entry: a graph with probability vectors [n_p][m].
+struct CubeJob {
+    int graph;  // entries of one graph follow each other
+    int32_t n, m, s, t;
+    const bat_arc *arcs;
+    const double *p;
+    int n_p;
+    std::vector<char> rel;  // arcs to enumerate
+    int M, levels;
+    u32 win_lo, win_last;   // (one level) vectors asked for, in arc order
+    u64 items;
+    u32 units, first_block, n_blocks;
+};
+
+// Most enumerated arcs swept with one level: 22 and 23 measured alike (0.67
+// and 0.71 ms with 3 vectors, 1.64 and 1.74 ms with 32), 20 and 17 slower.
+constexpr int kCubeBatchOneLevel = 22;
+constexpr int kCubeBatchP = 32;  // most probability vectors of an entry
+constexpr u64 kCubeBatchItems = 256;  // most work items of a block
+constexpr size_t kCubeBatchJobs = 1024;  // most entries of a sweep (about 12 KiB of staging each)
+
+// Vectors a lane group of the kernel is made for.
+int cube_batch_width(int n_p) { return n_p <= 1 ? 1 : n_p <= 4 ? 4 : n_p <= 8 ? 8 : n_p <= 16 ? 16 : 32; }
+
+// All jobs (of at most kCubeMaxBits enumerated arcs, the largest first) in
+// one sweep, many of them in two launches so that the device works on the
+// largest while the host still plans the others.  sums: [jobs][width]; fits = false
+// (nothing to wait for) when a plan needs more than the kernels hold.
+// At most kCubeBatchJobs at once, which bounds the buffers.
+int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std::vector<bat::double2_t> &sums,
+                   std::vector<u64> &counts, bool &fits);
+int cube_batch_all(std::vector<CubeJob> &jobs, int width, const DeviceInfo &D, std::vector<bat::double2_t> &sums,
+                   std::vector<u64> &counts, bool &fits)
+{
+    u64 start = 0;
+    int32_t blocks = 0, steps = 0;
+    for (size_t at = 0; at < jobs.size(); at += kCubeBatchJobs) {
+        int rc = cube_batch_run(&jobs[at], std::min(jobs.size() - at, kCubeBatchJobs), width, D, sums, counts, fits);
+        if (rc || !fits) return rc;
+        // the launch report covers all of them
+        u64 *slot = t_state.diag.slots + 4 * (t_state.cube_seq % kDiagSlots);
+        if (at == 0) start = slot[0];
+        slot[0] = start;
+        t_state.info.n_chunks = blocks += t_state.info.n_chunks;
+        t_state.info.relaxations = steps += t_state.info.relaxations;
+    }
+    return BAT_OK;
+}
+
+int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std::vector<bat::double2_t> &sums,
+                   std::vector<u64> &counts, bool &fits)
+{
+    fits = true;
+    hipStream_t st;
+    int rc = thread_stream(D.id, st);
+    if (rc) return rc;
+    const u64 waves = width == 1 ? bat::kCubeWaves : batk::kCubeBatchWaves;
+    u64 blocks = 0, items = 0;
+    int m_max = 0;
+    for (size_t i = 0; i < n; ++i) {
+        CubeJob &J = jobs[i];
+        const int rb = bat::kCubeGroup * J.levels +
+                       std::max(0, std::min(bat::kLaneBits, J.M - bat::kCubeGroup * J.levels));
+        J.items = 1ull << std::max(0, J.M - rb);
+        items += J.items;
+        m_max = std::max(m_max, J.m);
+    }
+    // items per block: enough to be worth its tables, few enough for an even
+    // end (256 graphs x 32 vectors: 1.5 ms with 8 blocks per CU, 1.62 ms with
+    // 4, 3.2 ms with 32; one vector, whose blocks are a quarter the size: 0.58
+    // ms with 32, 0.72 ms with 8)
+    const u64 per_cu = width == 1 ? 32 : 8;
+    u64 units = waves;
+    while (units < kCubeBatchItems && items / (2 * units) >= per_cu * (u64)D.cus) units *= 2;
+    for (size_t i = 0; i < n; ++i) {
+        CubeJob &J = jobs[i];
+        J.units = (u32)std::min<u64>(J.items, units);
+        J.first_block = (u32)blocks;
+        J.n_blocks = (u32)((J.items + J.units - 1) / J.units);
+        blocks += J.n_blocks;
+    }
+    if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)blocks);
+    // records: the entry, its steps, its probabilities
+    const size_t o_step = align_up(sizeof(bat::BatchCube), 64);
+    const size_t o_p = o_step + align_up(sizeof(u32) * (bat::kCubeSteps + 4), 64);
+    const size_t stride = align_up(o_p + sizeof(double) * (size_t)width * (size_t)m_max, 256);
+    const size_t o_ent = align_up(sizeof(u32) * blocks, 256), in_bytes = o_ent + stride * n;
+    const size_t o_part = align_up(in_bytes, 256), o_pc = o_part + 16 * (size_t)width * blocks;
+    const size_t o_done = o_pc + 8 * blocks, h_sums = in_bytes, h_cnt = h_sums + 16 * (size_t)width * n;
+    Scratch *S = nullptr;
+    rc = scratch_reserve(D.id, st, o_done + 8, h_cnt + 8 * n, S);
+    if (rc) return rc;
+    bat::BatchCubes L;
+    memset(&L, 0, sizeof L);
+    L.entries = S->dev + o_ent;
+    L.stride = (u32)stride;
+    L.block_entry = (const u32 *)S->dev;
+    L.part = (bat::double2_t *)(S->dev + o_part);
+    L.pcount = (u64 *)(S->dev + o_pc);
+    L.done = (u32 *)(S->dev + o_done);
+    L.sums = (bat::double2_t *)(S->host + h_sums);
+    L.counts = (u64 *)(S->host + h_cnt);
+    u64 *slot = nullptr;
+    rc = diag_next(st, slot, L.seq);
+    if (rc) return rc;
+    L.diag = slot;
+    u32 *be = (u32 *)S->host;
+    for (size_t i = 0; i < n; ++i)
+        for (u32 b = 0; b < jobs[i].n_blocks; ++b) be[jobs[i].first_block + b] = (u32)i;
+    batcube::CubePlan C;
+    size_t sent = 0, first = 0;
+    u64 steps = 0;
+    const bool two = n > 64;
+    SideStreams *SS = nullptr;
+    if (two) {
+        rc = side_streams(D.id, SS);
+        if (rc) return rc;
+    }
+    size_t chunk = two ? n / 8 : n;
+    for (size_t i = 0; i < n; ++i) {
+        CubeJob &J = jobs[i];
+        char *rec = S->host + o_ent + stride * i;
+        if (i == 0 || J.graph != jobs[i - 1].graph)
+            batcube::make_cube_plan(J.n, J.m, J.arcs, J.rel, J.s, J.t, false, J.levels, C);
+        bat::BatchCube &E = *(bat::BatchCube *)rec;
+        memset(&E, 0, sizeof E);
+        E.m = (u32)J.m;
+        E.M = (u32)C.M;
+        E.levels = (u32)C.levels;
+        E.lane_bits = (u32)C.lane_bits;
+        E.n_p = (u32)J.n_p;
+        E.split = 1;
+        E.units = J.units;
+        E.first_block = J.first_block;
+        E.n_blocks = J.n_blocks;
+        E.win_lo = J.win_lo;
+        E.win_last = J.win_last;
+        E.n_items = J.items;
+        E.item_mul = 0x9E3779B97F4A7C15ull;
+        E.item_mask = J.items - 1;
+        E.p = (const double *)(S->dev + o_ent + stride * i + o_p);
+        E.step = (const u32 *)(S->dev + o_ent + stride * i + o_step);
+        for (int c = 0; c < C.M; ++c) E.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
+        bool ok = C.slots <= bat::kCubeSlots && C.levels == J.levels;
+        bat::CubeProg prog[bat::kCubeProgs];
+        ok = ok && cube_pack(C, prog, (u32 *)(rec + o_step));
+        if (!ok) {
+            fits = false;
+            if (SS) HIPCHK(hipStreamSynchronize(SS->s[0]));
+            HIPCHK(hipStreamSynchronize(st));
+            return BAT_OK;
+        }
+        memcpy(E.prog, prog, sizeof E.prog);
+        if (J.m > 0) memcpy(rec + o_p, J.p, sizeof(double) * (size_t)J.n_p * (size_t)J.m);
+        steps += C.M;
+        if (i + 1 == n || i + 1 - first >= chunk) {
+            const size_t to = o_ent + stride * (i + 1);
+            // the later launch runs beside the first one, whose last blocks
+            // leave CUs idle
+            const hipStream_t ls = first ? SS->s[0] : st;
+            HIPCHK(hipMemcpyAsync(S->dev + sent, S->host + sent, to - sent, hipMemcpyHostToDevice, ls));
+            sent = to;
+            L.block0 = jobs[first].first_block;
+            HIPCHK(batk::cube_batch(ls, (unsigned)(J.first_block + J.n_blocks - L.block0), width, L));
+            first = i + 1;
+            chunk = n;
+        }
+    }
+    if (SS) {
+        HIPCHK(hipEventRecord(SS->join[0], SS->s[0]));
+        HIPCHK(hipStreamWaitEvent(st, SS->join[0], 0));
+    }
+    HIPCHK(batk::cube_batch_finish(st, (unsigned)n, width, L));
+    bat::CubeParams K;
+    K.diag = L.diag;
+    K.seq = L.seq;
+    rc = cube_wait(K, st);
+    if (rc) {
+        (void)hipStreamSynchronize(st);
+        return rc;
+    }
+    sums.insert(sums.end(), L.sums, L.sums + n * (size_t)width);
+    counts.insert(counts.end(), L.counts, L.counts + n);
+    bat_launch_info &I = t_state.info;
+    memset(&I, 0, sizeof I);
+    I.n_chunks = (int32_t)std::min<u64>(blocks, 0x7fffffff);
+    I.relaxations = (int32_t)std::min<u64>(steps, 0x7fffffff);
+    I.perm = kPermInfluence;
+    I.check_every = 1;
+    I.item_order = 1;
+    I.block_waves = (int32_t)waves;
+    I.kernel_id = aot_kernel_id("k_cube_batch", width, false);
+    t_state.have_launch = true;
+    t_state.cube_seq = L.seq;
+    t_state.cube_dev = D.id;
+    t_state.cube_khz = D.clock_khz;
+    return BAT_OK;
+}
+
+// A batch in that form; fits = false where a graph is too large for it.
+int cube_batched(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_offsets, const bat_arc *arcs,
+                 const int32_t *s, const int32_t *t, int32_t n_pvec, const double *p, const DeviceInfo &D, double *R_out,
+                 uint64_t *counts_out, bool &fits)
+{
+    fits = false;
+    const int groups = (n_pvec + kCubeBatchP - 1) / kCubeBatchP, per = (n_pvec + groups - 1) / groups;
+    const int width = cube_batch_width(per);
+    std::vector<std::vector<char>> rel(n_graphs);
+    std::vector<int> M(n_graphs, 0), order(n_graphs);
+    u64 vectors = 0;
+    for (int32_t g = 0; g < n_graphs; ++g) {
+        const int32_t m = arc_offsets[g + 1] - arc_offsets[g];
+        rel[g] = cube_arcs(n_nodes[g], m, arcs + arc_offsets[g], s[g], t[g], false);
+        rel[g].resize(m);
+        for (char x : rel[g]) M[g] += x ? 1 : 0;
+        if (M[g] > batk::kCubeMaxBits) return BAT_OK;
+        order[g] = g;
+        vectors += 1ull << m;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return M[a] > M[b]; });
+    std::vector<CubeJob> jobs;
+    std::vector<std::pair<int, int>> of;  // graph, first vector
+    for (int g : order)
+        for (int b = 0; b < n_pvec; b += per) {
+            CubeJob J;
+            J.graph = g;
+            J.n = n_nodes[g];
+            J.m = arc_offsets[g + 1] - arc_offsets[g];
+            J.s = s[g];
+            J.t = t[g];
+            J.arcs = arcs + arc_offsets[g];
+            J.p = p + (int64_t)n_pvec * arc_offsets[g] + (int64_t)b * J.m;
+            J.n_p = std::min(per, n_pvec - b);
+            J.rel = rel[g];
+            J.M = M[g];
+            J.levels = M[g] <= kCubeBatchOneLevel ? 1 : 2;
+            if (opts().cube_levels.load() > 0)
+                J.levels = std::max(1, std::min({(int)opts().cube_levels.load(), 2, J.M / bat::kCubeGroup}));
+            J.win_lo = 0;
+            J.win_last = ~0u;
+            jobs.push_back(std::move(J));
+            of.push_back({g, b});
+        }
+    std::vector<bat::double2_t> sums;
+    std::vector<u64> counts;
+    int rc = cube_batch_all(jobs, width, D, sums, counts, fits);
+    if (rc || !fits) return rc;
+    for (size_t i = 0; i < jobs.size(); ++i) {
+        for (int q = 0; q < jobs[i].n_p; ++q)
+            R_out[(size_t)of[i].first * n_pvec + of[i].second + q] = sums[i * width + q].x + sums[i * width + q].y;
+        counts_out[of[i].first] = counts[i];
+    }
+    t_state.info.vectors = vectors;
+    return BAT_OK;
+}
+
 // Tuned knobs of the batched launch: chained iteration bits and the
 // per-wavefront segment size, cached under the batch's structure.
 struct BatchTune {
@@ -3430,6 +3700,7 @@ struct BatchTune {
     int seg = -1;    // -1: batk::kBatchSegLog
     int jit_arcs = -1;  // graphs with at least this many arcs run graph-specialised (0: none; -1: option)
     int streams = -1;   // side streams of the specialised kernels (0: the thread's stream; -1: option, else 3)
+    int cubes = 0;      // (forced only) sub-cube sweeps
 };
 std::mutex g_btune_mu;
 std::map<std::string, BatchTune> g_btune;
@@ -3450,6 +3721,13 @@ std::string batch_key(int device, int32_t n_graphs, const int32_t *n_nodes, cons
     mix(t, sizeof(int32_t) * n_graphs);
     return std::to_string(device) + " batch " + std::to_string(n_graphs) + " " + std::to_string(n_pvec) + " " +
            std::to_string(h);
+}
+
+bool batch_cubes_wanted()
+{
+    const Options &o = opts();
+    return cubes_wanted() && (o.cubes.load() == 1 || (o.batch_jit_arcs.load() < 0 && o.batch_streams.load() < 0 &&
+                                                      o.batch_acc.load() == 1));
 }
 
 int batched_impl(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_offsets, const bat_arc *arcs,
@@ -3475,6 +3753,16 @@ int batched_impl(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_of
     DeviceInfo D;
     int rc = current_device(D);
     if (rc) return rc;
+    // sub-cube sweeps unless a knob of the plain launch has been set; they
+    // have none to tune (256 graphs of 16 to 28 arcs x 32 p-vectors: 2.9 ms
+    // a call against 11.6 ms with the tuned plain launch, 16 of 8 to 20 arcs
+    // x 3: 0.10 ms against 0.9 ms)
+    if (force ? force->cubes != 0 : batch_cubes_wanted()) {
+        bool fits = false;
+        rc = cube_batched(n_graphs, n_nodes, arc_offsets, arcs, s, t, n_pvec, p, D, R_out, counts_out, fits);
+        if (rc || fits) return rc;
+        if (force) return BAT_PENDING;
+    }
     hipStream_t st;
     rc = thread_stream(D.id, st);
     if (rc) return rc;
@@ -3803,6 +4091,27 @@ extern "C" int bat_autotune_batched(int32_t n_graphs, const int32_t *n_nodes, co
     // (a batch is one launch: sampling it would change its load balance)
     double best = 1e300;
     BatchTune bb;
+    // sub-cube sweeps have no knobs, so where they are taken the plain
+    // launch, slower on every batch measured, is not timed
+    if (batch_cubes_wanted()) {
+        BatchTune c;
+        c.cubes = 1;
+        for (int rep = 0; rep < 3; ++rep) {
+            rc = batched_impl(n_graphs, n_nodes, arc_offsets, arcs, s, t, n_pvec, p, R.data(), cnt.data(), &c);
+            if (rc == BAT_PENDING) break;  // a graph too large for them
+            if (rc) return rc;
+            bat_launch_info li;
+            rc = bat_last_launch(&li);
+            if (rc) return rc;
+            if (rep > 0) best = std::min(best, li.kernel_ms);
+        }
+        if (verbose) fprintf(stderr, "bat_autotune_batched: sub-cubes -> %.3f ms\n", best);
+        if (rc == BAT_OK) {
+            if (best_kernel_ms) *best_kernel_ms = best;
+            t_err.clear();
+            return BAT_OK;
+        }
+    }
     for (int seg : {6, 5, 4})
         for (int chain : {0, 3, 4, 5, 6}) {
             if (chain > seg) continue;

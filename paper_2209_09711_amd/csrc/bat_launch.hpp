@@ -6,6 +6,38 @@
 #include "bat_device.hpp"
 #include "bat_cube.hpp"
 
+namespace bat {
+
+// An entry of a batched sub-cube launch: a graph with some of its
+// probability vectors, in device memory.
+struct BatchCube {
+    u32 m, M, levels, lane_bits;
+    u32 n_p;                  // probability vectors
+    u32 split;                // 1
+    u32 units;                // work items per block
+    u32 first_block, n_blocks;
+    u32 win_lo, win_last;     // one level only: the vectors first and last asked for
+    u64 n_items, item_mul, item_mask;
+    const double *p;          // [n_p][m]
+    const u32 *step;          // (read 16 bytes past the last)
+    CubeProg prog[3];
+    unsigned char arc_of_bit[64];
+};
+
+struct BatchCubes {
+    const char *entries;      // one BatchCube every `stride` bytes
+    u32 stride, block0;       // first block of this launch
+    const u32 *block_entry;   // of every block
+    double2_t *part;          // [blocks][pw]
+    u64 *pcount;              // [blocks]
+    u32 *done;
+    double2_t *sums;          // [entries][pw], on the host
+    u64 *counts;              // [entries], on the host
+    u64 *diag, seq;           // as in CubeParams
+};
+
+}  // namespace bat
+
 namespace batk {
 
 // ---- batched form: many graphs x many probability vectors in one launch.
@@ -104,5 +136,11 @@ hipError_t cube_sweep(hipStream_t st, unsigned blocks, int waves, const bat::Cub
 hipError_t cube_finish(hipStream_t st, unsigned blocks, const bat::CubeParams &P);
 hipError_t cube_grad(hipStream_t st, unsigned blocks, int waves, const bat::CubeParams &P);
 hipError_t cube_grad_finish(hipStream_t st, unsigned blocks, const bat::CubeParams &P);
+
+// ---- many of them in one launch (bat_cube_batch.hip); pw: 1, 4, 8, 16 or 32
+// probability vectors per entry
+constexpr int kCubeBatchWaves = 16;  // wavefronts of a block (pw > 1)
+hipError_t cube_batch(hipStream_t st, unsigned blocks, int pw, const bat::BatchCubes &L);
+hipError_t cube_batch_finish(hipStream_t st, unsigned entries, int pw, const bat::BatchCubes &L);
 
 }  // namespace batk

@@ -221,3 +221,79 @@ def test_cube_gradients_checkpointed(tmp_path):
     assert (got.R, got.count) == (whole.R, whole.count) and np.array_equal(got.dRdp, whole.dRdp)
     o = oracle.net_reliability(net, grad=True)
     assert got.count == o.count and _rel(got.T1, o.T1) <= REL_GRAD and _rel(got.T0, o.T0) <= REL_GRAD
+
+
+@pytest.mark.parametrize("levels", [0, 1, 2])
+@pytest.mark.parametrize("n_pvec", [1, 2, 5, 12, 32, 33])
+def test_cube_batches_vs_oracle(n_pvec, levels):
+    """Batches by sub-cubes: one kernel for each number of vectors a word's
+    sum is spread over, graphs of no arc, fewer arcs than a word, one and
+    several work items, probabilities of 1; the same bits twice."""
+    B = _B()
+    rng = np.random.default_rng(2000 + n_pvec)
+    graphs, pblocks = [], []
+    for k in range(13):
+        if k % 5 == 4:
+            net = W.random_multigraph(int(rng.integers(2, 7)), int(rng.integers(0, 12)), seed=int(rng.integers(1 << 30)))
+        else:
+            n = int(rng.integers(3, 12))
+            net = W.random_connected(n, int(rng.integers(n - 1, min(17, n * (n - 1) // 2) + 1)),
+                                     seed=int(rng.integers(1 << 30)))
+        s, t = (int(x) for x in rng.choice(net.n, 2, replace=False))
+        graphs.append((net.n, net.arcs, s, t))
+        pblocks.append(np.where(rng.random((n_pvec, len(net.arcs))) < 0.05, 1.0,
+                                rng.uniform(0.0, 1.0, (n_pvec, len(net.arcs)))))
+    with options(BAT_CUBE_LEVELS=levels):
+        print("cube batch", levels, n_pvec, flush=True)
+        R, cnt = B.bat_reliability_batched(graphs, pblocks)
+        assert B.bat_last_launch().perm == 5
+        R2, cnt2 = B.bat_reliability_batched(graphs, pblocks)
+    assert np.array_equal(R, R2) and np.array_equal(cnt, cnt2)
+    for g, (n, arcs, s, t) in enumerate(graphs):
+        for j in sorted({g % n_pvec, n_pvec - 1}):
+            o = oracle.reliability(n, arcs, pblocks[g][j], s, t)
+            assert cnt[g] == o.count and abs(R[g, j] - o.sum) <= REL_GRAD * o.sum, (g, j)
+
+
+@pytest.mark.parametrize("n_pvec", [1, 20])
+def test_cube_batch_two_launches(n_pvec):
+    """More graphs than one launch takes, up to 27 arcs, against single
+    sweeps; a graph of more arcs than the kernels hold sends the whole batch
+    to the plain launch."""
+    B = _B()
+    rng = np.random.default_rng(2100)
+    graphs, pblocks = [], []
+    for k in range(70):
+        m = 27 if k == 33 else 9 + k % 16
+        net = W.random_connected(max(6, m // 2), m, seed=3000 + k)
+        graphs.append((net.n, net.arcs, net.s, net.t))
+        pblocks.append(rng.uniform(0.4, 0.99, (n_pvec, m)))
+    print("cube batch of 70", n_pvec, flush=True)
+    R, cnt = B.bat_reliability_batched(graphs, pblocks)
+    assert B.bat_last_launch().perm == 5
+    for g in range(0, 70, 3):
+        n, arcs, s, t = graphs[g]
+        Rg, cg = B.bat_reliability(n, arcs, pblocks[g][g % n_pvec], s, t)
+        assert cnt[g] == cg and abs(R[g, g % n_pvec] - Rg) <= REL_GRAD * Rg
+    ring = (34, [(i, (i + 1) % 34) for i in range(34)], 0, 17)
+    p = rng.uniform(0.9, 0.999, (n_pvec, 34))
+    R, cnt = B.bat_reliability_batched(graphs[:2] + [ring], pblocks[:2] + [p])
+    assert B.bat_last_launch().perm != 5
+    want = 1.0 - (1.0 - np.prod(p[:, :17], axis=1)) * (1.0 - np.prod(p[:, 17:], axis=1))
+    assert np.allclose(R[2], want, rtol=1e-13, atol=0) and cnt[2] == (1 << 34) - ((1 << 17) - 1) ** 2
+
+
+def test_cube_batch_of_many_entries():
+    """More entries than one sweep takes."""
+    B = _B()
+    rng = np.random.default_rng(2200)
+    nets = [W.random_connected(6 + k % 4, 9 + k % 5, seed=4000 + k) for k in range(23)]
+    graphs = [(nets[k % 23].n, nets[k % 23].arcs, 0, nets[k % 23].n - 1) for k in range(1100)]
+    pblocks = [rng.uniform(0.1, 0.99, (2, len(g[1]))) for g in graphs]
+    print("cube batch of 1100", flush=True)
+    R, cnt = B.bat_reliability_batched(graphs, pblocks)
+    li = B.bat_last_launch()
+    assert li.perm == 5 and 0.0 < li.kernel_ms <= li.total_ms
+    for g in list(range(0, 1100, 37)) + [1023, 1024, 1099]:
+        o = oracle.reliability(graphs[g][0], graphs[g][1], pblocks[g][1], graphs[g][2], graphs[g][3])
+        assert cnt[g] == o.count and abs(R[g, 1] - o.sum) <= REL_GRAD * o.sum, g
