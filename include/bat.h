@@ -433,7 +433,8 @@ int bat_ms_reliability_range(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *                      each in this process when first launched).  The
  *                      code objects are those of an in-process compile:
  *                      the helper uses this process's hiprtc library
- *   "BAT_CUBES"        whole sweeps by sub-cubes: cubes of state vectors that
+ *   "BAT_CUBES"        whole sweeps, batches and undirected ranges without
+ *                      gradients by sub-cubes: cubes of state vectors that
  *                      all connect, or that all do not, are decided by two
  *                      bit-sliced closures (every arc free in the cube up,
  *                      every one down) and added as one, the undecided ones

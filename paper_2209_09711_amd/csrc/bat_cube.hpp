@@ -146,6 +146,9 @@ __device__ __forceinline__ double cube_q(const CubeTables &T, u32 M, u32 cb, u32
 __device__ __forceinline__ double cube_p(CubeArgs *P, u32 a) { return P->p_dev ? P->p_dev[a] : P->p[a]; }
 __device__ __forceinline__ const __attribute__((address_space(4))) u32 *cube_steps(CubeArgs *P) { return P->step; }
 
+// The vectors of word [base, base + 32) that the launch asks for.
+__device__ __forceinline__ u32 cube_window(CubeArgs *, u32) { return ~0u; }
+
 // The block's probability tables (all threads).
 template <class Args>
 __device__ __forceinline__ void cube_tables(Args *P, CubeTables &T)
@@ -441,7 +444,7 @@ struct CubeSweep {
         if (levels == 1u) {
             u32 V = clo.close(0u, lane << kCubeGroup, live);
             if (M < 5u) V &= (1u << (1u << M)) - 1u;  // bits past the last arc
-            add(0u, q, V);
+            add(0u, q, V & cube_window(P, ((u32)block << rb) | lane << kCubeGroup));
             return;
         }
         const u32 U = classify(levels - 1u, lane << (kCubeGroup * levels), q, live, sub == 0u);

@@ -41,8 +41,7 @@ __device__ __forceinline__ const __attribute__((address_space(4))) u32 *cube_ste
     return (const __attribute__((address_space(4))) u32 *)P->step;
 }
 
-// The vectors of word [base, base + 32) that the entry asks for.
-__device__ __forceinline__ u32 batch_window(BatchArgs *P, u32 base)
+__device__ __forceinline__ u32 cube_window(BatchArgs *P, u32 base)
 {
     const u32 lo = P->win_lo, last = P->win_last;
     u32 m = ~0u;
@@ -253,7 +252,7 @@ struct BatchSweep {
         if (levels == 1u) {
             u32 V = clo.close(0u, lane << kCubeGroup, live);
             if (M < 5u) V &= (1u << (1u << M)) - 1u;  // bits past the last arc
-            words<false>(V & batch_window(P, ((u32)block << rb) | lane << kCubeGroup), lane << 5);
+            words<false>(V & cube_window(P, ((u32)block << rb) | lane << kCubeGroup), lane << 5);
         } else {
             const u32 rel = lane << (2 * kCubeGroup);
             const u32 up = clo.close(1u, rel, live);

@@ -2157,6 +2157,9 @@ void split_grad(const std::vector<double> &res, const std::vector<int> &cb_of_ar
     }
 }
 
+int range_cubes(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t s, int32_t t, const DeviceInfo &D,
+                bool forward, u64 c_lo, u64 c_hi, double *R, u64 &count, bool &fits);
+
 // Partial sums over [c_lo, c_hi) of the counter whose bits follow arc-to-bit
 // order kind `perm` (0: the paper's backward BAT indices, kPermForward: its
 // forward ones); arguments already validated except the probabilities.
@@ -2920,6 +2923,23 @@ int bat_reliability_range_ex(int32_t n, int32_t m, const bat_arc *arcs, const do
     if (m < 0 || m > BAT_MAX_ARCS) return validate(n, m, arcs, p, s, t);
     if (c_lo > c_hi || c_hi > (1ull << m)) return fail(BAT_EINVAL, "bad range [%llu, %llu) for m = %d",
                                                      (unsigned long long)c_lo, (unsigned long long)c_hi, m);
+    if (!T1_out && !(flags & BAT_DIRECTED) && c_lo < c_hi && (p || m == 0) && cubes_wanted()) {
+        int rc = validate(n, m, arcs, p, s, t);
+        DeviceInfo D;
+        if (!rc) rc = current_device(D);
+        if (rc) return rc;
+        double R[2];
+        u64 count = 0;
+        bool fits = false;
+        rc = range_cubes(n, m, arcs, p, s, t, D, (flags & BAT_FORWARD_ORDER) != 0, c_lo, c_hi, R, count, fits);
+        if (rc) return rc;
+        if (fits) {
+            *R_hi = R[0];
+            *R_lo = R[1];
+            *count_out = count;
+            return BAT_OK;
+        }
+    }
     // the indices are the paper's: backward BAT (Eq. 2-3) or forward (Eq. 4-5)
     return range_in_order(n, m, arcs, p, s, t, flags, (flags & BAT_FORWARD_ORDER) ? kPermForward : 0, c_lo, c_hi,
                           R_hi, R_lo, count_out, T1_out, T0_out);
@@ -3436,6 +3456,8 @@ int bat_autotune(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int
 
 }  // extern "C"
 
+namespace {
+
 // ------------------------------------------------ batched sub-cube sweeps
 // An entry: a graph with probability vectors [n_p][m].
 struct CubeJob {
@@ -3636,6 +3658,133 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
     return BAT_OK;
 }
 
+// ------------------------------------------------- ranges of the counter
+// A range of the paper's counter is a few aligned cubes: blocks of vectors
+// that share the leading arcs' states.  With those arcs joined (up) or left
+// out (down), a cube is a whole sweep of a smaller graph, whose arcs may take
+// the counter bits in any order.  The ends of the range, up to 2^20 vectors,
+// stay in the counter's order: a one-level sweep of the block that holds the
+// end, of which only the words inside the range count.  All of them run in
+// one batched launch (2^30 vectors of 36 arcs: 83 us against 2.85 ms with the
+// plain sweep; a hundredth of 2^36 from an odd index 0.10 against 2.5 ms;
+// 4000 of 2^20 vectors 36 against 99 us; 33 arcs whole 0.37 against 0.94 ms).
+constexpr int kRangeEnd = 20;       // log2 of an end's block
+constexpr size_t kRangeCubes = 256;  // most cubes
+
+// The cube of `bits` low counter bits under the higher bits `high`, or its
+// vectors first to last; scale: the probability of `high`.
+void range_job(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t s, int32_t t, bool forward,
+               int bits, u64 high, bool whole, u64 first, u64 last, std::vector<CubeJob> &jobs,
+               std::vector<std::vector<bat_arc>> &job_arcs, std::vector<std::vector<double>> &job_p,
+               std::vector<double> &scale)
+{
+    std::vector<int> root(n);
+    for (int x = 0; x < n; ++x) root[x] = x;
+    auto find = [&](int x) {
+        while (root[x] != x) x = root[x] = root[root[x]];
+        return x;
+    };
+    double q = 1.0;
+    for (int b = bits; b < m; ++b) {
+        const int a = forward ? b : m - 1 - b;
+        const bool up = (high >> (b - bits)) & 1u;
+        q *= up ? p[a] : 1.0 - p[a];
+        if (up) root[find(arcs[a].u)] = find(arcs[a].v);
+    }
+    std::vector<int> id(n, -1);
+    int nn = 0;
+    auto node = [&](int x) {
+        x = find(x);
+        if (id[x] < 0) id[x] = nn++;
+        return id[x];
+    };
+    CubeJob J;
+    J.s = node(s);
+    J.t = node(t);
+    std::vector<bat_arc> sub(bits);
+    std::vector<double> sp(bits);
+    for (int b = 0; b < bits; ++b) {  // job arc i at counter bit bits - 1 - i
+        const int a = forward ? b : m - 1 - b;
+        sub[bits - 1 - b] = {node(arcs[a].u), node(arcs[a].v)};
+        sp[bits - 1 - b] = p[a];
+    }
+    J.graph = (int)jobs.size();
+    J.n = nn;
+    J.m = bits;
+    J.n_p = 1;
+    J.win_lo = 0;
+    J.win_last = ~0u;
+    if (whole) {
+        if (J.s != J.t) J.rel = cube_arcs(J.n, J.m, sub.data(), J.s, J.t, false);
+        else J.rel.assign(bits, 0);  // always connected
+        J.rel.resize(bits);
+        J.M = 0;
+        for (char x : J.rel) J.M += x ? 1 : 0;
+        J.levels = J.M <= 23 ? 1 : 2;
+    } else {
+        J.rel.assign(bits, 1);
+        J.M = bits;
+        J.levels = 1;
+        J.win_lo = (u32)first;
+        J.win_last = (u32)last;
+    }
+    job_arcs.push_back(std::move(sub));
+    job_p.push_back(std::move(sp));
+    J.arcs = job_arcs.back().data();
+    J.p = job_p.back().data();
+    jobs.push_back(std::move(J));
+    scale.push_back(q);
+}
+
+int range_cubes(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t s, int32_t t, const DeviceInfo &D,
+                bool forward, u64 c_lo, u64 c_hi, double *R, u64 &count, bool &fits)
+{
+    fits = false;
+    std::vector<CubeJob> jobs;
+    std::vector<std::vector<bat_arc>> job_arcs;
+    std::vector<std::vector<double>> job_p;
+    std::vector<double> scale;
+    R[0] = R[1] = 0.0;
+    count = 0;
+    const int g = std::min<int>(m, kRangeEnd);
+    const u64 block = 1ull << g;
+    auto add = [&](int bits, u64 high, bool whole, u64 first, u64 last) {
+        range_job(n, m, arcs, p, s, t, forward, bits, high, whole, first, last, jobs, job_arcs, job_p, scale);
+    };
+    u64 a = c_lo >> g, b = c_hi >> g;
+    size_t cubes = 0;
+    if (c_lo % block != 0 || a == b) {  // the first block, not from its start or not to its end
+        const u64 end = std::min(c_hi, (a + 1) << g);
+        add(g, a, false, c_lo - (a << g), end - 1 - (a << g));
+        ++a;
+    }
+    while (a < b) {
+        int k = 0;
+        while (g + k < batk::kCubeMaxBits && g + k < m && a % (2ull << k) == 0 && b - a >= 2ull << k) ++k;
+        if (++cubes > kRangeCubes) return BAT_OK;
+        add(g + k, a >> k, true, 0, 0);
+        a += 1ull << k;
+    }
+    if (a == b && c_hi % block != 0) add(g, b, false, 0, c_hi - 1 - (b << g));
+    // the largest first
+    std::vector<size_t> order(jobs.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](size_t i, size_t j) { return jobs[i].M > jobs[j].M; });
+    std::vector<CubeJob> sorted;
+    for (size_t i : order) sorted.push_back(std::move(jobs[i]));
+    std::vector<bat::double2_t> sums;
+    std::vector<u64> counts;
+    int rc = cube_batch_all(sorted, 1, D, sums, counts, fits);
+    if (rc || !fits) return rc;
+    for (size_t i = 0; i < sorted.size(); ++i) {
+        const double q = scale[order[i]], x = q * sums[i].x;
+        dd_acc(R, x, std::fma(q, sums[i].x, -x) + q * sums[i].y);
+        count += counts[i];
+    }
+    t_state.info.vectors = c_hi - c_lo;
+    return BAT_OK;
+}
+
 // A batch in that form; fits = false where a graph is too large for it.
 int cube_batched(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_offsets, const bat_arc *arcs,
                  const int32_t *s, const int32_t *t, int32_t n_pvec, const double *p, const DeviceInfo &D, double *R_out,
@@ -3692,6 +3841,8 @@ int cube_batched(int32_t n_graphs, const int32_t *n_nodes, const int32_t *arc_of
     t_state.info.vectors = vectors;
     return BAT_OK;
 }
+
+}  // namespace
 
 // Tuned knobs of the batched launch: chained iteration bits and the
 // per-wavefront segment size, cached under the batch's structure.

@@ -297,3 +297,44 @@ def test_cube_batch_of_many_entries():
     for g in list(range(0, 1100, 37)) + [1023, 1024, 1099]:
         o = oracle.reliability(graphs[g][0], graphs[g][1], pblocks[g][1], graphs[g][2], graphs[g][3])
         assert cnt[g] == o.count and abs(R[g, 1] - o.sum) <= REL_GRAD * o.sum, g
+
+
+@pytest.mark.parametrize("forward", [False, True])
+def test_cube_ranges_vs_oracle(forward):
+    """Ranges of the paper's counters as aligned cubes and windowed ends:
+    from 0, to the end, aligned, inside one block, of one vector; graphs whose
+    leading arcs join or separate the terminals."""
+    B = _B()
+    rng = np.random.default_rng(2300 + forward)
+    nets = [W.parallel(3, [0.2, 0.5, 0.7]), W.series(6, np.full(6, 0.9)), W.bridge(0.9),
+            W.Network("apart", 4, [(0, 1), (2, 3)], 0, 3, np.full(2, 0.5)), W.random_multigraph(5, 12, seed=3)]
+    nets += [W.random_connected(n, m, seed=80 + m, p_lo=0.0, p_hi=1.0) for n, m in ((6, 11), (8, 15), (9, 17), (11, 18))]
+    for net in nets:
+        end = 1 << net.m
+        lo, hi = sorted(int(x) for x in rng.integers(0, end + 1, 2))
+        part = max(1, end >> 3)
+        for a, b in {(0, hi), (lo, end), (lo, hi), (lo // part * part, min(end, lo // part * part + part)), (lo, lo + 1)}:
+            if a == b or b > end:
+                continue
+            print("cube range", net.name, net.m, a, b, forward, flush=True)
+            r = B.bat_reliability_range(net.n, net.arcs, net.p, net.s, net.t, a, b, forward=forward)
+            assert B.bat_last_launch().perm == 5
+            o = oracle.reliability_range(net.n, net.arcs, net.p, net.s, net.t, a, b, forward=forward)
+            assert r.count == o.count and abs(r.R - o.sum) <= REL_GRAD * o.sum
+
+
+@pytest.mark.parametrize("n,m,lo,hi", [(12, 24, 12345, 7654321), (13, 25, 1 << 20, 3 << 20), (14, 27, 1 << 26, 1 << 27),
+                                       (15, 30, (1 << 30) // 100 * 17, (1 << 30) // 100 * 18), (13, 33, 0, 1 << 33)])
+def test_cube_ranges_larger(n, m, lo, hi):
+    """Several cubes of both numbers of levels, against the plain sweep of
+    the range: the same count, R within rounding."""
+    B = _B()
+    net = W.random_connected(n, m, seed=m, p_lo=0.5, p_hi=0.99)
+    for forward in (False, True):
+        print("cube range", net.name, lo, hi, forward, flush=True)
+        r = B.bat_reliability_range(net.n, net.arcs, net.p, net.s, net.t, lo, hi, forward=forward)
+        assert B.bat_last_launch().perm == 5
+        with options(BAT_CUBES=0):
+            q = B.bat_reliability_range(net.n, net.arcs, net.p, net.s, net.t, lo, hi, forward=forward)
+            assert B.bat_last_launch().perm != 5
+        assert r.count == q.count and abs(r.R - q.R) <= REL_GRAD * q.R
