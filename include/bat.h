@@ -367,10 +367,10 @@ int bat_ms_reliability_range(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *                      cover distant parts of the counter), 0 = counter
  *                      order; R and counts never depend on it beyond
  *                      floating-point rounding
- *   "BAT_MS_RUN"       consecutive state vectors each lane of the
- *                      multi-state augmenting-path sweep decides, and the
- *                      most words each lane of the bit-sliced sweep
- *                      (demand <= 2) steps through (0 = automatic)
+ *   "BAT_MS_RUN"       the most state vectors of a cube that a lane of the
+ *                      multi-state augmenting-path sweep starts from, and
+ *                      the most words each lane of the bit-sliced sweep
+ *                      (demand <= 3) steps through (0 = automatic)
  *   "BAT_MS_BITS"      1 (default) = multi-state sweeps with demand 1 to 3
  *                      run the bit-sliced kernel; 0 = always the
  *                      augmenting-path kernel

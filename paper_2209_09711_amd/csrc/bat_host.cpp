@@ -2699,27 +2699,35 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
                     (unsigned long long)c_hi, (unsigned long long)N);
     // Slots: the kernel sweeps arcs in slot order, and slot 0 is the
     // fastest-changing coordinate of its index.  A whole space may take any
-    // arc order (R and the count are sums over every vector): arcs near s
-    // first, by breadth-first distance of their nearer end, so one search
-    // sweep reaches far.  A range reads its indices in the caller's order,
+    // arc order (R and the count are sums over every vector): for the
+    // bit-sliced kernel arcs near s first, by breadth-first distance of their
+    // nearer end, so one search sweep reaches far; for the flow kernel, whose
+    // cubes leave the lowest slots free, the arcs farthest from both
+    // terminals first.  A range reads its indices in the caller's order,
     // arc 0 most significant: slot j is arc m - 1 - j.
+    const bool bits = d <= 3 && m > 0 && c_hi > c_lo && opts().ms_bits.load() != 0;
     std::vector<int> ord(m);
     for (int i = 0; i < m; ++i) ord[i] = whole ? i : m - 1 - i;
     if (whole && m > 1) {
-        std::vector<int> dist(n, 1 << 30);
-        std::vector<int> q{s};
-        dist[s] = 0;
-        for (size_t h = 0; h < q.size(); ++h)
-            for (int i = 0; i < m; ++i) {
-                const int a = arcs[i].u, b = arcs[i].v, x = q[h];
-                const int y = a == x ? b : (b == x ? a : -1);
-                if (y >= 0 && dist[y] > dist[x] + 1) {
-                    dist[y] = dist[x] + 1;
-                    q.push_back(y);
+        auto distances = [&](int from) {
+            std::vector<int> dist(n, 1 << 30);
+            std::vector<int> q{from};
+            dist[from] = 0;
+            for (size_t h = 0; h < q.size(); ++h)
+                for (int i = 0; i < m; ++i) {
+                    const int a = arcs[i].u, b = arcs[i].v, x = q[h];
+                    const int y = a == x ? b : (b == x ? a : -1);
+                    if (y >= 0 && dist[y] > dist[x] + 1) {
+                        dist[y] = dist[x] + 1;
+                        q.push_back(y);
+                    }
                 }
-            }
+            return dist;
+        };
+        const std::vector<int> dist = distances(s), back = bits ? std::vector<int>() : distances(t);
         auto key = [&](int i) {
             const int a = dist[arcs[i].u], b = dist[arcs[i].v];
+            if (!bits) return std::make_pair(-std::min({a, b, back[arcs[i].u], back[arcs[i].v]}), 0);
             return std::make_pair(std::min(a, b), std::max(a, b));
         };
         std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return key(x) < key(y); });
@@ -2761,7 +2769,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
         o += (u32)sigma[i];
     }
     // demand 1 to 3: the bit-sliced kernel
-    if (d <= 3 && m > 0 && c_hi > c_lo && opts().ms_bits.load() != 0) {
+    if (bits) {
         std::vector<int> su(m), sv(m);
         for (int j = 0; j < m; ++j) {
             su[j] = K.u[j];
@@ -2771,17 +2779,32 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
                            R_hi, R_lo, count, src_only);
     }
     if (src_only) return fail(BAT_EINVAL, "no bit-sliced kernel for this sweep (it needs demand 1 to 3 and arcs)");
-    // slot 0's capacity nondecreasing in its state: the kernel's shortcuts
-    // along slot 0 are exact
-    K.warm = m > 0 ? 1u : 0u;
-    for (int k = 1; m > 0 && k < sigma[ord[0]]; ++k)
-        if (capt[k] < capt[k - 1]) K.warm = 0u;
-    // launch shape: ~32K wavefront work items, each 64 runs of `run` indices
+    // cubes of the L lowest slots: as large as leave some 1024 work items of
+    // 64 (3^15 vectors, demand 4: 0.36 ms with 2768 items, 0.46 ms with 923,
+    // 0.50 ms with 8304; option BAT_MS_RUN > 0: of at most that many vectors)
     const u64 span = c_hi - c_lo;
-    const u64 target = 32768;
-    K.run = std::max<u64>(1, (span + 64 * target - 1) / (64 * target));
-    if (opts().ms_run.load() > 0) K.run = (u64)opts().ms_run.load();
-    K.n_items = span ? (span + 64 * K.run - 1) / (64 * K.run) : 0;
+    const u64 most_size = opts().ms_run.load() > 0 ? (u64)opts().ms_run.load()
+                                                   : std::max<u64>(1, span / (64 * 1024));
+    K.size[0] = 1;
+    K.weight[0] = 1.0;
+    for (int j = 0; j < slots; ++j) {
+        K.least[j] = K.most[j] = capt[K.off[j]];
+        double sum = 0.0;
+        for (u32 k = 0; k < K.sig[j]; ++k) {
+            K.least[j] = std::min(K.least[j], capt[K.off[j] + k]);
+            K.most[j] = std::max(K.most[j], capt[K.off[j] + k]);
+            sum += wt[K.off[j] + k];
+        }
+        if (j == (int)K.L && j < std::min<int>(m, batk::kMsTreeSlots) && K.size[j] * K.sig[j] <= most_size) {
+            K.size[j + 1] = K.size[j] * K.sig[j];
+            K.weight[j + 1] = K.weight[j] * sum;
+            K.most_states = std::max(K.most_states, K.sig[j]);
+            K.L = (u32)(j + 1);
+        }
+    }
+    K.root_lo = c_lo / K.size[K.L];
+    K.root_hi = span ? (c_hi + K.size[K.L] - 1) / K.size[K.L] : K.root_lo;
+    K.n_items = (K.root_hi - K.root_lo + 63) / 64;
     K.c_lo = c_lo;
     K.c_hi = c_hi;
     DeviceInfo D;

@@ -100,13 +100,18 @@ constexpr int kMsMaxTable = 1024;  // sum of the arcs' state counts (LDS tables)
 constexpr int kMsMaxDemand = 1024;
 constexpr int kMsMaxCapacity = 1 << 20;
 
+constexpr int kMsTreeSlots = 9;    // most free slots of a cube
+
 struct MsParams {
     bat::u64 c_lo, c_hi;   // index range of the mixed-radix counter (slot 0 least significant)
-    bat::u64 run;          // consecutive indices per lane in a work item
-    bat::u64 n_items;      // wavefront work items: item i covers [c_lo + 64 i run, c_lo + 64 (i+1) run)
+    bat::u64 root_lo, root_hi;  // the cubes of the L lowest slots that it touches
+    bat::u64 n_items;      // wavefront work items, 64 of those cubes each
+    bat::u64 size[kMsTreeSlots + 1];   // [k]: vectors of a cube of the k lowest slots
+    double weight[kMsTreeSlots + 1];   // [k]: product of those slots' probability sums
     bat::u32 m, n, s, t, d, directed;
     bat::u32 n_table;      // sum of the state counts
-    bat::u32 warm;         // 1: slot 0's capacity is nondecreasing in its state
+    bat::u32 L, most_states;   // most states of one of the L lowest slots
+    int least[kMsMaxArcs], most[kMsMaxArcs];  // of the slot's capacities
     bat::u32 sig[kMsMaxArcs];  // states of the arc in slot i (sweep position i)
     bat::u32 off[kMsMaxArcs];  // its first table entry
     unsigned char u[kMsMaxArcs], v[kMsMaxArcs];

@@ -361,3 +361,47 @@ def test_bit_sliced_range_in_a_huge_space():
             assert B.bat_last_launch().specialised == 1
             o = oracle.ms_reliability_range(n, arcs, sigma, cap, w, 0, n - 1, d, c_lo, c_hi)
             assert r.count == o.count and _ok(r.R, o.sum), (d, c_lo, c_hi, r.R, o.sum)
+
+
+def _many_states(n, m, seed, most, d):
+    """Random multigraph with up to `most` states per arc, capacities in any
+    order, weights that do not sum to 1."""
+    rng = np.random.default_rng(seed)
+    arcs = [(int(rng.integers(0, n)), int(rng.integers(0, n))) for _ in range(m)]
+    sigma = [int(rng.integers(1, most + 1)) for _ in range(m)]
+    cap = [[int(c) for c in rng.integers(0, d + 2, size=k)] for k in sigma]
+    w = [rng.uniform(0.0, 1.0, k) / k for k in sigma]
+    s, t = (int(x) for x in rng.choice(n, 2, replace=False))
+    return W.MsNetwork(f"ms_many_{seed}", n, arcs, s, t, sigma, cap, w, d)
+
+
+@pytest.mark.parametrize("run", [0, 1, 3, 10, 81, 30000])
+def test_flow_cubes(run):
+    """The augmenting-path sweep's cubes from single vectors to more slots
+    than a node holds, split on the shared stack (few states) and by each
+    lane alone (many states), over whole spaces and ragged ranges: counts
+    exact, R within some 40 roundings of the product on either side."""
+    B = _B()
+    nets = [W.ms_random(6, 9, seed=500 + k, d=1 + k % 5) for k in range(4)]
+    nets += [W.ms_random(7, 11, seed=510, d=4), W.ms_mixed(6, 9, seed=511), W.ms_bridge(3)]
+    nets += [_many_states(5, 6, 520 + k, (3, 7, 9, 12)[k % 4], 1 + k) for k in range(6)]
+    old = {k: B.bat_get_option(k) for k in ("BAT_MS_RUN", "BAT_MS_BITS")}
+    try:
+        B.bat_set_option("BAT_MS_RUN", run)
+        B.bat_set_option("BAT_MS_BITS", 0)
+        for i, net in enumerate(nets):
+            say("ms cubes", run, net.name)
+            args = (net.n, net.arcs, net.sigma, net.cap, net.w, net.s, net.t, net.d)
+            N = net.space
+            for directed in (False, True):
+                R, c = B.bat_ms_reliability(*args, directed=directed)
+                o = oracle.ms_reliability(*args, directed=directed)
+                assert c == o.count and abs(R - o.sum) <= 1e-14 * o.sum, (run, i, directed)
+                assert (R, c) == B.bat_ms_reliability(*args, directed=directed)
+            for lo, hi in [(0, N), (N // 3, N - N // 5), (N // 2, min(N, N // 2 + 1)), (7 % N, N)]:
+                r = B.bat_ms_reliability_range(*args, lo, hi)
+                o = oracle.ms_reliability_range(*args, lo, hi)
+                assert r.count == o.count and abs(r.R - o.sum) <= 1e-14 * o.sum, (run, i, lo, hi)
+    finally:
+        for k, v in old.items():
+            B.bat_set_option(k, v)
