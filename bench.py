@@ -226,7 +226,12 @@ def ms_cpu_baseline(net, sample_log2: int, procs: int):
 def roofline_alu(vectors: int, work_per_vector: float, kernel_s: float):
     """Integer-ALU roofline of a bit-sliced sweep: algorithmic bit-operations
     (the oracle's arc inspections per vector) per second against the bit-op
-    peak."""
+    peak.
+
+    The work is that of the oracle's search of every single vector.  A
+    sub-cube sweep decides whole cubes of vectors at once, so its fraction
+    can exceed 1.
+    """
     ach = vectors * work_per_vector / kernel_s
     return {"bound": "alu", "achieved": ach / 1e12, "peak": PEAK_BIT_OPS / 1e12, "unit": "Tbitop/s",
             "frac": ach / PEAK_BIT_OPS, "work_per_vector": work_per_vector,
