@@ -442,7 +442,9 @@ int bat_ms_reliability_range(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *                      (default) = where it applies, unless one of the
  *                      options above that shape the plain sweep's launch
  *                      is set; 0 = never; 1 = wherever it can run.  R
- *                      agrees to rounding, counts exactly
+ *                      agrees to rounding, counts exactly.  Also whole
+ *                      multi-state sweeps with demand 1 to 3, from 2^26
+ *                      (demand 1) or 2^23 vectors on (1 = of any size)
  *   "BAT_CUBE_LEVELS"  words of 5 arcs a sub-cube sweep's work item splits
  *                      (1..3; 0 = by size)
  *   "BAT_CUBE_SPLIT"   wavefronts that share such a work item (0 = by size)

@@ -1,10 +1,9 @@
 """Build the HIP library in-tree: ``paper_2209_09711_amd/libbat_hip.so``.
 
-Steps: embed ``csrc/bat_device.hpp`` and ``csrc/bat_cube.hpp`` as string
-literals (the source the library hands to hiprtc for graph-specialised
-kernels) with a digest of the
-ahead-of-time kernel sources, then compile the
-ahead-of-time kernels and the C ABI with hipcc for gfx950, and the compile
+Steps: embed the headers with device code (``bat_device.hpp``,
+``bat_cube.hpp``, ``bat_ms_cube.hpp``) as string literals (the source the
+library hands to hiprtc for graph-specialised kernels) with a digest of the
+ahead-of-time kernel sources, then compile the ahead-of-time kernels and the C ABI with hipcc for gfx950, and the compile
 helper ``bat_jitc`` (a host program the library runs to compile several
 graph-specialised kernels side by side) with the host compiler.
 """
@@ -31,22 +30,23 @@ def embed_device_source() -> str:
     import hashlib
     delim = "BATDEV"
     srcs = {}
-    for f in ("bat_device.hpp", "bat_cube.hpp"):
+    for f in ("bat_device.hpp", "bat_cube.hpp", "bat_ms_cube.hpp"):
         srcs[f] = open(os.path.join(CSRC, f)).read()
         assert f"){delim}\"" not in srcs[f]
     # digest of everything the ahead-of-time kernels are compiled from,
     # reported in each launch's kernel identity
     h = hashlib.sha256()
     for f in ("bat_device.hpp", "bat_cube.hpp", "bat_kernels.hip", "bat_cube.hip", "bat_cube_batch.hip",
-              "bat_launch.hpp", "bat_ms.hip"):
+              "bat_ms_cube.hpp", "bat_launch.hpp", "bat_ms.hip"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     out = os.path.join(CSRC, "bat_device_embed.inc")
-    text = ("// Generated by build.py from bat_device.hpp and bat_cube.hpp: the device\n"
-            "// templates as text, compiled at run time by hiprtc for graph-specialised\n"
-            "// kernels.\n"
+    text = ("// Generated by build.py from bat_device.hpp, bat_cube.hpp and\n"
+            "// bat_ms_cube.hpp: the device templates as text, compiled at run time by\n"
+            "// hiprtc for graph-specialised kernels.\n"
             f"static const char kDeviceSource[] = R\"{delim}(\n{srcs['bat_device.hpp']}\n){delim}\";\n"
             f"static const char kCubeSource[] = R\"{delim}(\n{srcs['bat_cube.hpp']}\n){delim}\";\n"
+            f"static const char kMsCubeSource[] = R\"{delim}(\n{srcs['bat_ms_cube.hpp']}\n){delim}\";\n"
             f"static const char kAotKernelDigest[] = \"{h.hexdigest()[:32]}\";\n")
     if not os.path.exists(out) or open(out).read() != text:
         with open(out, "w") as f:

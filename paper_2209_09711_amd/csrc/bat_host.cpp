@@ -1242,6 +1242,17 @@ void jit_precompile_sources(const DeviceInfo &D, const std::vector<std::string> 
     rmdir(dir.c_str());
 }
 
+// A kernel loaded before, without the text of its source.
+bool jit_ready(const std::string &key, hipFunction_t &fn, uint64_t &id)
+{
+    std::lock_guard<std::mutex> lk(g_jit_mu);
+    auto it = g_jit.find(key);
+    if (it == g_jit.end()) return false;
+    fn = it->second.fn;
+    id = it->second.id;
+    return true;
+}
+
 // The kernel `kname` of source `src`, loaded once per process under `key`:
 // from the precompiled table, else the disk cache, else compiled here.
 int jit_load(const DeviceInfo &D, const std::string &key, const std::string &src, const char *kname,
@@ -1916,15 +1927,7 @@ int cube_jit_get(const batcube::CubePlan &C, const DeviceInfo &D, bool grad, hip
         }
         key += ";";
     }
-    {
-        std::lock_guard<std::mutex> lk(g_jit_mu);
-        auto it = g_jit.find(key);
-        if (it != g_jit.end()) {
-            fn = it->second.fn;
-            id = it->second.id;
-            return BAT_OK;
-        }
-    }
+    if (jit_ready(key, fn, id)) return BAT_OK;
     return jit_load(D, key, cube_source(C, grad), grad ? "bat_cube_grad_jit" : "bat_cube_jit", fn, jit_ms, id);
 }
 
@@ -2593,8 +2596,11 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     hipFunction_t fn;
     double jit_ms = 0.0;
     uint64_t kid = 0;
-    rc = jit_load(D, std::to_string(D.id) + " ms" + g, std::string(kDeviceSource) + g, "bat_ms_bits", fn, jit_ms, kid);
-    if (rc) return rc;
+    const std::string key = std::to_string(D.id) + " ms" + g;
+    if (!jit_ready(key, fn, kid)) {
+        rc = jit_load(D, key, std::string(kDeviceSource) + g, "bat_ms_bits", fn, jit_ms, kid);
+        if (rc) return rc;
+    }
     hipStream_t st;
     rc = thread_stream(D.id, st);
     if (rc) return rc;
@@ -2682,6 +2688,205 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     return BAT_OK;
 }
 
+// Fewest prefixes worth their own wavefronts: 3^16 vectors at demand 3 took 66
+// us with 59049 prefixes and words of 27 cubes, 97 us with 531441 and words of
+// 3; 3^15 98 us with 177147, 114 us with 19683, a wavefront per CU.
+constexpr u64 kMsCubePrefixes = 32768;
+// Vectors from which the cubes win.  Whole calls, cubes against every word by
+// itself: 3^14 90 and 66 us at demand 1, 90 and 75 us at 2, 91 and 81 us at 3;
+// 3^15 90 and 79, 93 and 111, 181 and 174 us; 3^17 89 and 114, 97 and 295,
+// 455 and 1101 us.
+constexpr u64 ms_cube_vectors(int d) { return 1ull << (d == 1 ? 26 : 23); }
+
+// A whole space with demand <= 3 by cubes (bat_ms_cube.hpp); slots as above,
+// ordered by distance from the nearer terminal.
+int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u32 *sig, const bat::u32 *off,
+                 const std::vector<int32_t> &capt, const std::vector<double> &wt, int32_t s, int32_t t, int32_t d,
+                 bool directed, u64 N, double &R_hi, double &R_lo, u64 &count, std::string *src_only)
+{
+    // the two words: as many slots as fit 32 vectors each
+    int kw = 0, kw1 = 0;
+    u64 B0 = 1, B1 = 1;
+    while (kw < m && B0 * sig[kw] <= 32) B0 *= sig[kw++];
+    const u64 fewest = opts().cubes.load() == 1 ? 1 : kMsCubePrefixes;
+    while (kw + kw1 < m && B1 * sig[kw + kw1] <= 32 && N / (B0 * B1 * sig[kw + kw1]) >= fewest)
+        B1 *= sig[kw + kw1++];
+    const u64 n_prefix = N / (B0 * B1), n_items = (n_prefix + bat::kWave - 1) / bat::kWave;
+    const u64 blocks = (n_items + bat::kMsCubeWaves - 1) / bat::kMsCubeWaves;
+    if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)n_items);
+    auto kinds = [](int32_t c) { return (c >= 1 ? 1u : 0u) | (c == 1 ? 2u : 0u) | (c == 1 || c == 2 ? 4u : 0u); };
+    std::vector<u32> c[3], word[3], lo(m, 0u), hi(m, 0u), m1(96, 0u);
+    for (int k = 0; k < 3; ++k) {
+        c[k].assign(m, 0u);
+        word[k].assign(m, 0u);
+    }
+    double sum0 = 1.0;
+    std::vector<double> q[2] = {std::vector<double>(32, 0.0), std::vector<double>(32, 0.0)}, tb(2048, 0.0);
+    for (u64 b = 0; b < B0; ++b) q[0][b] = 1.0;
+    for (u64 b = 0; b < B1; ++b) q[1][b] = 1.0;
+    u64 stride = 1;
+    u32 upair = 0u;
+    for (int j = 0; j < m; ++j) {
+        int32_t least = capt[off[j]], most = least;
+        double sum = 0.0;
+        for (u32 x = 0; x < sig[j]; ++x) {
+            const int32_t cap = capt[off[j] + x];
+            least = std::min(least, cap);
+            most = std::max(most, cap);
+            sum += wt[off[j] + x];
+            for (int k = 0; k < 3; ++k) c[k][j] |= ((kinds(cap) >> k) & 1u) << x;
+        }
+        if (c[1][j]) upair |= 1u << j;
+        if (j < kw) {
+            lo[j] = kinds(least);
+            hi[j] = kinds(most);
+            sum0 *= sum;
+        }
+        if (j == kw) stride = 1;
+        if (j < kw + kw1) {
+            const int level = j < kw ? 0 : 1;
+            for (u64 b = 0; b < (level ? B1 : B0); ++b) {
+                const u32 x = (u32)((b / stride) % sig[j]);
+                q[level][b] *= wt[off[j] + x];
+                for (int k = 0; k < 3; ++k) {
+                    word[k][j] |= ((c[k][j] >> x) & 1u) << b;
+                    if (level) m1[32 * k + b] |= ((c[k][j] >> x) & 1u) << j;
+                }
+            }
+            stride *= sig[j];
+        }
+    }
+    for (int level = 0; level < 2; ++level)
+        for (int h = 0; h < 4; ++h)
+            for (int x = 0; x < 256; ++x) {
+                double a = 0.0;
+                for (int i = 0; i < 8; ++i)
+                    if ((x >> i) & 1) a += q[level][8 * h + i];
+                tb[1024 * level + 256 * h + x] = level ? a * sum0 : a;
+            }
+    // the closure, on slots
+    std::vector<bat_arc> sa(m);
+    std::vector<int> bit(m);
+    for (int j = 0; j < m; ++j) {
+        sa[j].u = su[j];
+        sa[j].v = sv[j];
+        bit[j] = j;
+    }
+    const batcube::Program pr = batcube::make_program(n, sa.data(), bit, s, t, 0, false, directed);
+    std::string g = "\nstruct JitMs {\n";
+    auto num = [&](const char *k, u64 v) { g += std::string("  static constexpr unsigned ") + k + " = " + std::to_string(v) + "u;\n"; };
+    num("M", (u64)m);
+    num("D", (u64)d);
+    num("KW", (u64)kw);
+    num("KW1", (u64)kw1);
+    num("B0", B0);
+    num("FULL0", B0 == 32 ? 0xffffffffull : (1ull << B0) - 1ull);
+    num("B1", B1);
+    num("FULL1", B1 == 32 ? 0xffffffffull : (1ull << B1) - 1ull);
+    num("UPAIR", upair);
+    num("SLOTS", (u64)std::max(pr.slots, m));
+    num("RESULT", pr.result < 0 ? 255ull : (u64)pr.result);
+    auto arr = [&](const char *k, auto get) {
+        g += std::string("  static constexpr unsigned ") + k + "[" + std::to_string(m) + "] = {";
+        for (int j = 0; j < m; ++j) g += (j ? "," : "") + std::to_string((u64)get(j)) + "u";
+        g += "};\n";
+    };
+    arr("SIG", [&](int j) { return sig[j]; });
+    arr("OFF", [&](int j) { return off[j]; });
+    arr("C1", [&](int j) { return c[0][j]; });
+    arr("CE1", [&](int j) { return c[1][j]; });
+    arr("CE12", [&](int j) { return c[2][j]; });
+    arr("P1", [&](int j) { return word[0][j]; });
+    arr("PE1", [&](int j) { return word[1][j]; });
+    arr("PE12", [&](int j) { return word[2][j]; });
+    arr("LO", [&](int j) { return lo[j]; });
+    arr("HI", [&](int j) { return hi[j]; });
+    g += "  __device__ static __forceinline__ void steps(unsigned (&r)[SLOTS]) {\n";
+    for (const batcube::Step &x : pr.step) {
+        const std::string a = "r[" + std::to_string(x.a) + "]", b = "r[" + std::to_string(x.b) + "]",
+                          dd = "r[" + std::to_string(x.d) + "]";
+        g += "    " + dd + (x.assign ? " = " + a + " & " + b : " = bat::and_or(" + a + ", " + b + ", " + dd + ")") + ";\n";
+    }
+    g += "  }\n};\n"
+         "extern \"C\" __global__ void __launch_bounds__(256) bat_ms_cubes(bat::MsCubeParams P) {\n"
+         "  __shared__ bat::MsCubeLds L;\n"
+         "  bat::ms_cube_kernel<JitMs>(P, L);\n}\n";
+    auto source = [&]() { return std::string(kDeviceSource) + kCubeSource + kMsCubeSource + g; };
+    if (src_only) {
+        *src_only = source();
+        return BAT_OK;
+    }
+    DeviceInfo D;
+    int rc = current_device(D);
+    if (rc) return rc;
+    hipFunction_t fn;
+    double jit_ms = 0.0;
+    uint64_t kid = 0;
+    const std::string key = std::to_string(D.id) + " mscube" + g;
+    if (!jit_ready(key, fn, kid)) {  // (the source is some 200 KiB)
+        rc = jit_load(D, key, source(), "bat_ms_cubes", fn, jit_ms, kid);
+        if (rc) return rc;
+    }
+    hipStream_t st;
+    rc = thread_stream(D.id, st);
+    if (rc) return rc;
+    // workspace: input (tb | q1 | m1 | w) | partials | counts | output (res | count)
+    const size_t o_q1 = sizeof(double) * tb.size(), o_m1 = o_q1 + sizeof(double) * 32, o_w = o_m1 + sizeof(u32) * 96;
+    const size_t in_bytes = align_up(o_w + sizeof(double) * (wt.size() + 1), 256);
+    const size_t o_part = in_bytes, o_pc = align_up(o_part + sizeof(double) * 2 * n_items, 256);
+    const size_t o_res = align_up(o_pc + sizeof(u64) * n_items, 256), o_cnt = o_res + 2 * sizeof(double);
+    const size_t out_bytes = o_cnt + sizeof(u64) - o_res;
+    Scratch *S = nullptr;
+    rc = scratch_reserve(D.id, st, align_up(o_cnt + sizeof(u64) + 64, 256), in_bytes + out_bytes, S);
+    if (rc) return rc;
+    memcpy(S->host, tb.data(), sizeof(double) * tb.size());
+    memcpy(S->host + o_q1, q[1].data(), sizeof(double) * 32);
+    memcpy(S->host + o_m1, m1.data(), sizeof(u32) * 96);
+    memcpy(S->host + o_w, wt.data(), sizeof(double) * wt.size());
+    rc = events_ready();
+    if (rc) return rc;
+    char *ws = S->dev;
+    HIPCHK(hipMemcpyAsync(ws, S->host, in_bytes, hipMemcpyHostToDevice, st));
+    bat::MsCubeParams K;
+    memset(&K, 0, sizeof K);
+    K.n_prefix = n_prefix;
+    K.n_items = n_items;
+    K.tb = (const double *)ws;
+    K.q1 = (const double *)(ws + o_q1);
+    K.m1 = (const u32 *)(ws + o_m1);
+    K.w = (const double *)(ws + o_w);
+    K.part = (double *)(ws + o_part);
+    K.pcount = (u64 *)(ws + o_pc);
+    HIPCHK(hipEventRecord(t_state.ev[0], st));
+    HIPCHK(hipEventRecord(t_state.ev[1], st));
+    void *args[] = {&K};
+    HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kMsCubeWaves), 1, 1, 0, st, args,
+                                 nullptr));
+    HIPCHK(hipEventRecord(t_state.ev[2], st));
+    HIPCHK(batk::reduce(st, K.part, K.pcount, n_items, 1, (double *)(ws + o_res), (u64 *)(ws + o_cnt)));
+    HIPCHK(hipEventRecord(t_state.ev[3], st));
+    char *out = S->host + in_bytes;
+    HIPCHK(hipMemcpyAsync(out, ws + o_res, out_bytes, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    bat_launch_info &I = t_state.info;
+    memset(&I, 0, sizeof I);
+    t_state.cube_seq = 0;
+    I.vectors = N;
+    I.n_chunks = (int32_t)std::min<u64>(n_items, 0x7fffffff);
+    I.chunk_log2 = -1;
+    I.relaxations = m;
+    I.specialised = 1;
+    I.jit_ms = jit_ms;
+    I.kernel_id = kid;
+    I.perm = kPermInfluence;
+    I.block_waves = bat::kMsCubeWaves;
+    t_state.have_launch = true;
+    memcpy(&R_hi, out, sizeof(double));
+    memcpy(&R_lo, out + sizeof(double), sizeof(double));
+    memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
+    return BAT_OK;
+}
+
 int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, const int32_t *cap, const double *w,
            int32_t s, int32_t t, int32_t d, uint32_t flags, bool whole, u64 c_lo, u64 c_hi, double &R_hi,
            double &R_lo, u64 &count, std::string *src_only = nullptr)
@@ -2706,6 +2911,9 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     // terminals first.  A range reads its indices in the caller's order,
     // arc 0 most significant: slot j is arc m - 1 - j.
     const bool bits = d <= 3 && m > 0 && c_hi > c_lo && opts().ms_bits.load() != 0;
+    const int64_t want_cubes = opts().cubes.load();
+    const bool cubes = bits && whole && opts().ms_run.load() <= 0 &&
+                       (want_cubes == 1 || (want_cubes != 0 && N >= ms_cube_vectors(d)));
     std::vector<int> ord(m);
     for (int i = 0; i < m; ++i) ord[i] = whole ? i : m - 1 - i;
     if (whole && m > 1) {
@@ -2724,10 +2932,10 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
                 }
             return dist;
         };
-        const std::vector<int> dist = distances(s), back = bits ? std::vector<int>() : distances(t);
+        const std::vector<int> dist = distances(s), back = bits && !cubes ? std::vector<int>() : distances(t);
         auto key = [&](int i) {
             const int a = dist[arcs[i].u], b = dist[arcs[i].v];
-            if (!bits) return std::make_pair(-std::min({a, b, back[arcs[i].u], back[arcs[i].v]}), 0);
+            if (!bits || cubes) return std::make_pair(-std::min({a, b, back[arcs[i].u], back[arcs[i].v]}), 0);
             return std::make_pair(std::min(a, b), std::max(a, b));
         };
         std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return key(x) < key(y); });
@@ -2775,6 +2983,9 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
             su[j] = K.u[j];
             sv[j] = K.v[j];
         }
+        if (cubes)
+            return ms_cubes_run(n, m, su.data(), sv.data(), K.sig, K.off, capt, wt, s, t, d, K.directed != 0, N, R_hi,
+                                R_lo, count, src_only);
         return ms_bits_run(n, m, su.data(), sv.data(), K.sig, K.off, capt, wt, s, t, d, K.directed != 0, c_lo, c_hi,
                            R_hi, R_lo, count, src_only);
     }

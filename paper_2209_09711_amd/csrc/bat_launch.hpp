@@ -5,6 +5,7 @@
 
 #include "bat_device.hpp"
 #include "bat_cube.hpp"
+#include "bat_ms_cube.hpp"
 
 namespace bat {
 

@@ -49,9 +49,8 @@
 // wavefront at half its lanes on 3^15 vectors and demand 4: 0.36 ms against
 // 1.27 ms with a run of vectors per lane, each tested by itself.  (An item of
 // 64 neighbouring cubes 0.63 ms; one sweep, one way, per step 1.15 ms; slots
-// ordered outward from s leave twice as many cubes undecided.  Where demands
-// of 1 to 3 have many vectors the bit-sliced kernel is still faster: 3^18,
-// demand 2, 0.83 against 2.4 ms.)
+// ordered outward from s leave twice as many cubes undecided.  Demands of 1
+// to 3 run bit-sliced: 3^18 vectors, demand 2, 0.11 against 2.4 ms.)
 #include <hip/hip_runtime.h>
 
 #include "bat_launch.hpp"

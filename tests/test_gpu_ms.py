@@ -405,3 +405,47 @@ def test_flow_cubes(run):
     finally:
         for k, v in old.items():
             B.bat_set_option(k, v)
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+def test_bit_sliced_cubes(d):
+    """The bit-sliced sweep by cubes at small spaces: one slot to several
+    words and prefixes, one-state slots, capacities in any order, weights
+    that do not sum to 1, terminals apart; counts exact, R within some 40
+    roundings of the product on either side."""
+    B = _B()
+    nets = [W.ms_random(n, m, seed=600 + m, d=d) for n, m in ((2, 1), (4, 5), (6, 9), (7, 11), (8, 12))]
+    nets += [_many_states(5, 6 + k, 620 + k, (2, 3, 4, 6)[k % 4], d) for k in range(6)]
+    nets.append(W.MsNetwork("apart", 4, [(0, 1), (2, 3)], 0, 3, [3, 3], [[0, 1, 2]] * 2, [[.2, .3, .5]] * 2, d))
+    old = B.bat_get_option("BAT_CUBES")
+    try:
+        B.bat_set_option("BAT_CUBES", 1)
+        for net in nets:
+            for directed in (False, True):
+                say("ms bit cubes", d, net.name, directed)
+                R, c, o = _both(net, directed)
+                li = B.bat_last_launch()
+                assert li.perm == 5 and li.specialised == 1
+                assert c == o.count and abs(R - o.sum) <= 1e-14 * o.sum, (net.name, directed, R, o.sum)
+    finally:
+        B.bat_set_option("BAT_CUBES", old)
+
+
+@pytest.mark.parametrize("n,m,d", [(9, 17, 1), (9, 15, 2), (10, 16, 2), (9, 15, 3)])
+def test_bit_sliced_cubes_larger(n, m, d):
+    """The sizes at which the default takes the cubes, against the sweep that
+    tests every word."""
+    B = _B()
+    net = W.ms_random(n, m, seed=700 + m, d=d)
+    args = (net.n, net.arcs, net.sigma, net.cap, net.w, net.s, net.t, net.d)
+    say("ms bit cubes", net.name)
+    R, c = B.bat_ms_reliability(*args)
+    assert B.bat_last_launch().perm == 5
+    old = B.bat_get_option("BAT_CUBES")
+    try:
+        B.bat_set_option("BAT_CUBES", 0)
+        R0, c0 = B.bat_ms_reliability(*args)
+        assert B.bat_last_launch().perm != 5
+    finally:
+        B.bat_set_option("BAT_CUBES", old)
+    assert c == c0 and abs(R - R0) <= 1e-14 * R0
