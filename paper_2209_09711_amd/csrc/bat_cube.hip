@@ -51,6 +51,7 @@ __global__ void __launch_bounds__(kFinishThreads) k_cube_finish(bat::CubeParams,
     if (tid == 0) bat::cube_clock(P, 1);
     double h = 0.0, l = 0.0;
     u64 c = 0;
+#pragma unroll 4
     for (u32 k = tid; k < n; k += kFinishThreads) {
         const bat::double2_t x = P->part[k];
         bat::dd_add(h, l, x.x, x.y);

@@ -1419,6 +1419,7 @@ struct MsBitsParams {
     const double *w;   // probability of (slot, state), at OFF[slot] + state
     double *part;      // [n_items][2] double-double partials
     u64 *pcount;       // [n_items]
+    u64 *diag;         // [0]: the device clock at the start
 };
 
 // Reach from s, in the vectors of `src`, over the slots' masks W (slot E
@@ -1518,6 +1519,7 @@ template <class G>
 __device__ void ms_bits_kernel(const MsBitsParams &P, double (&tb)[4][256])
 {
     const u32 tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid == 0) P.diag[0] = wall_clock64();
     for (u32 i = tid; i < 1024u; i += blockDim.x) tb[i >> 8][i & 255u] = P.tb[i];
     __syncthreads();
     const u32 lane = tid & (kWave - 1);

@@ -2500,6 +2500,38 @@ int ms_validate(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma,
     return BAT_OK;
 }
 
+// The sums of a multi-state sweep's work items, written by the device to the
+// pinned `out` and waited for by its report, as a sub-cube sweep's (four
+// events, a copy back and the stream's own wait took half of a small call:
+// 3^9 vectors 62 us with them).  Clears the launch info.
+int ms_finish(hipStream_t st, const DeviceInfo &D, double *part, u64 *pcount, u64 n_items, u64 *slot, u64 seq, char *out,
+              double &R_hi, double &R_lo, u64 &count)
+{
+    bat::CubeParams K;
+    memset(&K, 0, sizeof K);
+    K.part = (bat::double2_t *)part;
+    K.pcount = pcount;
+    K.res = (double *)out;
+    K.count = (u64 *)(out + 2 * sizeof(double));
+    K.diag = slot;
+    K.seq = seq;
+    HIPCHK(batk::cube_finish(st, (unsigned)n_items, K));
+    const int rc = cube_wait(K, st);
+    if (rc) {
+        (void)hipStreamSynchronize(st);
+        return rc;
+    }
+    memcpy(&R_hi, out, sizeof(double));
+    memcpy(&R_lo, out + sizeof(double), sizeof(double));
+    memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
+    memset(&t_state.info, 0, sizeof t_state.info);
+    t_state.cube_seq = seq;
+    t_state.cube_dev = D.id;
+    t_state.cube_khz = D.clock_khz;
+    t_state.have_launch = true;
+    return BAT_OK;
+}
+
 // Demand <= 3: the bit-sliced kernel (ms_bits_kernel in bat_device.hpp)
 // compiled for the graph and its states, over the vector indices
 // [c_lo, c_hi) (slot 0 least significant).  Slots in sweep order: slot j
@@ -2654,25 +2686,15 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     K.w = (const double *)(ws + o_w);
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
-    double *res = (double *)(ws + o_res);
-    u64 *cnt = (u64 *)(ws + o_cnt);
-    rc = events_ready();
+    u64 seq = 0;
+    rc = diag_next(st, K.diag, seq);
     if (rc) return rc;
-    HIPCHK(hipEventRecord(t_state.ev[0], st));
-    HIPCHK(hipEventRecord(t_state.ev[1], st));
     void *args[] = {&K};
-    if (blocks)
-        HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kWavesPerBlock), 1, 1, 0,
-                                     st, args, nullptr));
-    HIPCHK(hipEventRecord(t_state.ev[2], st));
-    HIPCHK(batk::reduce(st, (const double *)K.part, (const u64 *)K.pcount, n_items, 1, res, cnt));
-    HIPCHK(hipEventRecord(t_state.ev[3], st));
-    char *out = S->host + out_host_off;
-    HIPCHK(hipMemcpyAsync(out, ws + o_res, out_bytes, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    HIPCHK(hipModuleLaunchKernel(fn, (unsigned)std::max<u64>(blocks, 1), 1, 1,
+                                 (unsigned)(bat::kWave * bat::kWavesPerBlock), 1, 1, 0, st, args, nullptr));
+    rc = ms_finish(st, D, K.part, K.pcount, n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
+    if (rc) return rc;
     bat_launch_info &I = t_state.info;
-    memset(&I, 0, sizeof I);
-    t_state.cube_seq = 0;
     I.vectors = c_hi - c_lo;
     I.n_chunks = (int32_t)std::min<u64>(n_items, 0x7fffffff);
     I.chunk_log2 = -1;
@@ -2681,10 +2703,6 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     I.jit_ms = jit_ms;
     I.kernel_id = kid;
     I.block_waves = bat::kWavesPerBlock;
-    t_state.have_launch = true;
-    memcpy(&R_hi, out, sizeof(double));
-    memcpy(&R_lo, out + sizeof(double), sizeof(double));
-    memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
     return BAT_OK;
 }
 
@@ -2843,8 +2861,6 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     memcpy(S->host + o_q1, q[1].data(), sizeof(double) * 32);
     memcpy(S->host + o_m1, m1.data(), sizeof(u32) * 96);
     memcpy(S->host + o_w, wt.data(), sizeof(double) * wt.size());
-    rc = events_ready();
-    if (rc) return rc;
     char *ws = S->dev;
     HIPCHK(hipMemcpyAsync(ws, S->host, in_bytes, hipMemcpyHostToDevice, st));
     bat::MsCubeParams K;
@@ -2857,20 +2873,15 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     K.w = (const double *)(ws + o_w);
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
-    HIPCHK(hipEventRecord(t_state.ev[0], st));
-    HIPCHK(hipEventRecord(t_state.ev[1], st));
+    u64 seq = 0;
+    rc = diag_next(st, K.diag, seq);
+    if (rc) return rc;
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kMsCubeWaves), 1, 1, 0, st, args,
                                  nullptr));
-    HIPCHK(hipEventRecord(t_state.ev[2], st));
-    HIPCHK(batk::reduce(st, K.part, K.pcount, n_items, 1, (double *)(ws + o_res), (u64 *)(ws + o_cnt)));
-    HIPCHK(hipEventRecord(t_state.ev[3], st));
-    char *out = S->host + in_bytes;
-    HIPCHK(hipMemcpyAsync(out, ws + o_res, out_bytes, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    rc = ms_finish(st, D, K.part, K.pcount, n_items, K.diag, seq, S->host + in_bytes, R_hi, R_lo, count);
+    if (rc) return rc;
     bat_launch_info &I = t_state.info;
-    memset(&I, 0, sizeof I);
-    t_state.cube_seq = 0;
     I.vectors = N;
     I.n_chunks = (int32_t)std::min<u64>(n_items, 0x7fffffff);
     I.chunk_log2 = -1;
@@ -2880,10 +2891,6 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     I.kernel_id = kid;
     I.perm = kPermInfluence;
     I.block_waves = bat::kMsCubeWaves;
-    t_state.have_launch = true;
-    memcpy(&R_hi, out, sizeof(double));
-    memcpy(&R_lo, out + sizeof(double), sizeof(double));
-    memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
     return BAT_OK;
 }
 
@@ -3048,34 +3055,21 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     K.w = (const double *)(ws + o_w);
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
-    double *res = (double *)(ws + o_res);
-    u64 *cnt = (u64 *)(ws + o_cnt);
-    rc = events_ready();
-    if (rc) return rc;
     const u64 blocks = (K.n_items + bat::kWavesPerBlock - 1) / bat::kWavesPerBlock;
     if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)blocks);
-    HIPCHK(hipEventRecord(t_state.ev[0], st));
-    HIPCHK(hipEventRecord(t_state.ev[1], st));
-    if (blocks) HIPCHK(batk::ms_sweep(st, (unsigned)blocks, K));
-    HIPCHK(hipEventRecord(t_state.ev[2], st));
-    HIPCHK(batk::reduce(st, (const double *)K.part, (const u64 *)K.pcount, K.n_items, 1, res, cnt));
-    HIPCHK(hipEventRecord(t_state.ev[3], st));
-    char *out = S->host + out_host_off;
-    HIPCHK(hipMemcpyAsync(out, ws + o_res, out_bytes, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    u64 seq = 0;
+    rc = diag_next(st, K.diag, seq);
+    if (rc) return rc;
+    HIPCHK(batk::ms_sweep(st, (unsigned)std::max<u64>(blocks, 1), K));
+    rc = ms_finish(st, D, K.part, K.pcount, K.n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
+    if (rc) return rc;
     bat_launch_info &I = t_state.info;
-    memset(&I, 0, sizeof I);
-    t_state.cube_seq = 0;
     I.vectors = span;
     I.n_chunks = (int32_t)std::min<u64>(K.n_items, 0x7fffffff);
     I.chunk_log2 = -1;
     I.relaxations = m;
     I.kernel_id = aot_kernel_id("k_ms_flow", batk::ms_slots(m), K.directed != 0);
     I.block_waves = bat::kWavesPerBlock;
-    t_state.have_launch = true;
-    memcpy(&R_hi, out, sizeof(double));
-    memcpy(&R_lo, out + sizeof(double), sizeof(double));
-    memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
     return BAT_OK;
 }
 

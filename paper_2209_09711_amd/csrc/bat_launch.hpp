@@ -120,6 +120,7 @@ struct MsParams {
     const double *w;       // [n_table] probability of (arc, state)
     double *part;          // [n_items][2] double-double partials
     bat::u64 *pcount;      // [n_items]
+    bat::u64 *diag;        // [0]: the device clock at the start
 };
 hipError_t ms_sweep(hipStream_t st, unsigned blocks, const MsParams &P);
 

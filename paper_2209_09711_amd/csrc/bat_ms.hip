@@ -81,6 +81,7 @@ k_ms_flow(batk::MsParams P)
     __shared__ u64 size[batk::kMsTreeSlots + 1];       // vectors of a cube
     __shared__ double weight[batk::kMsTreeSlots + 1];  // and its free slots' probability
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == 0 && tid == 0) P.diag[0] = wall_clock64();
     for (u32 i = tid; i < P.n_table; i += blockDim.x) {
         capt[i] = P.cap[i];
         wt[i] = P.w[i];

@@ -43,6 +43,7 @@ struct MsCubeParams {
     const double *w;        // probability of (slot, state)
     double *part;           // [n_items][2]
     u64 *pcount;            // [n_items]
+    u64 *diag;              // [0]: the device clock at the start
 };
 
 struct MsCubeWave {
@@ -122,6 +123,7 @@ template <class G>
 __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
 {
     const u32 tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == 0 && tid == 0) P.diag[0] = wall_clock64();
     for (u32 i = tid; i < 2048u; i += blockDim.x) L.tb[i >> 10][(i >> 8) & 3u][i & 255u] = P.tb[i];
     if (tid < 32u) L.q1[tid] = P.q1[tid];
     if (tid < 96u) L.m1[tid >> 5][tid & 31u] = P.m1[tid];
