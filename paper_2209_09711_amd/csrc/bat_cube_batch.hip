@@ -392,7 +392,7 @@ constexpr int kBatchFinish = 256;
 __global__ void __launch_bounds__(kBatchFinish) k_cube_batch_finish(BatchCubes L, u32 pw)
 {
     __shared__ bat::double2_t sh[kBatchFinish];
-    __shared__ u64 sc[kBatchFinish];
+    __shared__ u64 sc[kBatchFinish / kWave];
     const u32 tid = threadIdx.x, e = blockIdx.x, p = tid % pw, row = tid / pw, rows = kBatchFinish / pw;
     if (e == 0 && tid == 0) L.diag[1] = wall_clock64();
     const BatchCube &E = *(const BatchCube *)(L.entries + (u64)e * L.stride);
@@ -403,17 +403,22 @@ __global__ void __launch_bounds__(kBatchFinish) k_cube_batch_finish(BatchCubes L
         bat::dd_add(h, l, x.x, x.y);
     }
     for (u32 b = tid; b < E.n_blocks; b += kBatchFinish) n += L.pcount[E.first_block + b];
+    // a tree over the rows (one thread after them all took 8 us here)
     sh[tid] = {h, l};
-    sc[tid] = n;
-    __syncthreads();
-    if (tid < pw) {
-        h = l = 0.0;
-        for (u32 r = 0; r < rows; ++r) bat::dd_add(h, l, sh[r * pw + tid].x, sh[r * pw + tid].y);
-        L.sums[(u64)e * pw + tid] = {h, l};
+    n = bat::wave_sum_u64(n);
+    if ((tid & (kWave - 1)) == 0) sc[tid / kWave] = n;
+    for (u32 r = rows / 2; r; r >>= 1) {
+        __syncthreads();
+        if (row < r) {
+            bat::dd_add(h, l, sh[tid + r * pw].x, sh[tid + r * pw].y);
+            sh[tid] = {h, l};
+        }
     }
+    if (tid < pw) L.sums[(u64)e * pw + tid] = {h, l};
+    __syncthreads();
     if (tid == 0) {
         n = 0;
-        for (u32 k = 0; k < (u32)kBatchFinish; ++k) n += sc[k];
+        for (int w = 0; w < kBatchFinish / kWave; ++w) n += sc[w];
         L.counts[e] = n << (E.m - E.M);
     }
     __threadfence_system();

@@ -3893,7 +3893,7 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
 // the counter bits in any order.  The ends of the range, up to 2^20 vectors,
 // stay in the counter's order: a one-level sweep of the block that holds the
 // end, of which only the words inside the range count.  All of them run in
-// one batched launch (2^30 vectors of 36 arcs: 83 us against 2.85 ms with the
+// one batched launch (2^30 vectors of 36 arcs: 74 us against 2.85 ms with the
 // plain sweep; a hundredth of 2^36 from an odd index 0.10 against 2.5 ms;
 // 4000 of 2^20 vectors 36 against 99 us; 33 arcs whole 0.37 against 0.94 ms).
 constexpr int kRangeEnd = 20;       // log2 of an end's block
