@@ -178,7 +178,8 @@ struct BatchSweep {
             const double a0 = T.a4[2 * half][p], a1 = T.a4[2 * half + 1][p];
             for (u64 nz = __ballot(V != 0u); nz != 0ull;) {
                 // kBatchWords at a time (the last ones perhaps none), so that
-                // their LDS reads overlap: 1.9 ms one by one, 1.6 ms so
+                // their LDS reads overlap: 1.9 ms one by one, 1.5 ms by 4,
+                // 1.57 ms by 8, which spill
                 u32 v[kBatchWords], y[kBatchWords];
                 int i = 0;
 #pragma unroll
