@@ -587,7 +587,8 @@ struct SideStreams {
 
 // Where a thread's sub-cube sweeps report to (pinned host memory, never
 // freed): the device clocks and sequence number of its last kDiagSlots
-// launches, [start, swept, done, seq] each.
+// asynchronous launches, then of its last synchronous one, [start, swept,
+// done, seq] each.
 constexpr u64 kDiagSlots = 16;
 struct Diag {
     u64 *slots = nullptr;
@@ -616,6 +617,7 @@ struct ThreadState {
     Diag diag;
     bool have_launch = false;
     u64 cube_seq = 0;  // the last launch was this sub-cube sweep (0: another kernel)
+    u64 *cube_slot = nullptr;  // which reports here
     int cube_dev = 0, cube_khz = 0;
     bat_launch_info info{};
     ~ThreadState()
@@ -738,9 +740,10 @@ int events_ready()
     return BAT_OK;
 }
 
-// The next launch's report slot (null: `stream` is being captured and the
+// The next launch's report slot; synchronous calls, which wait on theirs,
+// have one that no launch still running or replayed can write to (null: `stream` is being captured and the
 // thread has no slots yet, which cannot be allocated then).
-int diag_next(hipStream_t stream, u64 *&slot, u64 &seq)
+int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, bool sync)
 {
     Diag &G = t_state.diag;
     if (!G.slots) {
@@ -757,12 +760,12 @@ int diag_next(hipStream_t stream, u64 *&slot, u64 &seq)
         slot = nullptr;
         if (cs != hipStreamCaptureStatusNone) return BAT_OK;
         void *h = nullptr;
-        HIPCHK(hipHostMalloc(&h, sizeof(u64) * 4 * kDiagSlots, hipHostMallocDefault));
-        memset(h, 0, sizeof(u64) * 4 * kDiagSlots);
+        HIPCHK(hipHostMalloc(&h, sizeof(u64) * 4 * (kDiagSlots + 1), hipHostMallocDefault));
+        memset(h, 0, sizeof(u64) * 4 * (kDiagSlots + 1));
         G.slots = (u64 *)h;
     }
     seq = ++G.seq;
-    slot = G.slots + 4 * (seq % kDiagSlots);
+    slot = G.slots + 4 * (sync ? kDiagSlots : seq % kDiagSlots);
     return BAT_OK;
 }
 
@@ -1951,7 +1954,7 @@ void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int 
 // No event is recorded: the kernels report their clocks themselves (four
 // event records took a third of a small call's time).
 int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, bool jit, bool grad,
-               const DeviceInfo &D, hipStream_t stream)
+               const DeviceInfo &D, hipStream_t stream, bool sync)
 {
     hipFunction_t fn = nullptr;
     double jit_ms = 0.0;
@@ -1961,7 +1964,7 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
         if (rc) return rc;
     }
     u64 *slot = nullptr;
-    int rc = diag_next(stream, slot, K.seq);
+    int rc = diag_next(stream, slot, K.seq, sync);
     if (rc) return rc;
     K.diag = slot;
     if (jit) {
@@ -1980,6 +1983,7 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
     t_state.info.kernel_id = kid;
     t_state.have_launch = slot != nullptr;
     t_state.cube_seq = K.seq;
+    t_state.cube_slot = slot;
     t_state.cube_dev = D.id;
     t_state.cube_khz = D.clock_khz;
     return BAT_OK;
@@ -2023,7 +2027,7 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     cube_parts(K, blocks, grad, S->dev);
     K.res = (double *)S->host;
     K.count = (u64 *)(S->host + 8 * n);
-    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream);
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, true);
     if (!rc) rc = cube_wait(K, stream);
     if (rc) {
         (void)hipStreamSynchronize(stream);
@@ -2060,7 +2064,7 @@ int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo
     K.dRdp = dRdp;
     K.T1 = T1;
     K.T0 = T0;
-    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream);
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, false);
     if (own) {
         const hipError_t e = hipFreeAsync(own, stream);
         if (!rc) HIPCHK(e);
@@ -2526,6 +2530,7 @@ int ms_finish(hipStream_t st, const DeviceInfo &D, double *part, u64 *pcount, u6
     memcpy(&count, out + 2 * sizeof(double), sizeof(u64));
     memset(&t_state.info, 0, sizeof t_state.info);
     t_state.cube_seq = seq;
+    t_state.cube_slot = slot;
     t_state.cube_dev = D.id;
     t_state.cube_khz = D.clock_khz;
     t_state.have_launch = true;
@@ -2687,7 +2692,7 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
     u64 seq = 0;
-    rc = diag_next(st, K.diag, seq);
+    rc = diag_next(st, K.diag, seq, true);
     if (rc) return rc;
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)std::max<u64>(blocks, 1), 1, 1,
@@ -2874,7 +2879,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
     u64 seq = 0;
-    rc = diag_next(st, K.diag, seq);
+    rc = diag_next(st, K.diag, seq, true);
     if (rc) return rc;
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kMsCubeWaves), 1, 1, 0, st, args,
@@ -3058,7 +3063,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     const u64 blocks = (K.n_items + bat::kWavesPerBlock - 1) / bat::kWavesPerBlock;
     if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)blocks);
     u64 seq = 0;
-    rc = diag_next(st, K.diag, seq);
+    rc = diag_next(st, K.diag, seq, true);
     if (rc) return rc;
     HIPCHK(batk::ms_sweep(st, (unsigned)std::max<u64>(blocks, 1), K));
     rc = ms_finish(st, D, K.part, K.pcount, K.n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
@@ -3397,7 +3402,7 @@ int bat_last_launch(bat_launch_info *info)
     if (!info) return fail(BAT_EINVAL, "NULL info");
     if (!t_state.have_launch) return fail(BAT_EINVAL, "no launch on this thread yet");
     if (t_state.cube_seq) {
-        const u64 *d = t_state.diag.slots + 4 * (t_state.cube_seq % kDiagSlots);
+        const u64 *d = t_state.cube_slot;
         if (!diag_done(d, t_state.cube_seq)) {
             int dev = 0;
             HIPCHK(hipGetDevice(&dev));
@@ -3405,7 +3410,12 @@ int bat_last_launch(bat_launch_info *info)
             const hipError_t e = hipDeviceSynchronize();
             (void)hipSetDevice(dev);
             HIPCHK(e);
-            if (!diag_done(d, t_state.cube_seq)) return fail(BAT_EDEVICE, "the last launch has not run");
+            if (!diag_done(d, t_state.cube_seq)) {
+                // an older launch or a replayed one ended after it, in its slot
+                t_state.info.kernel_ms = t_state.info.total_ms = 0.0;
+                *info = t_state.info;
+                return BAT_OK;
+            }
         }
         const double khz = std::max(t_state.cube_khz, 1);
         t_state.info.kernel_ms = (double)(d[1] - d[0]) / khz;
@@ -3727,7 +3737,7 @@ int cube_batch_all(std::vector<CubeJob> &jobs, int width, const DeviceInfo &D, s
         int rc = cube_batch_run(&jobs[at], std::min(jobs.size() - at, kCubeBatchJobs), width, D, sums, counts, fits);
         if (rc || !fits) return rc;
         // the launch report covers all of them
-        u64 *slot = t_state.diag.slots + 4 * (t_state.cube_seq % kDiagSlots);
+        u64 *slot = t_state.cube_slot;
         if (at == 0) start = slot[0];
         slot[0] = start;
         t_state.info.n_chunks = blocks += t_state.info.n_chunks;
@@ -3790,7 +3800,7 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
     L.sums = (bat::double2_t *)(S->host + h_sums);
     L.counts = (u64 *)(S->host + h_cnt);
     u64 *slot = nullptr;
-    rc = diag_next(st, slot, L.seq);
+    rc = diag_next(st, slot, L.seq, true);
     if (rc) return rc;
     L.diag = slot;
     u32 *be = (u32 *)S->host;
@@ -3881,6 +3891,7 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
     I.kernel_id = aot_kernel_id("k_cube_batch", width, false);
     t_state.have_launch = true;
     t_state.cube_seq = L.seq;
+    t_state.cube_slot = slot;
     t_state.cube_dev = D.id;
     t_state.cube_khz = D.clock_khz;
     return BAT_OK;

@@ -338,3 +338,37 @@ def test_cube_ranges_larger(n, m, lo, hi):
             q = B.bat_reliability_range(net.n, net.arcs, net.p, net.s, net.t, lo, hi, forward=forward)
             assert B.bat_last_launch().perm != 5
         assert r.count == q.count and abs(r.R - q.R) <= REL_GRAD * q.R
+
+
+def test_cube_reports_of_overlapping_launches():
+    """Synchronous calls while asynchronous launches, more than there are
+    report slots, and a replayed graph still write their reports."""
+    import torch
+    B = _B()
+    long, short = W.random_connected(16, 34, seed=71, p_lo=0.6, p_hi=0.99), W.random_connected(9, 16, seed=72)
+    want = [B.bat_reliability(x.n, x.arcs, x.p, x.s, x.t) for x in (long, short)]
+    side = torch.cuda.Stream()
+    pl, ps = (torch.tensor(x.p, dtype=torch.float64, device="cuda") for x in (long, short))
+    out = [(torch.zeros((), dtype=torch.float64, device="cuda"), torch.zeros((), dtype=torch.int64, device="cuda"))
+           for _ in range(3)]
+
+    def launch(x, p, o, stream):
+        B.bat_reliability_async(x.n, x.arcs, p.data_ptr(), x.s, x.t, o[0].data_ptr(), o[1].data_ptr(), None,
+                                stream.cuda_stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.bat_reliability_noalloc(short.n, short.arcs, ps.data_ptr(), short.s, short.t, out[2][0].data_ptr(),
+                                  out[2][1].data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    for k in range(40):
+        launch(long, pl, out[0], side)
+        launch(short, ps, out[1], torch.cuda.current_stream())
+        g.replay()
+        assert B.bat_reliability(short.n, short.arcs, short.p, short.s, short.t) == want[1], k
+        li = B.bat_last_launch()
+        assert 0.0 < li.kernel_ms <= li.total_ms
+    launch(short, ps, out[1], torch.cuda.current_stream())
+    B.bat_last_launch()
+    torch.cuda.synchronize()
+    for o, w in zip(out, (want[0], want[1], want[1])):
+        assert int(o[1]) == w[1] and abs(float(o[0]) - w[0]) <= REL * w[0]
