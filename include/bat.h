@@ -488,7 +488,10 @@ int bat_autotune(int32_t n_nodes, int32_t n_arcs, const bat_arc *arcs, const dou
  * its own stream, or for sub-cube sweeps the device clock at its first
  * block's start and at the reduction's start or its only block's end), the
  * number of state vectors it covered, which kernel ran
- * and the launch choices it ran with.  Returns BAT_EINVAL if nothing ran yet.
+ * and the launch choices it ran with.  The times of an asynchronous sub-cube
+ * sweep are 0 if more than 15 later ones of the thread, or replays of
+ * captured ones, have reported since in its place.  Returns BAT_EINVAL if
+ * nothing ran yet.
  */
 typedef struct {
     double kernel_ms;      /* enumeration kernel only */
