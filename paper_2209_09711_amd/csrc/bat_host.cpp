@@ -3855,9 +3855,12 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
         if (i + 1 == n || i + 1 - first >= chunk) {
             const size_t to = o_ent + stride * (i + 1);
             // the later launch runs beside the first one, whose last blocks
-            // leave CUs idle
+            // leave CUs idle; it reads the table of blocks that went up with
+            // the first copy, so it waits for that
             const hipStream_t ls = first ? SS->s[0] : st;
+            if (first) HIPCHK(hipStreamWaitEvent(ls, SS->fork, 0));
             HIPCHK(hipMemcpyAsync(S->dev + sent, S->host + sent, to - sent, hipMemcpyHostToDevice, ls));
+            if (two && !first) HIPCHK(hipEventRecord(SS->fork, st));
             sent = to;
             L.block0 = jobs[first].first_block;
             HIPCHK(batk::cube_batch(ls, (unsigned)(J.first_block + J.n_blocks - L.block0), width, L));

@@ -1,0 +1,42 @@
+"""Sub-cube sweeps at the edges of their launches: batches whose launches
+follow each other at once on a busy device, spaces of many work items,
+checkpoints and reports under other settings than they began with."""
+import numpy as np
+import pytest
+
+import bat_workloads as W
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# sums of terms of one sign by plain additions, at most some 2^9 in a chain
+# between the compensated ones: 2^9 roundings of 1.1e-16 at worst
+REL_SUMS = 6e-14
+
+
+def _B():
+    import paper_2209_09711_amd as B
+    return B
+
+
+@pytest.mark.parametrize("n_graphs,n_pvec", [(3, 1024), (2, 1023), (40, 100)])
+def test_batches_of_many_entries_per_graph(n_graphs, n_pvec):
+    """More than 64 entries, several to a graph, so that the second launch
+    follows the first without planning in between; with other work of the
+    process in front of them."""
+    import torch
+    B = _B()
+    rng = np.random.default_rng(2400 + n_pvec)
+    nets = [W.random_connected(8 + k % 3, 14 + k % 5, seed=500 + k) for k in range(n_graphs)]
+    p = [rng.uniform(0.2, 0.99, (n_pvec, x.m)) for x in nets]
+    a = torch.ones(4096, 4096, device="cuda")
+    for _ in range(8):
+        a = (a @ a).clamp_(0.0, 1.0)
+    print("cube batch", n_graphs, n_pvec, flush=True)
+    R, cnt = B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t) for x in nets], p)
+    assert B.bat_last_launch().perm == 5
+    torch.cuda.synchronize()
+    for g in range(n_graphs):
+        for j in (0, 31, 32, n_pvec // 2, n_pvec - 1) if n_graphs < 10 else (g % n_pvec,):
+            o = oracle.reliability(nets[g].n, nets[g].arcs, p[g][j], nets[g].s, nets[g].t)
+            assert cnt[g] == o.count and abs(R[g, j] - o.sum) <= REL_SUMS * o.sum, (g, j)

@@ -1,0 +1,46 @@
+"""The order in which the library's work reaches the device, on a recording
+HIP runtime (no GPU is needed)."""
+import pytest
+
+import recorder
+
+
+def _batch(graphs, pvec, arcs=12):
+    return f"""
+nets = [W.random_connected(8, {arcs}, seed=50 + k) for k in range({graphs})]
+g = [(x.n, x.arcs, x.s, x.t) for x in nets]
+p = [np.full(({pvec}, {arcs}), 0.5) for _ in g]
+try:
+    B.bat_reliability_batched(g, p)
+except B.BatError as e:
+    result = e.code
+"""
+
+
+_RANGE = """
+x = W.random_connected(16, 40, seed=9)
+try:
+    B.bat_reliability_range(x.n, x.arcs, x.p, x.s, x.t, 0, 70 << 32)
+except B.BatError as e:
+    result = e.code
+"""
+
+BATCHES = [_batch(16, 3), _batch(70, 3), _batch(3, 1024), _batch(40, 100), _batch(70, 1), _batch(1100, 2), _RANGE]
+
+
+@pytest.mark.parametrize("code", BATCHES, ids=["16x3", "70x3", "3x1024", "40x100", "70x1", "1100x2", "range"])
+def test_batch_launches_follow_their_copies(code):
+    """Every launch of a sub-cube batch, also the one on the side stream,
+    starts after all that was copied for it: the table of its blocks goes up
+    with the first copy."""
+    code, ops = recorder.run(code, fail="finish")
+    assert code == -3
+    sweeps = [i for i, o in enumerate(ops) if o.kind == "launch" and "k_cube_batch" in o.args[1] and not o.failed]
+    copies = [i for i, o in enumerate(ops) if o.kind == "copy"]
+    assert sweeps and copies
+    for i in sweeps:
+        assert {c for c in copies if c < i} <= ops[i].after
+    # and the reduction after them all
+    (end,) = [i for i, o in enumerate(ops) if o.kind == "launch" and o.failed]
+    last = max(i for i in range(end) if ops[i].kind != "sync" and ops[i].stream == ops[end].stream)
+    assert set(sweeps) <= ops[last].after | {last}
