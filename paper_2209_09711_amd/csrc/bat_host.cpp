@@ -3746,6 +3746,19 @@ int cube_batch_all(std::vector<CubeJob> &jobs, int width, const DeviceInfo &D, s
     return BAT_OK;
 }
 
+// Waits for its streams where a sweep is left early, so that nothing queued
+// still uses the thread's buffers when its next call does.
+struct Drain {
+    hipStream_t st = nullptr, side = nullptr;
+    bool on = true;
+    ~Drain()
+    {
+        if (!on) return;
+        if (side) (void)hipStreamSynchronize(side);
+        (void)hipStreamSynchronize(st);
+    }
+};
+
 int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std::vector<bat::double2_t> &sums,
                    std::vector<u64> &counts, bool &fits)
 {
@@ -3815,6 +3828,7 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
         rc = side_streams(D.id, SS);
         if (rc) return rc;
     }
+    Drain drain{st, SS ? SS->s[0] : nullptr};
     size_t chunk = two ? n / 8 : n;
     for (size_t i = 0; i < n; ++i) {
         CubeJob &J = jobs[i];
@@ -3845,8 +3859,6 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
         ok = ok && cube_pack(C, prog, (u32 *)(rec + o_step));
         if (!ok) {
             fits = false;
-            if (SS) HIPCHK(hipStreamSynchronize(SS->s[0]));
-            HIPCHK(hipStreamSynchronize(st));
             return BAT_OK;
         }
         memcpy(E.prog, prog, sizeof E.prog);
@@ -3877,10 +3889,8 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
     K.diag = L.diag;
     K.seq = L.seq;
     rc = cube_wait(K, st);
-    if (rc) {
-        (void)hipStreamSynchronize(st);
-        return rc;
-    }
+    if (rc) return rc;
+    drain.on = false;
     sums.insert(sums.end(), L.sums, L.sums + n * (size_t)width);
     counts.insert(counts.end(), L.counts, L.counts + n);
     bat_launch_info &I = t_state.info;

@@ -44,3 +44,19 @@ def test_batch_launches_follow_their_copies(code):
     (end,) = [i for i, o in enumerate(ops) if o.kind == "launch" and o.failed]
     last = max(i for i in range(end) if ops[i].kind != "sync" and ops[i].stream == ops[end].stream)
     assert set(sweeps) <= ops[last].after | {last}
+
+
+@pytest.mark.parametrize("code", [BATCHES[1], BATCHES[6]], ids=["70x3", "range"])
+def test_failed_batch_leaves_nothing_in_flight(code):
+    """Whichever call fails, both streams are waited for before the batch
+    returns: the thread's next call uses the same buffers."""
+    for k in range(40):
+        rc, ops = recorder.run(code, fail=f"#{k},k_cube_batch_finish")
+        assert rc == -3, k
+        queued = {o.stream for o in ops if o.kind in ("copy", "launch") and not o.failed}
+        for s in queued:
+            last = max(i for i, o in enumerate(ops) if o.kind in ("copy", "launch") and o.stream == s and not o.failed)
+            assert any(o.kind == "sync" and o.stream == s for o in ops[last:]), (k, s)
+        if any(o.failed and o.kind == "launch" and "finish" in o.args[1] for o in ops):
+            break
+    assert 6 < k < 39
