@@ -2711,6 +2711,11 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     return BAT_OK;
 }
 
+// Most wavefronts of a multi-state launch, so that neither its threads (HIP's
+// limit is 2^32) nor its partials grow with the space: past that each takes
+// several work items, or there are several launches.
+constexpr u64 kMsWaves = 65536;
+
 // Fewest prefixes worth their own wavefronts: 3^16 vectors at demand 3 took 66
 // us with 59049 prefixes and words of 27 cubes, 97 us with 531441 and words of
 // 3; 3^15 98 us with 177147, 114 us with 19683, a wavefront per CU.
@@ -2735,8 +2740,8 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     while (kw + kw1 < m && B1 * sig[kw + kw1] <= 32 && N / (B0 * B1 * sig[kw + kw1]) >= fewest)
         B1 *= sig[kw + kw1++];
     const u64 n_prefix = N / (B0 * B1), n_items = (n_prefix + bat::kWave - 1) / bat::kWave;
-    const u64 blocks = (n_items + bat::kMsCubeWaves - 1) / bat::kMsCubeWaves;
-    if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)n_items);
+    const u64 n_waves = std::min(n_items, kMsWaves);
+    const u64 blocks = (n_waves + bat::kMsCubeWaves - 1) / bat::kMsCubeWaves;
     auto kinds = [](int32_t c) { return (c >= 1 ? 1u : 0u) | (c == 1 ? 2u : 0u) | (c == 1 || c == 2 ? 4u : 0u); };
     std::vector<u32> c[3], word[3], lo(m, 0u), hi(m, 0u), m1(96, 0u);
     for (int k = 0; k < 3; ++k) {
@@ -2856,11 +2861,10 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     // workspace: input (tb | q1 | m1 | w) | partials | counts | output (res | count)
     const size_t o_q1 = sizeof(double) * tb.size(), o_m1 = o_q1 + sizeof(double) * 32, o_w = o_m1 + sizeof(u32) * 96;
     const size_t in_bytes = align_up(o_w + sizeof(double) * (wt.size() + 1), 256);
-    const size_t o_part = in_bytes, o_pc = align_up(o_part + sizeof(double) * 2 * n_items, 256);
-    const size_t o_res = align_up(o_pc + sizeof(u64) * n_items, 256), o_cnt = o_res + 2 * sizeof(double);
-    const size_t out_bytes = o_cnt + sizeof(u64) - o_res;
+    const size_t o_part = in_bytes, o_pc = align_up(o_part + sizeof(double) * 2 * n_waves, 256);
+    const size_t out_bytes = 2 * sizeof(double) + sizeof(u64);
     Scratch *S = nullptr;
-    rc = scratch_reserve(D.id, st, align_up(o_cnt + sizeof(u64) + 64, 256), in_bytes + out_bytes, S);
+    rc = scratch_reserve(D.id, st, o_pc + sizeof(u64) * n_waves, in_bytes + out_bytes, S);
     if (rc) return rc;
     memcpy(S->host, tb.data(), sizeof(double) * tb.size());
     memcpy(S->host + o_q1, q[1].data(), sizeof(double) * 32);
@@ -2872,6 +2876,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     memset(&K, 0, sizeof K);
     K.n_prefix = n_prefix;
     K.n_items = n_items;
+    K.n_waves = n_waves;
     K.tb = (const double *)ws;
     K.q1 = (const double *)(ws + o_q1);
     K.m1 = (const u32 *)(ws + o_m1);
@@ -2884,7 +2889,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kMsCubeWaves), 1, 1, 0, st, args,
                                  nullptr));
-    rc = ms_finish(st, D, K.part, K.pcount, n_items, K.diag, seq, S->host + in_bytes, R_hi, R_lo, count);
+    rc = ms_finish(st, D, K.part, K.pcount, n_waves, K.diag, seq, S->host + in_bytes, R_hi, R_lo, count);
     if (rc) return rc;
     bat_launch_info &I = t_state.info;
     I.vectors = N;
@@ -3025,11 +3030,10 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
             K.L = (u32)(j + 1);
         }
     }
-    K.root_lo = c_lo / K.size[K.L];
-    K.root_hi = span ? (c_hi + K.size[K.L] - 1) / K.size[K.L] : K.root_lo;
-    K.n_items = (K.root_hi - K.root_lo + 63) / 64;
-    K.c_lo = c_lo;
-    K.c_hi = c_hi;
+    // roots: those cubes.  A launch takes at most kMsWaves work items of 64;
+    // longer ranges go in several, one after the other
+    const u64 size_L = K.size[K.L], root_end = span ? (c_hi + size_L - 1) / size_L : c_lo / size_L;
+    const u64 n_items = (root_end - c_lo / size_L + 63) / 64;
     DeviceInfo D;
     rc = current_device(D);
     if (rc) return rc;
@@ -3041,13 +3045,11 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     const size_t o_cap = 0;
     const size_t o_w = align_up(o_cap + sizeof(int32_t) * (n_tab + 1), 256);
     const size_t in_bytes = align_up(o_w + sizeof(double) * (n_tab + 1), 256);
-    const u64 items = std::max<u64>(K.n_items, 1);
+    const u64 items = std::min(std::max<u64>(n_items, 1), kMsWaves);
     const size_t o_part = in_bytes;
     const size_t o_pc = align_up(o_part + sizeof(double) * 2 * items, 256);
-    const size_t o_res = align_up(o_pc + sizeof(u64) * items, 256);
-    const size_t o_cnt = o_res + 2 * sizeof(double);
-    const size_t out_bytes = o_cnt + sizeof(u64) - o_res;
-    const size_t total = align_up(o_cnt + sizeof(u64) + 64, 256);
+    const size_t total = align_up(o_pc + sizeof(u64) * items, 256);
+    const size_t out_bytes = 2 * sizeof(double) + sizeof(u64);
     Scratch *S = nullptr;
     const size_t out_host_off = in_bytes;
     rc = scratch_reserve(D.id, st, total, out_host_off + out_bytes, S);
@@ -3060,17 +3062,34 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     K.w = (const double *)(ws + o_w);
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
-    const u64 blocks = (K.n_items + bat::kWavesPerBlock - 1) / bat::kWavesPerBlock;
-    if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)blocks);
-    u64 seq = 0;
-    rc = diag_next(st, K.diag, seq, true);
-    if (rc) return rc;
-    HIPCHK(batk::ms_sweep(st, (unsigned)std::max<u64>(blocks, 1), K));
-    rc = ms_finish(st, D, K.part, K.pcount, K.n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
-    if (rc) return rc;
+    double sum[2] = {0.0, 0.0};
+    u64 number = 0, start = 0;
+    K.root_hi = c_lo / size_L;
+    do {
+        K.root_lo = K.root_hi;
+        K.root_hi = std::min(K.root_lo + 64 * kMsWaves, root_end);
+        K.n_items = (K.root_hi - K.root_lo + 63) / 64;
+        K.c_lo = std::max(c_lo, K.root_lo * size_L);
+        K.c_hi = std::min(c_hi, K.root_hi * size_L);
+        const u64 blocks = (K.n_items + bat::kWavesPerBlock - 1) / bat::kWavesPerBlock;
+        u64 seq = 0;
+        rc = diag_next(st, K.diag, seq, true);
+        if (rc) return rc;
+        HIPCHK(batk::ms_sweep(st, (unsigned)std::max<u64>(blocks, 1), K));
+        rc = ms_finish(st, D, K.part, K.pcount, K.n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
+        if (rc) return rc;
+        dd_acc(sum, R_hi, R_lo);
+        number += count;
+        // the launch report covers all of them
+        if (!start) start = K.diag[0];
+        K.diag[0] = start;
+    } while (K.root_hi < root_end);
+    R_hi = sum[0];
+    R_lo = sum[1];
+    count = number;
     bat_launch_info &I = t_state.info;
     I.vectors = span;
-    I.n_chunks = (int32_t)std::min<u64>(K.n_items, 0x7fffffff);
+    I.n_chunks = (int32_t)std::min<u64>(n_items, 0x7fffffff);
     I.chunk_log2 = -1;
     I.relaxations = m;
     I.kernel_id = aot_kernel_id("k_ms_flow", batk::ms_slots(m), K.directed != 0);

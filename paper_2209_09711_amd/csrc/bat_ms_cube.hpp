@@ -37,12 +37,13 @@ constexpr int kMsCubeQueue = 512;
 
 struct MsCubeParams {
     u64 n_prefix, n_items;  // 64 prefixes an item
+    u64 n_waves;            // wavefronts, at most the items: each takes every n_waves-th
     const double *tb;       // [2][4][256]: word 0, word 1 (times word 0's probability)
     const double *q1;       // [32] word 1's vectors
     const u32 *m1;          // [3][32] capacity bits of word 1's slots, per vector
     const double *w;        // probability of (slot, state)
-    double *part;           // [n_items][2]
-    u64 *pcount;            // [n_items]
+    double *part;           // [n_waves][2]
+    u64 *pcount;            // [n_waves]
     u64 *diag;              // [0]: the device clock at the start
 };
 
@@ -137,23 +138,8 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
             low[k] |= ((G::LO[j] >> k) & 1u) << j;
             high[k] |= ((G::HI[j] >> k) & 1u) << j;
         }
-    const u64 item = (u64)blockIdx.x * kMsCubeWaves + wave;
-    if (item >= P.n_items) return;
-    // neighbouring prefixes lie in different items
-    const u64 prefix = item + (u64)lane * P.n_items;
-    const bool live = prefix < P.n_prefix;
-    u64 r = prefix;
-    u32 up[3] = {0u, 0u, 0u};
-    double q = 1.0;
-#pragma unroll
-    for (int j = (int)(G::KW + G::KW1); j < (int)G::M; ++j) {
-        const u32 x = (u32)(r % G::SIG[j]);
-        r /= G::SIG[j];
-        up[0] |= ((G::C1[j] >> x) & 1u) << j;
-        up[1] |= ((G::CE1[j] >> x) & 1u) << j;
-        up[2] |= ((G::CE12[j] >> x) & 1u) << j;
-        q *= P.w[G::OFF[j] + x];
-    }
+    const u64 first = (u64)blockIdx.x * kMsCubeWaves + wave;
+    if (first >= P.n_waves) return;
     double hi = 0.0, lo = 0.0;
     u64 cnt = 0;
     auto add = [&](int level, double p, u32 V) {
@@ -165,39 +151,56 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
         hi = s;
         lo += e;
     };
-    const u32 most[3] = {up[0] | high[0], up[1] | high[1], up[2] | high[2]};
-    const u32 can = ms_meets<G, 1>(most, live ? G::FULL1 : 0u);
-    if (__ballot(can != 0u) != 0ull) {
-        const u32 least[3] = {up[0] | low[0], up[1] | low[1], up[2] | low[2]};
-        const u32 sure = ms_meets<G, 1>(least, can), U = can & ~sure;
-        cnt += (u64)__popc(sure) * G::B0;
-        add(1, q, sure);
-        u32 total;
-        const u32 e = wave_excl_popc(U, total);
+    for (u64 item = first; item < P.n_items; item += P.n_waves) {
+        // neighbouring prefixes lie in different items
+        const u64 prefix = item + (u64)lane * P.n_items;
+        const bool live = prefix < P.n_prefix;
+        u64 r = prefix;
+        u32 up[3] = {0u, 0u, 0u};
+        double q = 1.0;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) W.bits[k][lane] = up[k];
-        W.q[lane] = q;
-        for (u32 w0 = 0; w0 < total; w0 += kMsCubeQueue) {
-            cube_enqueue<kMsCubeQueue>(W.queue, U, e, w0, lane);
-            const u32 end = min(total, w0 + (u32)kMsCubeQueue);
-            for (u32 i = w0; i < end; i += (u32)kWave) {
-                const bool on = i + lane < end;
-                const u32 x = W.queue[(on ? i + lane : end - 1u) - w0], own = x >> 5, y = x & 31u;
-                const u32 bits[3] = {W.bits[0][own] | L.m1[0][y], W.bits[1][own] | L.m1[1][y],
-                                     W.bits[2][own] | L.m1[2][y]};
-                const u32 V = ms_meets<G, 0>(bits, on ? G::FULL0 : 0u);
-                cnt += (u64)__popc(V);
-                add(0, W.q[own] * L.q1[y], V);
+        for (int j = (int)(G::KW + G::KW1); j < (int)G::M; ++j) {
+            const u32 x = (u32)(r % G::SIG[j]);
+            r /= G::SIG[j];
+            up[0] |= ((G::C1[j] >> x) & 1u) << j;
+            up[1] |= ((G::CE1[j] >> x) & 1u) << j;
+            up[2] |= ((G::CE12[j] >> x) & 1u) << j;
+            q *= P.w[G::OFF[j] + x];
+        }
+        const u32 most[3] = {up[0] | high[0], up[1] | high[1], up[2] | high[2]};
+        const u32 can = ms_meets<G, 1>(most, live ? G::FULL1 : 0u);
+        if (__ballot(can != 0u) != 0ull) {
+            const u32 least[3] = {up[0] | low[0], up[1] | low[1], up[2] | low[2]};
+            const u32 sure = ms_meets<G, 1>(least, can), U = can & ~sure;
+            cnt += (u64)__popc(sure) * G::B0;
+            add(1, q, sure);
+            u32 total;
+            const u32 e = wave_excl_popc(U, total);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) W.bits[k][lane] = up[k];
+            W.q[lane] = q;
+            for (u32 w0 = 0; w0 < total; w0 += kMsCubeQueue) {
+                cube_enqueue<kMsCubeQueue>(W.queue, U, e, w0, lane);
+                const u32 end = min(total, w0 + (u32)kMsCubeQueue);
+                for (u32 i = w0; i < end; i += (u32)kWave) {
+                    const bool on = i + lane < end;
+                    const u32 x = W.queue[(on ? i + lane : end - 1u) - w0], own = x >> 5, y = x & 31u;
+                    const u32 bits[3] = {W.bits[0][own] | L.m1[0][y], W.bits[1][own] | L.m1[1][y],
+                                         W.bits[2][own] | L.m1[2][y]};
+                    const u32 V = ms_meets<G, 0>(bits, on ? G::FULL0 : 0u);
+                    cnt += (u64)__popc(V);
+                    add(0, W.q[own] * L.q1[y], V);
+                }
+                wave_lds_sync();
             }
-            wave_lds_sync();
         }
     }
     wave_sum_dd(hi, lo);
     const u64 c = wave_sum_u64(cnt);
     if (lane == 0) {
-        P.part[2 * item] = hi;
-        P.part[2 * item + 1] = lo;
-        P.pcount[item] = c;
+        P.part[2 * first] = hi;
+        P.part[2 * first + 1] = lo;
+        P.pcount[first] = c;
     }
 }
 

@@ -137,6 +137,7 @@ hipError_t hipGetLastError()
 
 hipError_t hipMalloc(void **p, size_t n)
 {
+    if (n >> 30) return note(hipErrorOutOfMemory, "alloc device %zu", n);
     *p = aligned_alloc(256, (n + 255) / 256 * 256);
     return note(hipSuccess, "alloc device %zu", n);
 }

@@ -40,3 +40,28 @@ def test_batches_of_many_entries_per_graph(n_graphs, n_pvec):
         for j in (0, 31, 32, n_pvec // 2, n_pvec - 1) if n_graphs < 10 else (g % n_pvec,):
             o = oracle.reliability(nets[g].n, nets[g].arcs, p[g][j], nets[g].s, nets[g].t)
             assert cnt[g] == o.count and abs(R[g, j] - o.sum) <= REL_SUMS * o.sum, (g, j)
+
+
+def _ms(B, net, demand, seed=0):
+    """A three-level network's arguments."""
+    w = np.random.default_rng(seed).uniform(0.1, 1.0, (net.m, 3))
+    w /= w.sum(axis=1, keepdims=True)
+    return net.n, net.arcs, [3] * net.m, [0, 1, 2] * net.m, list(w.ravel()), net.s, net.t, demand
+
+
+@pytest.mark.parametrize("m,demand", [(21, 1), (22, 2), (21, 3)])
+def test_multi_state_spaces_of_many_items(m, demand):
+    """More work items than wavefronts, against the sweep of every word."""
+    B = _B()
+    args = _ms(B, W.random_connected(12, m, seed=m), demand)
+    print("multi-state cubes", m, demand, flush=True)
+    R, cnt = B.bat_ms_reliability(*args)
+    li = B.bat_last_launch()
+    assert li.perm == 5 and li.n_chunks > 65536
+    old = B.bat_get_option("BAT_CUBES")
+    try:
+        B.bat_set_option("BAT_CUBES", 0)
+        want, wcnt = B.bat_ms_reliability(*args)
+    finally:
+        B.bat_set_option("BAT_CUBES", old)
+    assert cnt == wcnt and abs(R - want) <= REL_SUMS * want

@@ -60,3 +60,22 @@ def test_failed_batch_leaves_nothing_in_flight(code):
         if any(o.failed and o.kind == "launch" and "finish" in o.args[1] for o in ops):
             break
     assert 6 < k < 39
+
+
+@pytest.mark.parametrize("states,arcs,demand", [(3, 27, 1), (3, 27, 2), (3, 32, 1), (4, 31, 1), (2, 32, 3)])
+def test_large_multi_state_spaces_are_launched(states, arcs, demand):
+    """Whole multi-state spaces of any accepted size: the launch stays under
+    2^32 threads (which the recorder refuses, as HIP does) and its partials
+    under a few MiB."""
+    rc, ops = recorder.run(f"""
+x = W.random_connected(14, {arcs}, seed=5)
+try:
+    B.bat_ms_reliability(x.n, x.arcs, [{states}] * {arcs}, list(range({states})) * {arcs},
+                         [1.0 / {states}] * {states * arcs}, x.s, x.t, {demand})
+except B.BatError as e:
+    result = e.code
+""", fail="finish")
+    assert rc == -3
+    sweeps = [o for o in ops if o.kind == "launch" and "finish" not in o.args[1]]
+    assert sweeps and not any(o.failed for o in sweeps)
+    assert sum(int(o.args[1]) for o in ops if o.kind == "alloc") < 16 << 20
