@@ -65,3 +65,33 @@ def test_multi_state_spaces_of_many_items(m, demand):
     finally:
         B.bat_set_option("BAT_CUBES", old)
     assert cnt == wcnt and abs(R - want) <= REL_SUMS * want
+
+
+@pytest.mark.parametrize("states,m,demand", [(3, 15, 4), (2, 23, 2), (5, 10, 7)])
+def test_multi_state_flow_in_several_launches(states, m, demand):
+    """More cubes than one launch of the flow kernel takes (of one vector
+    each): the whole space, and a range with ends inside two launches."""
+    B = _B()
+    net = W.random_connected(9, m, seed=m + demand)
+    w = np.random.default_rng(m).uniform(0.1, 1.0, (m, states))
+    w /= w.sum(axis=1, keepdims=True)
+    args = (net.n, net.arcs, [states] * m, list(range(states)) * m, list(w.ravel()), net.s, net.t, demand)
+    N = states ** m
+    lo, hi = N // 10 + 3, N - N // 7
+    print("multi-state flow", states, m, demand, flush=True)
+    got = {}
+    old = {k: B.bat_get_option(k) for k in ("BAT_MS_RUN", "BAT_MS_BITS")}
+    try:
+        B.bat_set_option("BAT_MS_BITS", 0)
+        for run in (0, 1):
+            B.bat_set_option("BAT_MS_RUN", run)
+            got[run] = [B.bat_ms_reliability(*args)]
+            li = B.bat_last_launch()
+            assert li.vectors == N and 0.0 < li.kernel_ms <= li.total_ms and (run == 0 or li.n_chunks > 65536)
+            r = B.bat_ms_reliability_range(*args, lo, hi)
+            got[run].append((r.R, r.count))
+    finally:
+        for k, v in old.items():
+            B.bat_set_option(k, v)
+    for (R, cnt), (want, wcnt) in zip(got[1], got[0]):
+        assert cnt == wcnt and abs(R - want) <= REL_SUMS * want

@@ -62,7 +62,8 @@ def test_failed_batch_leaves_nothing_in_flight(code):
     assert 6 < k < 39
 
 
-@pytest.mark.parametrize("states,arcs,demand", [(3, 27, 1), (3, 27, 2), (3, 32, 1), (4, 31, 1), (2, 32, 3)])
+@pytest.mark.parametrize("states,arcs,demand", [(3, 27, 1), (3, 27, 2), (3, 32, 1), (4, 31, 1), (2, 32, 3),
+                                                  (3, 30, 4), (3, 32, 7), (4, 31, 5)])
 def test_large_multi_state_spaces_are_launched(states, arcs, demand):
     """Whole multi-state spaces of any accepted size: the launch stays under
     2^32 threads (which the recorder refuses, as HIP does) and its partials
