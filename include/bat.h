@@ -447,7 +447,8 @@ int bat_ms_reliability_range(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *                      (demand 1) or 2^23 vectors on (1 = of any size)
  *   "BAT_CUBE_LEVELS"  words of 5 arcs a sub-cube sweep's work item splits
  *                      (1..3; 0 = by size)
- *   "BAT_CUBE_SPLIT"   wavefronts that share such a work item (0 = by size)
+ *   "BAT_CUBE_SPLIT"   wavefronts that share such a work item (1..64; 0 = by
+ *                      size)
  *   "BAT_JIT_FLUSH"    setting it to a nonzero value unloads every
  *                      graph-specialised kernel this process compiled or
  *                      loaded (after the current device finishes its work;

@@ -62,8 +62,8 @@ struct CubeParams {
     u32 m, M;                 // arcs, arcs enumerated (counter bits)
     u32 levels, lane_bits;
     u32 split;                // units an item is split into (see cube_share)
-    u32 units;                // units per block (with gradients: chunks)
-    u32 chunk;                // with gradients: units per chunk
+    u32 units;                // units per block (with gradients and chunked sweeps: chunks)
+    u32 chunk;                // with gradients and chunked sweeps: units per chunk
     u32 fused;                // one block: it writes the results itself
     // partials: [blocks] double-doubles and counts; with gradients
     // [1 + 2 M][blocks] (R, then bit cb down and up)
@@ -248,6 +248,7 @@ __device__ __forceinline__ void cube_enqueue(unsigned short *q, u32 U, u32 e, u3
 
 template <class Args>
 struct CubeDyn {
+    static constexpr bool kChunked = false;
     Args *P;
     u32 base;  // the item's counter bits
 
@@ -317,6 +318,7 @@ struct CubeDyn {
 // The masks of the item's arcs are uniform and stay scalar.
 template <class G>
 struct CubeStatic {
+    static constexpr bool kChunked = G::CHUNKED;
     u32 um[G::M > G::REL ? G::M - G::REL : 1];  // masks of the item's arcs
 
     __device__ __forceinline__ u32 levels() const { return G::LEVELS; }
@@ -522,7 +524,10 @@ __device__ __forceinline__ void cube_results(CubeArgs *P, double hi, double lo, 
 // block; later 8.65 ms with 32, 7.9 ms with 64, 8.6 ms with 128, whose
 // blocks are too few for an even end; 8 and 16 wavefronts per block: 8.7
 // and 9.7 ms).  Each unit's sum has its own place and they
-// are added in unit order, whichever wavefront formed them.
+// are added in unit order, whichever wavefront formed them.  Past 2^23 work
+// items a place takes the sum of a chunk of consecutive units, so that
+// neither the blocks (HIP launches fewer than 2^32 threads) nor their
+// partials grow with the sweep.
 template <class Clo>
 __device__ __forceinline__ void cube_kernel(CubeArgs *P, CubeTables &T, CubeWave *Ws, Clo clo)
 {
@@ -545,8 +550,14 @@ __device__ __forceinline__ void cube_kernel(CubeArgs *P, CubeTables &T, CubeWave
         const u32 k = __builtin_amdgcn_readfirstlane(atomicAdd(&next, 1u)) / kWave;
         if (k >= units) break;
         CubeSweep<Clo> S{P, T, Ws[wave], clo, lane, 0.0, 0.0, 0ull};
-        const u64 w = first + k, it = w / split;
-        if (w < all) S.item(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
+        if constexpr (Clo::kChunked) {
+            const u64 c0 = (first + k) * P->chunk, c1 = min(all, c0 + P->chunk);
+            for (u64 w = c0; w < c1; ++w)
+                S.item(P->item_base + ((w / split * P->item_mul) & P->item_mask), (u32)(w % split));
+        } else {
+            const u64 w = first + k, it = w / split;
+            if (w < all) S.item(P->item_base + ((it * P->item_mul) & P->item_mask), (u32)(w % split));
+        }
         wave_sum_dd(S.hi, S.lo);
         const u64 c = wave_sum_u64(S.cnt);
         if (lane == 0) {

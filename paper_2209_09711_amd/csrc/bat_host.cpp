@@ -1767,6 +1767,12 @@ bool cube_pack(const batcube::CubePlan &C, bat::CubeProg *prog, u32 *step)
     return true;
 }
 
+// Most blocks a sweep of many work items is cut into (40 arcs: 8192), and the
+// work items from which its units are taken in chunks.
+constexpr u64 kCubeBlocks = 1ull << 17;
+constexpr int64_t kCubeSplitMost = 64;
+bool cube_chunked(const batcube::CubePlan &C) { return cube_items(C) > kCubeBlocks * bat::kCubeUnits; }
+
 // Most chunks of units a gradient sweep is cut into, while a block takes no
 // more than kGradUnits of them.
 constexpr u64 kGradChunks = 65536;
@@ -1794,7 +1800,7 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     // in 4, 9.1 ms whole.
     u64 split = 1;
     const u64 enough = (u64)D.cus * (C.levels == 3 ? 1024 : grad ? 4 : 16);
-    if (opts().cube_split.load() > 0) split = (u64)opts().cube_split.load();
+    if (opts().cube_split.load() > 0) split = (u64)std::min<int64_t>(opts().cube_split.load(), kCubeSplitMost);
     else
         while (split < 4 && K.n_items * split < enough) split *= 2;
     if (C.levels == 1) split = 1;
@@ -1820,9 +1826,11 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     // units per block: as many as leave every CU some 16 blocks
     while (units < bat::kCubeUnits && w / (2 * units) >= (u64)D.cus * 16) units *= 2;
     if (!grad) {
+        u64 per = 1;
+        while (cube_chunked(C) && w / (units * per) > kCubeBlocks) per *= 2;
+        K.chunk = (u32)per;
         K.units = (u32)units;
-        const u64 nb = (w + units - 1) / units;
-        if (nb > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)w);
+        const u64 nb = (w + units * per - 1) / (units * per);
         blocks = (unsigned)nb;
         K.fused = nb == 1 ? 1u : 0u;
     }
@@ -1883,7 +1891,8 @@ std::string cube_source(const batcube::CubePlan &C, bool grad, bool with_arcs = 
     num("REL", C.rel_bits());
     num("SLOTS", std::max(C.slots, 1));
     g += "  static constexpr u32 LEVELS = " + std::to_string(C.levels) + "u, LANE_BITS = " + std::to_string(C.lane_bits) +
-         "u;\n  static constexpr u32 RESULT[5] = {";
+         "u;\n  static constexpr bool CHUNKED = " + (cube_chunked(C) ? "true" : "false") +
+         ";\n  static constexpr u32 RESULT[5] = {";
     for (int k = 0; k < bat::kCubeProgs; ++k) {
         const int r = k < 2 * C.levels - 1 ? C.prog[k].result : -1;
         g += (k ? ", " : "") + std::to_string(r == -1 ? bat::kCubeNever : r == -2 ? bat::kCubeAlways : (u32)r) + "u";

@@ -95,3 +95,19 @@ def test_multi_state_flow_in_several_launches(states, m, demand):
             B.bat_set_option(k, v)
     for (R, cnt), (want, wcnt) in zip(got[1], got[0]):
         assert cnt == wcnt and abs(R - want) <= REL_SUMS * want
+
+
+def test_sweep_of_chunked_units():
+    """2^24 work items and more: units in chunks; whole and in parts."""
+    from oracle import frontier_dp
+    B = _B()
+    net = W.random_connected(24, 46, seed=1, p_lo=0.6, p_hi=0.99)
+    Rd, cd = frontier_dp.reliability(net.n, net.arcs, net.p, net.s, net.t)
+    args = (net.n, net.arcs, net.p, net.s, net.t)
+    print("chunked", net.name, flush=True)
+    R, cnt = B.bat_reliability(*args)
+    li = B.bat_last_launch()
+    assert li.perm == 5 and li.specialised == 1 and li.n_chunks == 1 << 24
+    assert cnt == cd and abs(R - Rd) <= REL_SUMS * Rd
+    R, cnt = B.bat_reliability_checkpointed(*args, net.m - 2, None)
+    assert cnt == cd and abs(R - Rd) <= REL_SUMS * Rd

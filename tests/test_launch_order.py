@@ -80,3 +80,24 @@ except B.BatError as e:
     sweeps = [o for o in ops if o.kind == "launch" and "finish" not in o.args[1]]
     assert sweeps and not any(o.failed for o in sweeps)
     assert sum(int(o.args[1]) for o in ops if o.kind == "alloc") < 16 << 20
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("m", [44, 45, 51, 56, 62])
+def test_large_sweeps_are_launched(m, grad):
+    """Whole sweeps by sub-cubes up to the most arcs: the launch stays under
+    2^32 threads and its partials under a few MiB, at the default split and
+    at the largest."""
+    for split in (0, 64):
+        rc, ops = recorder.run(f"""
+x = W.random_connected(30, {m}, seed=4)
+B.bat_set_option("BAT_CUBE_SPLIT", {split})
+try:
+    (B.bat_reliability_grad if {grad} else B.bat_reliability)(x.n, x.arcs, x.p, x.s, x.t)
+except B.BatError as e:
+    result = e.code
+""", fail="finish")
+        assert rc == -3
+        sweeps = [o for o in ops if o.kind == "launch" and "finish" not in o.args[1]]
+        assert len(sweeps) == 1 and not sweeps[0].failed, (m, split, sweeps)
+        assert split or sum(int(o.args[1]) for o in ops if o.kind == "alloc") < 32 << 20
