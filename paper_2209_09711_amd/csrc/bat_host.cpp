@@ -2816,6 +2816,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     num("D", (u64)d);
     num("KW", (u64)kw);
     num("KW1", (u64)kw1);
+    num("LOOP", n_items > n_waves ? 1u : 0u);
     num("B0", B0);
     num("FULL0", B0 == 32 ? 0xffffffffull : (1ull << B0) - 1ull);
     num("B1", B1);

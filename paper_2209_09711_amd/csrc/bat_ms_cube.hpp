@@ -24,11 +24,11 @@
 // against 137 us, 0.76 ms, 3.1 ms.
 //
 // G (compiled for one graph and one set of states): M, D, KW, KW1, B0, FULL0,
-// B1, FULL1, SLOTS, RESULT (a slot, or 255: never connected), per slot SIG,
-// OFF, C1 / CE1 / CE12 (bit k: state k has capacity >= 1 / exactly 1 / 1 or
-// 2), per word slot P1 / PE1 / PE12 (its word's vectors whose state has such
-// a capacity), per slot of word 0 LO / HI (the same three, bits 0..2, of its
-// least and greatest capacity), steps(r).
+// B1, FULL1, LOOP (more items than wavefronts), SLOTS, RESULT (a slot, or
+// 255: never connected), per slot SIG, OFF, C1 / CE1 / CE12 (bit k: state k
+// has capacity >= 1 / exactly 1 / 1 or 2), per word slot P1 / PE1 / PE12 (its
+// word's vectors whose state has such a capacity), per slot of word 0 LO / HI
+// (the same three, bits 0..2, of its least and greatest capacity), steps(r).
 
 namespace bat {
 
@@ -151,7 +151,7 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
         hi = s;
         lo += e;
     };
-    for (u64 item = first; item < P.n_items; item += P.n_waves) {
+    auto take = [&](u64 item) {
         // neighbouring prefixes lie in different items
         const u64 prefix = item + (u64)lane * P.n_items;
         const bool live = prefix < P.n_prefix;
@@ -194,6 +194,13 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
                 wave_lds_sync();
             }
         }
+    };
+    // (the loop costs the small spaces, whose items fit the wavefronts, 10% of
+    // their kernel time)
+    if constexpr (G::LOOP != 0u) {
+        for (u64 item = first; item < P.n_items; item += P.n_waves) take(item);
+    } else {
+        take(first);
     }
     wave_sum_dd(hi, lo);
     const u64 c = wave_sum_u64(cnt);
