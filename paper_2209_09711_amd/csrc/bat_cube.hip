@@ -32,10 +32,10 @@ __global__ void __launch_bounds__(bat::kCubeWaves *bat::kWave) k_cube_fwd(bat::C
 __global__ void __launch_bounds__(bat::kCubeWaves *bat::kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_cube_grad(bat::CubeParams)
 {
-    __shared__ bat::CubeTables T;
+    __shared__ bat::CubeSumTables T;
     __shared__ bat::CubeGradTables X;
     __shared__ bat::CubeGradWave W[bat::kCubeWaves];
-    __shared__ double cols[bat::kGradUnits][2 + 2 * batk::kCubeMaxBits];
+    __shared__ bat::double2_t cols[bat::grad_units(batk::kCubeMaxBits)][1 + 2 * batk::kCubeMaxBits];
     bat::CubeArgs *P = cube_args();
     bat::cube_grad_kernel(P, T, X, W, cols, bat::CubeDyn<bat::CubeArgs>{P, 0u});
 }

@@ -88,42 +88,100 @@ struct CubeParams {
 
 typedef const __attribute__((address_space(4))) CubeParams CubeArgs;
 
-struct CubeTables {
-    double tb[kCubeLevels][256];  // per level: sums over bits 0..2 of the word's index
+// FIRST: the lowest level whose words are summed by the byte tables
+// (gradients have larger records for level 0).
+template <u32 FIRST>
+struct CubeTablesFrom {
+    double tb[kCubeLevels - FIRST][256];  // per level: sums over bits 0..2 of the word's index
     double a4[kCubeLevels][4];    // bits 3..4
     double q5[kCubeLevels][32];   // all five
     double ql[kWave];             // lane bits
     double pr[64];                // working probability of the arc at counter bit cb
 };
+using CubeTables = CubeTablesFrom<0>;
+using CubeSumTables = CubeTablesFrom<1>;
 struct CubeWave {
     unsigned short queue[2][kCubeQueue];
     unsigned short from[kWave];  // level 1 prefixes (lane << 5 | word 2 index, or the lane) of the final rounds
     double qp[2][kWave];         // their probabilities
 };
 
-// x of another lane through the data-parallel primitives, 0 where there is
-// none or its row is masked.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_d(double x)
+// x of another lane through the data-parallel primitives, where there is one
+// in a bank of BANKS; else `old`.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp_d(double old, double x)
 {
-    const u64 b = (u64)__double_as_longlong(x);
-    const u32 lo = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)b, CTRL, ROWS, 0xf, false);
-    const u32 hi = (u32)__builtin_amdgcn_update_dpp(0, (int)(u32)(b >> 32), CTRL, ROWS, 0xf, false);
+    const u64 o = (u64)__double_as_longlong(old), b = (u64)__double_as_longlong(x);
+    const u32 lo = (u32)__builtin_amdgcn_update_dpp((int)(u32)o, (int)(u32)b, CTRL, 0xf, BANKS, false);
+    const u32 hi = (u32)__builtin_amdgcn_update_dpp((int)(u32)(o >> 32), (int)(u32)(b >> 32), CTRL, 0xf, BANKS, false);
     return __longlong_as_double((long long)((u64)hi << 32 | lo));
 }
 
-// The sum over the 64 lanes, in lane 63: row shifts by 1, 2, 4 and 8, then
-// the rows' last lanes broadcast.  (18 instructions; a butterfly of
-// double-doubles through LDS takes over 100, too many for 50 columns.)
-__device__ __forceinline__ double wave_sum_last(double x)
+// Lanes with bit BIT of their number clear keep a and get the a of the lane
+// with that bit set, as b; the others keep b (as b) and get that lane's b.
+template <int BIT>
+__device__ __forceinline__ void exchange(double &a, double &b)
 {
-    x += dpp_d<0x111, 0xf>(x);
-    x += dpp_d<0x112, 0xf>(x);
-    x += dpp_d<0x114, 0xf>(x);
-    x += dpp_d<0x118, 0xf>(x);
-    x += dpp_d<0x142, 0xa>(x);
-    x += dpp_d<0x143, 0xc>(x);
-    return x;
+#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC_RTC__)
+    const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
+    if constexpr (BIT >= 4) {
+        const auto lo = BIT == 5 ? __builtin_amdgcn_permlane32_swap((u32)x, (u32)y, false, false)
+                                 : __builtin_amdgcn_permlane16_swap((u32)x, (u32)y, false, false);
+        const auto hi = BIT == 5 ? __builtin_amdgcn_permlane32_swap((u32)(x >> 32), (u32)(y >> 32), false, false)
+                                 : __builtin_amdgcn_permlane16_swap((u32)(x >> 32), (u32)(y >> 32), false, false);
+        a = __longlong_as_double((long long)((u64)hi[0] << 32 | lo[0]));
+        b = __longlong_as_double((long long)((u64)hi[1] << 32 | lo[1]));
+    } else if constexpr (BIT == 3) {  // 8 lanes on in the row, either way round
+        const double k = dpp_d<0x128, 0xc>(a, b);
+        b = dpp_d<0x128, 0x3>(b, a);
+        a = k;
+    } else if constexpr (BIT == 2) {  // 4 lanes down, 4 lanes up
+        const double k = dpp_d<0x114, 0xa>(a, b);
+        b = dpp_d<0x104, 0x5>(b, a);
+        a = k;
+    } else {  // within 4 lanes
+        const bool up = (threadIdx.x >> BIT) & 1u;
+        const double send = up ? a : b, keep = up ? b : a;
+        a = keep;
+        b = BIT == 1 ? dpp_d<0x4e, 0xf>(send, send) : dpp_d<0xb1, 0xf>(send, send);
+    }
+#else
+    (void)a, (void)b;  // hipcc's host pass, which parses this and has no such builtins
+#endif
+}
+
+// The sums over the 64 lanes of N columns (double-doubles h + l): two at a
+// time change places so that each half of the lanes adds up one of them,
+// then quarters, down to a column per lane: N + 1 additions or so in all,
+// where a fold of each column by itself takes 6 N.  Columns below LOW have no
+// low parts yet.  wave_column gives the column whose sum a lane ends up with,
+// in h[0] and l[0], or N.
+template <int N, int LOW, int BIT = 5, int K>
+__device__ __forceinline__ void wave_fold(double (&h)[K], double (&l)[K])
+{
+    constexpr int H = (N + 1) / 2;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        double a = h[i], b = i + H < N ? h[i + H] : 0.0, e;
+        exchange<BIT>(a, b);
+        two_sum(a, b, h[i], e);
+        if (i >= LOW || i + H >= LOW) {
+            double c = l[i], d = i + H < N ? l[i + H] : 0.0;
+            exchange<BIT>(c, d);
+            e += c + d;
+        }
+        l[i] = e;
+    }
+    if constexpr (BIT > 0) wave_fold<H, 0, BIT - 1>(h, l);
+}
+template <int N, int BIT = 5>
+__device__ __forceinline__ u32 wave_column(u32 lane)
+{
+    constexpr u32 H = (N + 1) / 2;
+    u32 i = 0u;
+    if constexpr (BIT > 0) i = wave_column<(int)H, BIT - 1>(lane);
+    i = i < H ? i + ((lane >> BIT) & 1u) * H : (u32)N;
+    return i < (u32)N ? i : (u32)N;
 }
 
 // LDS written by some lanes of a wavefront and read by others: the LDS
@@ -136,11 +194,21 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double cube_q(const CubeTables &T, u32 M, u32 cb, u32 x)
+template <u32 FIRST>
+__device__ __forceinline__ double cube_q(const CubeTablesFrom<FIRST> &T, u32 M, u32 cb, u32 x)
 {
     if (cb >= M) return x ? 0.0 : 1.0;  // a bit past the last arc: never set
     const double p = T.pr[cb];
     return x ? p : 1.0 - p;
+}
+
+// h + l times f.  The gradients' tables of products round them once, not at
+// each factor: an error that T1 and T0 do not share stays in their difference.
+__device__ __forceinline__ void dd_mul(double &h, double &l, double f)
+{
+    const double p = h * f;
+    l = __builtin_fma(l, f, __builtin_fma(h, f, -p));
+    h = p;
 }
 
 __device__ __forceinline__ double cube_p(CubeArgs *P, u32 a) { return P->p_dev ? P->p_dev[a] : P->p[a]; }
@@ -150,14 +218,14 @@ __device__ __forceinline__ const __attribute__((address_space(4))) u32 *cube_ste
 __device__ __forceinline__ u32 cube_window(CubeArgs *, u32) { return ~0u; }
 
 // The block's probability tables (all threads).
-template <class Args>
-__device__ __forceinline__ void cube_tables(Args *P, CubeTables &T)
+template <class Args, u32 FIRST>
+__device__ __forceinline__ void cube_tables(Args *P, CubeTablesFrom<FIRST> &T)
 {
     const u32 tid = threadIdx.x, nt = blockDim.x, M = P->M, levels = P->levels;
     if (tid < M) T.pr[tid] = cube_p(P, P->arc_of_bit[tid]);
     __syncthreads();
-    for (u32 i = tid; i < levels * 256u; i += nt) {
-        const u32 l = i >> 8, y = i & 255u, c0 = kCubeGroup * l;
+    for (u32 i = tid; i + FIRST * 256u < levels * 256u; i += nt) {
+        const u32 l = FIRST + (i >> 8), y = i & 255u, c0 = kCubeGroup * l;
         double b[2][3];
 #pragma unroll
         for (u32 k = 0; k < 3; ++k) {
@@ -167,7 +235,7 @@ __device__ __forceinline__ void cube_tables(Args *P, CubeTables &T)
         double s = 0.0;
 #pragma unroll
         for (u32 k = 0; k < 8; ++k) s += ((y >> k) & 1u) ? b[k & 1u][0] * b[(k >> 1) & 1u][1] * b[k >> 2][2] : 0.0;
-        T.tb[l][y] = s;
+        T.tb[l - FIRST][y] = s;
     }
     for (u32 i = tid; i < levels * 32u; i += nt) {
         const u32 l = i >> 5, j = i & 31u;
@@ -178,9 +246,13 @@ __device__ __forceinline__ void cube_tables(Args *P, CubeTables &T)
         if ((j & 7u) == 0u) T.a4[l][j >> 3] = hi;
     }
     if (tid < (u32)kWave) {
-        double q = 1.0;
-        for (u32 b = 0; b < P->lane_bits; ++b) q *= cube_q(T, M, kCubeGroup * levels + b, (tid >> b) & 1u);
-        T.ql[tid] = q;
+        double q = 1.0, e = 0.0;
+        for (u32 b = 0; b < P->lane_bits; ++b) {
+            const double f = cube_q(T, M, kCubeGroup * levels + b, (tid >> b) & 1u);
+            if constexpr (FIRST == 0) q *= f;
+            else dd_mul(q, e, f);
+        }
+        T.ql[tid] = q + e;
     }
     __syncthreads();
 }
@@ -604,10 +676,9 @@ struct CubeGradTables {
     alignas(16) double tbx[256 * 8];  // word 0, per byte value: TB, then TB without bit a = 0..2 of state x = 0, 1
     double a4m[8];                    // word 0: A without bit 3, without bit 4
     double q5m[kCubeLevels - 1][5][32];  // words 1, 2: their probability without arc a
-    double qlm[kLaneBits][kWave];     // lane bits without one
 };
 
-__device__ __forceinline__ void cube_grad_tables(CubeArgs *P, const CubeTables &T, CubeGradTables &X)
+__device__ __forceinline__ void cube_grad_tables(CubeArgs *P, const CubeSumTables &T, CubeGradTables &X)
 {
     const u32 tid = threadIdx.x, nt = blockDim.x, M = P->M;
     for (u32 y = tid; y < 256u; y += nt) {
@@ -637,17 +708,10 @@ __device__ __forceinline__ void cube_grad_tables(CubeArgs *P, const CubeTables &
     }
     for (u32 i = tid; i < (P->levels - 1u) * 160u; i += nt) {
         const u32 l = i / 160u, a = (i % 160u) >> 5, j = i & 31u;
-        double q = 1.0;
+        double q = 1.0, e = 0.0;
         for (u32 b = 0; b < 5u; ++b)
-            if (b != a) q *= cube_q(T, M, kCubeGroup * (l + 1u) + b, (j >> b) & 1u);
-        X.q5m[l][a][j] = q;
-    }
-    for (u32 i = tid; i < P->lane_bits * (u32)kWave; i += nt) {
-        const u32 a = i >> 6, j = i & 63u;
-        double q = 1.0;
-        for (u32 b = 0; b < P->lane_bits; ++b)
-            if (b != a) q *= cube_q(T, M, kCubeGroup * P->levels + b, (j >> b) & 1u);
-        X.qlm[a][j] = q;
+            if (b != a) dd_mul(q, e, cube_q(T, M, kCubeGroup * (l + 1u) + b, (j >> b) & 1u));
+        X.q5m[l][a][j] = q + e;
     }
     __syncthreads();
 }
@@ -664,7 +728,7 @@ struct CubeGradWave {
 template <class Clo>
 struct CubeGradSweep {
     CubeArgs *P;
-    const CubeTables &T;
+    const CubeSumTables &T;
     const CubeGradTables &X;
     CubeGradWave &W;
     Clo clo;
@@ -674,7 +738,7 @@ struct CubeGradSweep {
     double g0[3][2], tb0[4];  // word 0: bits 0..2 by state; per byte for bits 3, 4
     double g1[5][2], g2[5][2];  // words 1, 2
     double free1, free2;      // cubes that connect whole, of words 1 and 2
-    double tl[kLaneBits];     // lane bits (of the lane's own state)
+    double lane_hi, lane_lo;  // all under the lane's prefix, without the lane bits' probability
     double sh[2], sl[2];      // item bit `lane`, by state
 
     __device__ __forceinline__ void zero()
@@ -687,9 +751,7 @@ struct CubeGradSweep {
         for (int h = 0; h < 4; ++h) tb0[h] = 0.0;
 #pragma unroll
         for (int a = 0; a < 5; ++a) g1[a][0] = g1[a][1] = g2[a][0] = g2[a][1] = 0.0;
-#pragma unroll
-        for (int b = 0; b < kLaneBits; ++b) tl[b] = 0.0;
-        sh[0] = sh[1] = sl[0] = sl[1] = 0.0;
+        lane_hi = lane_lo = sh[0] = sh[1] = sl[0] = sl[1] = 0.0;
     }
 
     __device__ __forceinline__ void addR(double x)
@@ -731,7 +793,7 @@ struct CubeGradSweep {
 
     __device__ __forceinline__ double word_sum(u32 level, u32 V) const
     {
-        const double *tb = T.tb[level], *a4 = T.a4[level];
+        const double *tb = T.tb[level - 1u], *a4 = T.a4[level];
         double F = a4[0] * tb[V & 255u];
         F = __builtin_fma(a4[1], tb[(V >> 8) & 255u], F);
         F = __builtin_fma(a4[2], tb[(V >> 16) & 255u], F);
@@ -880,83 +942,94 @@ struct CubeGradSweep {
         wave_lds_sync();
         v = live ? v : 0.0;
         if (__ballot(v != 0.0) == 0ull) return;
-#pragma unroll
-        for (int b = 0; b < kLaneBits; ++b)
-            if ((u32)b < lane_bits) tl[b] = __builtin_fma(qi * X.qlm[b][lane], v, tl[b]);
+        const double w = qi * v;
+        dd_add(lane_hi, lane_lo, w, __builtin_fma(qi, v, -w));
         if (rb < M) {
             double h = T.ql[lane] * v, l = 0.0;
             wave_sum_dd(h, l);
+            // (the product's own error too: T1 and T0 share most of h, whose
+            // rounding would not cancel in their difference)
             const u32 x = (u32)(block >> lane) & 1u;
+            const double vh = qm * h, vl = __builtin_fma(qm, h, -vh) + qm * l;
             if (lane + rb < M) {
-                if (x) dd_add(sh[1], sl[1], qm * h, qm * l);
-                else dd_add(sh[0], sl[0], qm * h, qm * l);
+                if (x) dd_add(sh[1], sl[1], vh, vl);
+                else dd_add(sh[0], sl[0], vh, vl);
             }
         }
     }
 
     // Fold the wavefront's columns into the chunk's place (col: [1 + 2 M],
-    // R's low part last).
-    __device__ __forceinline__ u64 write(double *col)
+    // R first).
+    __device__ __forceinline__ u64 write(double2_t *col)
     {
         const u64 c = wave_sum_u64(cnt);
         if (c == 0ull) return 0ull;  // nothing connected: every sum is 0
         const u32 levels = clo.levels(), lane_bits = clo.lane_bits(), M = clo.arcs();
         const u32 rb = kCubeGroup * levels + lane_bits;
-        auto fold = [&](u32 cb, u32 x, double v) {
-            v = wave_sum_last(v);
-            if (lane == kWave - 1u && cb < M) col[1u + 2u * cb + x] = v;
-        };
-        wave_sum_dd(hi, lo);
-        if (lane == 0) {
-            col[0] = hi;
-            col[1u + 2u * M] = lo;
+        // the words' arcs (down, up), then the lane bits', then R
+        constexpr int words = 10 * kCubeLevels, N = words + 2 * kLaneBits + 1;
+        double h[N], l[N];
+        const double f0 = free1 + free2, *am = X.a4m;
+#pragma unroll
+        for (int a = 0; a < 5; ++a)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                if (a < 3) h[2 * a + x] = g0[a][x] + f0;
+                h[10 + 2 * a + x] = g1[a][x] + free2;
+                h[20 + 2 * a + x] = g2[a][x];
+            }
+        h[6] = am[0] * tb0[0] + am[2] * tb0[2] + f0;
+        h[7] = am[1] * tb0[1] + am[3] * tb0[3] + f0;
+        h[8] = am[4] * tb0[0] + am[5] * tb0[1] + f0;
+        h[9] = am[6] * tb0[2] + am[7] * tb0[3] + f0;
+        // the lane bits' probability without each: what is below it times
+        // what is above
+        double f[kLaneBits], above[kLaneBits], ea[kLaneBits], below = 1.0, eb = 0.0;
+#pragma unroll
+        for (int b = kLaneBits - 1; b >= 0; --b) {
+            f[b] = (u32)b < lane_bits ? cube_q(T, M, kCubeGroup * levels + b, (lane >> b) & 1u) : 1.0;
+            above[b] = b == kLaneBits - 1 ? 1.0 : above[b + 1];
+            ea[b] = b == kLaneBits - 1 ? 0.0 : ea[b + 1];
+            if (b < kLaneBits - 1) dd_mul(above[b], ea[b], f[b + 1]);
         }
-        const double f0 = free1 + free2;
 #pragma unroll
-        for (u32 a = 0; a < 3; ++a) {
-            fold(a, 0u, g0[a][0] + f0);
-            fold(a, 1u, g0[a][1] + f0);
+        for (int b = 0; b < kLaneBits; ++b) {
+            const double q = below * above[b], e = __builtin_fma(below, above[b], -q) + (below * ea[b] + eb * above[b]);
+            const double v = q * lane_hi, w = __builtin_fma(q, lane_hi, -v) + (q * lane_lo + e * lane_hi);
+            const bool x = (lane >> b) & 1u;
+            h[words + 2 * b] = x ? 0.0 : v;
+            l[words + 2 * b] = x ? 0.0 : w;
+            h[words + 2 * b + 1] = x ? v : 0.0;
+            l[words + 2 * b + 1] = x ? w : 0.0;
+            dd_mul(below, eb, f[b]);
         }
-        const double *am = X.a4m;
-        fold(3u, 0u, am[0] * tb0[0] + am[2] * tb0[2] + f0);
-        fold(3u, 1u, am[1] * tb0[1] + am[3] * tb0[3] + f0);
-        fold(4u, 0u, am[4] * tb0[0] + am[5] * tb0[1] + f0);
-        fold(4u, 1u, am[6] * tb0[2] + am[7] * tb0[3] + f0);
-        if (levels > 1u)
 #pragma unroll
-            for (u32 a = 0; a < 5; ++a) {
-                fold(kCubeGroup + a, 0u, g1[a][0] + free2);
-                fold(kCubeGroup + a, 1u, g1[a][1] + free2);
-            }
-        if (levels > 2u)
-#pragma unroll
-            for (u32 a = 0; a < 5; ++a) {
-                fold(2 * kCubeGroup + a, 0u, g2[a][0]);
-                fold(2 * kCubeGroup + a, 1u, g2[a][1]);
-            }
-#pragma unroll
-        for (u32 b = 0; b < (u32)kLaneBits; ++b)
-            if (b < lane_bits) {
-                const bool x = (lane >> b) & 1u;
-                fold(kCubeGroup * levels + b, 0u, x ? 0.0 : tl[b]);
-                fold(kCubeGroup * levels + b, 1u, x ? tl[b] : 0.0);
-            }
+        for (int i = 0; i < words; ++i) l[i] = 0.0;
+        h[N - 1] = hi;
+        l[N - 1] = lo;
+        wave_fold<N, words>(h, l);
+        const u32 i = wave_column<N>(lane), b = i < (u32)words ? i / 2u : kCubeGroup * levels + (i - words) / 2u;
+        const bool arc = i < (u32)words ? b < kCubeGroup * levels : i < N - 1u && b < rb;
+        if (i == N - 1u) col[0] = {h[0], l[0]};
+        else if (arc && b < M) col[1u + 2u * b + (i & 1u)] = {h[0], l[0]};
         if (lane + rb < M) {
-            col[1u + 2u * (rb + lane)] = sh[0] + sl[0];
-            col[2u + 2u * (rb + lane)] = sh[1] + sl[1];
+            col[1u + 2u * (rb + lane)] = {sh[0], sl[0]};
+            col[2u + 2u * (rb + lane)] = {sh[1], sl[1]};
         }
         return c;
     }
 };
 
-// cols: [kGradUnits][COLS], COLS >= 2 + 2 M.
-constexpr int kGradUnits = 8;  // most chunks of a block
-template <int COLS, class Clo>
-__device__ __forceinline__ void cube_grad_kernel(CubeArgs *P, CubeTables &T, CubeGradTables &X, CubeGradWave *Ws,
-                                                 double (&cols)[kGradUnits][COLS], Clo clo)
+// cols: [grad_units(M)][COLS], COLS >= 1 + 2 M.
+// Most chunks of a block: as many as leave the LDS room for three blocks on a
+// CU.
+constexpr int grad_units(int M) { return M <= 45 ? 8 : 4; }
+template <int UNITS, int COLS, class Clo>
+__device__ __forceinline__ void cube_grad_kernel(CubeArgs *P, CubeSumTables &T, CubeGradTables &X, CubeGradWave *Ws,
+                                                 double2_t (&cols)[UNITS][COLS], Clo clo)
 {
     __shared__ u32 next;
-    __shared__ u64 sc[kGradUnits];
+    __shared__ u64 sc[UNITS];
     if (threadIdx.x == 0) {
         next = 0u;
         if (blockIdx.x == 0) {
@@ -990,7 +1063,7 @@ __device__ __forceinline__ void cube_grad_kernel(CubeArgs *P, CubeTables &T, Cub
     for (u32 i = threadIdx.x; i < 1u + 2u * M; i += blockDim.x) {
         double h = 0.0, l = 0.0;
         for (u32 k = 0; k < units; ++k)
-            if (sc[k]) dd_add(h, l, cols[k][i], i == 0u ? cols[k][1u + 2u * M] : 0.0);
+            if (sc[k]) dd_add(h, l, cols[k][i].x, cols[k][i].y);
         P->part[(u64)i * n + blockIdx.x] = {h, l};
     }
     if (threadIdx.x == 0) {

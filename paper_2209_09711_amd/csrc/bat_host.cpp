@@ -1774,7 +1774,7 @@ constexpr int64_t kCubeSplitMost = 64;
 bool cube_chunked(const batcube::CubePlan &C) { return cube_items(C) > kCubeBlocks * bat::kCubeUnits; }
 
 // Most chunks of units a gradient sweep is cut into, while a block takes no
-// more than kGradUnits of them.
+// more than grad_units of them.
 constexpr u64 kGradChunks = 65536;
 
 int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
@@ -1817,7 +1817,7 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
         while (w / per > kGradChunks) per *= 2;
         const u64 chunks = (w + per - 1) / per;
         u64 cb = (u64)waves;
-        while (cb < bat::kGradUnits && chunks / (2 * cb) >= (u64)D.cus * 4) cb *= 2;
+        while (cb < (u64)bat::grad_units(C.M) && chunks / (2 * cb) >= (u64)D.cus * 4) cb *= 2;
         K.chunk = (u32)per;
         K.units = (u32)cb;
         blocks = (unsigned)((chunks + cb - 1) / cb);
@@ -1911,9 +1911,9 @@ std::string cube_source(const batcube::CubePlan &C, bool grad, bool with_arcs = 
     if (grad)
         g += "extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) "
              "bat_cube_grad_jit(bat::CubeParams) {\n"
-             "  __shared__ bat::CubeTables T; __shared__ bat::CubeGradTables X;\n"
+             "  __shared__ bat::CubeSumTables T; __shared__ bat::CubeGradTables X;\n"
              "  __shared__ bat::CubeGradWave W[bat::kCubeWaves];\n"
-             "  __shared__ double cols[bat::kGradUnits][2 + 2 * bat::JitCube::M];\n"
+             "  __shared__ bat::double2_t cols[bat::grad_units(bat::JitCube::M)][1 + 2 * bat::JitCube::M];\n"
              "  bat::cube_grad_kernel((bat::CubeArgs *)__builtin_amdgcn_kernarg_segment_ptr(), T, X, W, cols, "
              "bat::CubeStatic<bat::JitCube>{});\n}\n";
     else

@@ -111,3 +111,48 @@ def test_sweep_of_chunked_units():
     assert cnt == cd and abs(R - Rd) <= REL_SUMS * Rd
     R, cnt = B.bat_reliability_checkpointed(*args, net.m - 2, None)
     assert cnt == cd and abs(R - Rd) <= REL_SUMS * Rd
+
+
+def _exact_gradient(net):
+    """T1, T0 in extended precision, every vector by itself."""
+    m, L = net.m, np.longdouble
+    x = (np.arange(1 << m)[:, None] >> np.arange(m)) & 1 == 1
+    reach = np.zeros((1 << m, net.n), bool)
+    reach[:, net.s] = True
+    for _ in range(net.n):
+        for i, (a, b) in enumerate(net.arcs):
+            both = (reach[:, a] | reach[:, b]) & x[:, i]
+            reach[:, a] |= both
+            reach[:, b] |= both
+    up = np.asarray(net.p, L)
+    q = np.where(x, up, 1 - up)
+    T1, T0 = np.zeros(m, L), np.zeros(m, L)
+    for i in range(m):
+        w = np.prod(np.delete(q, i, axis=1), axis=1) * reach[:, net.t]
+        T1[i], T0[i] = w[x[:, i]].sum(), w[~x[:, i]].sum()
+    return T1, T0
+
+
+def test_gradients_as_accurate_as_the_plain_sweep():
+    """Root mean square errors of T1, T0 and dR/dp over 32 networks of 12 arcs,
+    where the fold of a wavefront's columns weighs most: no more than those of
+    the plain sweep, which folds in double-double (the two scatter by some 5%
+    over samples of 380 values; a plain fold gave three times the error of
+    dR/dp)."""
+    B = _B()
+    err = {0: [], -1: []}
+    old = B.bat_get_option("BAT_CUBES")
+    try:
+        for k in range(32):
+            net = W.random_connected(8, 12, seed=900 + k, p_lo=0.6, p_hi=0.99)
+            T1, T0 = _exact_gradient(net)
+            for v in err:
+                B.bat_set_option("BAT_CUBES", v)
+                g = B.bat_reliability_grad(net.n, net.arcs, net.p, net.s, net.t)
+                assert (B.bat_last_launch().perm == 5) == (v != 0)
+                err[v].append([np.abs(a - e) / T1 for a, e in ((g.T1, T1), (g.T0, T0), (g.dRdp, T1 - T0))])
+    finally:
+        B.bat_set_option("BAT_CUBES", old)
+    rms = {v: np.sqrt((np.array(e, float) ** 2).mean(axis=(0, 2))) for v, e in err.items()}
+    print("rms errors of T1, T0, dR/dp: plain", rms[0], "cubes", rms[-1], flush=True)
+    assert np.all(rms[-1] <= 1.15 * rms[0])
