@@ -242,8 +242,9 @@ struct BatchSweep {
         wave_lds_sync();
     }
 
-    // The sum of a work item for the lane's vector (over all lanes of it).
-    __device__ __forceinline__ double item(u64 block)
+    // The sum of a work item for the lane's vector (over all lanes of it),
+    // added to h + l.
+    __device__ __forceinline__ void item(u64 block, double &h, double &l)
     {
         const u32 levels = P->levels, lane_bits = P->lane_bits, M = P->M, rb = kCubeGroup * levels + lane_bits;
         clo.item(block);
@@ -257,7 +258,7 @@ struct BatchSweep {
         } else {
             const u32 rel = lane << (2 * kCubeGroup);
             const u32 up = clo.close(1u, rel, live);
-            if (__ballot(up != 0u) == 0ull) return 0.0;
+            if (__ballot(up != 0u) == 0ull) return;
             const u32 down = clo.close(2u, rel, live && up != 0u);
             cubes(down);
             u32 total;
@@ -273,16 +274,23 @@ struct BatchSweep {
             }
             flush();
         }
+        double s, e;
+        two_sum(acc, shfl_xor_d(acc, PW), s, e);
 #pragma unroll
-        for (int off = PW; off < kWave; off <<= 1) acc += shfl_xor_d(acc, off);
-        double q = acc;
+        for (int off = 2 * PW; off < kWave; off <<= 1) {
+            const double y = shfl_xor_d(s, off), z = shfl_xor_d(e, off);
+            double t;
+            two_sum(s, y, s, t);
+            e = (e + z) + t;
+        }
+        double q = 1.0;
         const u32 p = lane % PW;
 #pragma unroll 4
         for (u32 b = rb; b < M; ++b) {
             const double x = T.pr[b][p];
             q *= (block >> (b - rb)) & 1u ? x : 1.0 - x;
         }
-        return q;
+        dd_add(h, l, q * s, q * e);
     }
 };
 
@@ -294,7 +302,7 @@ __device__ __forceinline__ void batch_block(BatchArgs *P, const BatchCubes &L, u
 {
     __shared__ BatchTables<PW> T;
     __shared__ BatchWave Ws[kBatchWaves];
-    __shared__ double su[kBatchPlaces][PW];
+    __shared__ double2_t su[kBatchPlaces][PW];
     __shared__ u64 sc[kBatchWaves];
     __shared__ u32 next;
     if (threadIdx.x == 0) next = 0u;
@@ -308,10 +316,10 @@ __device__ __forceinline__ void batch_block(BatchArgs *P, const BatchCubes &L, u
         __builtin_amdgcn_wave_barrier();  // (see cube_kernel)
         const u32 k = __builtin_amdgcn_readfirstlane(atomicAdd(&next, 1u)) / kWave;
         if (k * run >= n) break;
-        double x = 0.0;
+        double h = 0.0, l = 0.0;
         for (u32 i = k * run; i < min(n, (k + 1u) * run); ++i)
-            x += S.item(((first + i) * P->item_mul) & P->item_mask);
-        if (lane < (u32)PW) su[k][lane] = x;
+            S.item(((first + i) * P->item_mul) & P->item_mask, h, l);
+        if (lane < (u32)PW) su[k][lane] = {h, l};
     }
     const u64 c = wave_sum_u64(S.cnt);
     if (lane == 0) sc[wave] = c;
@@ -322,7 +330,7 @@ __device__ __forceinline__ void batch_block(BatchArgs *P, const BatchCubes &L, u
     const u32 p = threadIdx.x % PW, row = threadIdx.x / PW;
     double h = 0.0, l = 0.0;
     if (row < rows) {
-        for (u32 k = row; k * run < n; k += rows) dd_add(h, l, su[k][p], 0.0);
+        for (u32 k = row; k * run < n; k += rows) dd_add(h, l, su[k][p].x, su[k][p].y);
         red[threadIdx.x] = {h, l};
     }
     for (u32 s = rows / 2; s; s >>= 1) {
