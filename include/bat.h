@@ -476,9 +476,13 @@ int bat_get_option(const char *key, int64_t *value);
  * chain length are then tuned on their own, starting from the forward's.
  * The candidates' specialised kernels are compiled side by side before
  * they are timed (option "BAT_JIT_PROCS").  Later calls on a graph of the same structure use it
- * while "BAT_AUTOTUNE" is 1.  *best_ns_per_vector (may be NULL) receives the
- * best measured time per state vector.  Results never depend on the choice
- * beyond floating-point rounding; counts never change.
+ * while "BAT_AUTOTUNE" is 1.  The choice is one of the plain launch, which
+ * takes what sub-cube sweeps ("BAT_CUBES") do not: ranges with gradients or
+ * of many cubes, and everything while BAT_CUBES is 0.  *best_ns_per_vector
+ * (may be NULL) receives the best measured time per state vector of the
+ * sweep that a whole call takes: sub-cubes where they apply, else the choice.
+ * Results never depend on the choice beyond floating-point rounding; counts
+ * never change.
  */
 int bat_autotune(int32_t n_nodes, int32_t n_arcs, const bat_arc *arcs, const double *p,
                  int32_t s, int32_t t, double *best_ns_per_vector);

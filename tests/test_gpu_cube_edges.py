@@ -156,3 +156,19 @@ def test_gradients_as_accurate_as_the_plain_sweep():
     rms = {v: np.sqrt((np.array(e, float) ** 2).mean(axis=(0, 2))) for v, e in err.items()}
     print("rms errors of T1, T0, dR/dp: plain", rms[0], "cubes", rms[-1], flush=True)
     assert np.all(rms[-1] <= 1.15 * rms[0])
+
+
+def test_autotune_reports_the_sweep_that_runs():
+    """The tuner's time per vector is that of the launch a whole call takes
+    (the plain launch it also tunes is several times slower here)."""
+    B = _B()
+    net = W.random_connected(16, 33, seed=77, p_lo=0.6, p_hi=0.99)
+    print("autotune", net.name, flush=True)
+    ns = B.bat_autotune(net.n, net.arcs, net.p, net.s, net.t)
+    ks = []
+    for _ in range(5):
+        B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
+        assert B.bat_last_launch().perm == 5
+        ks.append(B.bat_last_launch().kernel_ms)
+    got = min(ks) * 1e6 / 2.0 ** net.m
+    assert 0.5 * got <= ns <= 2.0 * got, (ns, got)
