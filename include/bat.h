@@ -493,10 +493,12 @@ int bat_autotune(int32_t n_nodes, int32_t n_arcs, const bat_arc *arcs, const dou
  * its own stream, or for sub-cube sweeps the device clock at its first
  * block's start and at the reduction's start or its only block's end), the
  * number of state vectors it covered, which kernel ran
- * and the launch choices it ran with.  The times of an asynchronous sub-cube
- * sweep are 0 if more than 15 later ones of the thread, or replays of
- * captured ones, have reported since in its place.  Returns BAT_EINVAL if
- * nothing ran yet.
+ * and the launch choices it ran with.  After an asynchronous sweep the call
+ * waits for its stream, which must still exist.  The times of an asynchronous
+ * sub-cube sweep are 0 if one of the thread's sweeps at least 16 launches
+ * older ended after it, or if it has not ended and its stream is being
+ * captured.  Returns BAT_EINVAL if nothing ran yet, BAT_EDEVICE if the launch
+ * was captured into a graph.
  */
 typedef struct {
     double kernel_ms;      /* enumeration kernel only */

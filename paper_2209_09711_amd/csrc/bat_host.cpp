@@ -617,7 +617,8 @@ struct ThreadState {
     Diag diag;
     bool have_launch = false;
     u64 cube_seq = 0;  // the last launch was this sub-cube sweep (0: another kernel)
-    u64 *cube_slot = nullptr;  // which reports here
+    u64 *cube_slot = nullptr;  // which reports here (null: it was captured)
+    hipStream_t cube_stream = nullptr;
     int cube_dev = 0, cube_khz = 0;
     bat_launch_info info{};
     ~ThreadState()
@@ -740,9 +741,9 @@ int events_ready()
     return BAT_OK;
 }
 
-// The next launch's report slot; synchronous calls, which wait on theirs,
-// have one that no launch still running or replayed can write to (null: `stream` is being captured and the
-// thread has no slots yet, which cannot be allocated then).
+// The next launch's report slot (null: `stream` is being captured; a replay
+// could write to the slot at any time).  Synchronous calls, which wait on
+// theirs, have one that no launch still running can write to.
 int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, bool sync)
 {
     Diag &G = t_state.diag;
@@ -754,11 +755,13 @@ int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, bool sync)
             P.diag.pop_back();
         }
     }
-    if (!G.slots) {
+    if (!sync && stream) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (stream) HIPCHK(hipStreamIsCapturing(stream, &cs));
+        HIPCHK(hipStreamIsCapturing(stream, &cs));
         slot = nullptr;
         if (cs != hipStreamCaptureStatusNone) return BAT_OK;
+    }
+    if (!G.slots) {
         void *h = nullptr;
         HIPCHK(hipHostMalloc(&h, sizeof(u64) * 4 * (kDiagSlots + 1), hipHostMallocDefault));
         memset(h, 0, sizeof(u64) * 4 * (kDiagSlots + 1));
@@ -1990,9 +1993,9 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
     t_state.info.specialised = jit ? 1 : 0;
     t_state.info.jit_ms = jit_ms;
     t_state.info.kernel_id = kid;
-    t_state.have_launch = slot != nullptr;
-    t_state.cube_seq = K.seq;
+    t_state.cube_seq = slot ? K.seq : ~0ull;
     t_state.cube_slot = slot;
+    t_state.cube_stream = stream;
     t_state.cube_dev = D.id;
     t_state.cube_khz = D.clock_khz;
     return BAT_OK;
@@ -3432,23 +3435,33 @@ int bat_last_launch(bat_launch_info *info)
     if (!t_state.have_launch) return fail(BAT_EINVAL, "no launch on this thread yet");
     if (t_state.cube_seq) {
         const u64 *d = t_state.cube_slot;
+        if (!d) return fail(BAT_EDEVICE, "the last launch was captured: it has no times");
         if (!diag_done(d, t_state.cube_seq)) {
-            int dev = 0;
-            HIPCHK(hipGetDevice(&dev));
-            HIPCHK(hipSetDevice(t_state.cube_dev));
-            const hipError_t e = hipDeviceSynchronize();
-            (void)hipSetDevice(dev);
-            HIPCHK(e);
-            if (!diag_done(d, t_state.cube_seq)) {
-                // an older launch or a replayed one ended after it, in its slot
-                t_state.info.kernel_ms = t_state.info.total_ms = 0.0;
-                *info = t_state.info;
-                return BAT_OK;
+            // wait for its stream, not for the device, which other streams may
+            // keep busy; a stream captured itself cannot be waited for, one
+            // destroyed since leaves only the device.  (Relaxed: the thread
+            // may be capturing another stream, which this does not touch.)
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            hipError_t e = t_state.cube_stream ? hipStreamIsCapturing(t_state.cube_stream, &cs) : hipSuccess;
+            if (e == hipSuccess && cs == hipStreamCaptureStatusNone) e = hipStreamSynchronize(t_state.cube_stream);
+            if (e != hipSuccess) {
+                int dev = 0;
+                e = hipGetDevice(&dev);
+                if (e == hipSuccess) e = hipSetDevice(t_state.cube_dev);
+                if (e == hipSuccess) e = hipDeviceSynchronize();
+                (void)hipSetDevice(dev);
             }
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            HIPCHK(e);
         }
+        // no times where an older launch ended later, in this one's slot
+        const u64 t0 = d[0], t1 = d[1], t2 = d[2];
+        const bool got = diag_done(d, t_state.cube_seq) && t0 <= t1 && t1 <= t2;
         const double khz = std::max(t_state.cube_khz, 1);
-        t_state.info.kernel_ms = (double)(d[1] - d[0]) / khz;
-        t_state.info.total_ms = (double)(d[2] - d[0]) / khz;
+        t_state.info.kernel_ms = got ? (double)(t1 - t0) / khz : 0.0;
+        t_state.info.total_ms = got ? (double)(t2 - t0) / khz : 0.0;
         *info = t_state.info;
         return BAT_OK;
     }

@@ -183,6 +183,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *c)
     *c = hipStreamCaptureStatusNone;
     return hipSuccess;
 }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
 {
     *e = (hipEvent_t) new Handle{++counter};

@@ -172,3 +172,45 @@ def test_autotune_reports_the_sweep_that_runs():
         ks.append(B.bat_last_launch().kernel_ms)
     got = min(ks) * 1e6 / 2.0 ** net.m
     assert 0.5 * got <= ns <= 2.0 * got, (ns, got)
+
+
+def test_reports_while_a_stream_is_captured():
+    """bat_last_launch after an asynchronous sweep, called while the thread
+    captures another stream, waits and leaves the capture whole; a captured
+    launch has no times, and its replays none to spoil."""
+    import torch
+    B = _B()
+    long, short = W.random_connected(24, 46, seed=1, p_lo=0.6, p_hi=0.99), W.random_connected(9, 16, seed=72)
+    side = torch.cuda.Stream()
+    pl, ps = (torch.tensor(x.p, dtype=torch.float64, device="cuda") for x in (long, short))
+    out = [(torch.zeros((), dtype=torch.float64, device="cuda"), torch.zeros((), dtype=torch.int64, device="cuda"))
+           for _ in range(2)]
+
+    def launch(x, p, o, stream):
+        B.bat_reliability_async(x.n, x.arcs, p.data_ptr(), x.s, x.t, o[0].data_ptr(), o[1].data_ptr(), None,
+                                stream.cuda_stream)
+    launch(long, pl, out[0], side)
+    launch(short, ps, out[1], side)
+    torch.cuda.synchronize()
+    print("capture and report", flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        launch(long, pl, out[0], side)
+        g.capture_begin()
+        li = B.bat_last_launch()
+        launch(short, ps, out[1], torch.cuda.current_stream())
+        with pytest.raises(B.BatError) as e:
+            B.bat_last_launch()
+        g.capture_end()
+    assert li.vectors == 1 << long.m and 1.0 < li.kernel_ms <= li.total_ms
+    assert e.value.code == B.BAT_EDEVICE
+    want = B.bat_reliability(short.n, short.arcs, short.p, short.s, short.t)
+    for k in range(20):
+        out[1][0].zero_()
+        out[1][1].zero_()
+        launch(long, pl, out[0], side) if k == 3 else launch(short, ps, out[1], side)
+        g.replay()
+        li = B.bat_last_launch()
+        assert 0.0 < li.kernel_ms <= li.total_ms < 1e4, k
+        torch.cuda.synchronize()
+        assert (float(out[1][0]), int(out[1][1])) == want, k

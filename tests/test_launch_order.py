@@ -101,3 +101,29 @@ except B.BatError as e:
         sweeps = [o for o in ops if o.kind == "launch" and "finish" not in o.args[1]]
         assert len(sweeps) == 1 and not sweeps[0].failed, (m, split, sweeps)
         assert split or sum(int(o.args[1]) for o in ops if o.kind == "alloc") < 32 << 20
+
+
+_ASYNC = """
+import ctypes
+rec = ctypes.CDLL(os.environ["HIP_RECORDER"])
+x = W.random_connected(8, 14, seed=3)
+buf = np.zeros(64)
+at = buf.ctypes.data
+stream = ctypes.c_void_p()
+rec.hipStreamCreateWithFlags(ctypes.byref(stream), 0)
+"""
+
+
+def test_last_launch_waits_for_its_own_stream():
+    """The report of an asynchronous launch is waited for on its stream, not
+    on the device, which other streams may keep busy or be capturing.  (The
+    recorder runs nothing, so there are no times.)"""
+    times, ops = recorder.run(_ASYNC + """
+B.bat_reliability_async(x.n, x.arcs, at, x.s, x.t, at + 256, at + 264, None, stream.value)
+li = B.bat_last_launch()
+result = [li.kernel_ms, li.total_ms, li.perm]
+""")
+    assert times == [0.0, 0.0, 5]
+    launch = next(i for i, o in enumerate(ops) if o.kind == "launch")
+    assert [o.kind for o in ops[launch + 1:] if o.kind != "launch"] == ["sync"]
+    assert ops[-1].stream == ops[launch].stream != 0
