@@ -743,8 +743,10 @@ int events_ready()
 
 // The next launch's report slot (null: `stream` is being captured; a replay
 // could write to the slot at any time).  Synchronous calls, which wait on
-// theirs, have one that no launch still running can write to.
-int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, bool sync)
+// theirs, have one that no launch still running can write to.  A call that
+// must allocate nothing has none (null) on a thread without slots.
+enum class Report { sync, async, noalloc };
+int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, Report kind, bool *captured = nullptr)
 {
     Diag &G = t_state.diag;
     if (!G.slots) {
@@ -755,20 +757,25 @@ int diag_next(hipStream_t stream, u64 *&slot, u64 &seq, bool sync)
             P.diag.pop_back();
         }
     }
-    if (!sync && stream) {
+    slot = nullptr;
+    if (captured) *captured = false;
+    if (kind != Report::sync && stream) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIPCHK(hipStreamIsCapturing(stream, &cs));
-        slot = nullptr;
-        if (cs != hipStreamCaptureStatusNone) return BAT_OK;
+        if (cs != hipStreamCaptureStatusNone) {
+            if (captured) *captured = true;
+            return BAT_OK;
+        }
     }
     if (!G.slots) {
+        if (kind == Report::noalloc) return BAT_OK;
         void *h = nullptr;
         HIPCHK(hipHostMalloc(&h, sizeof(u64) * 4 * (kDiagSlots + 1), hipHostMallocDefault));
         memset(h, 0, sizeof(u64) * 4 * (kDiagSlots + 1));
         G.slots = (u64 *)h;
     }
     seq = ++G.seq;
-    slot = G.slots + 4 * (sync ? kDiagSlots : seq % kDiagSlots);
+    slot = G.slots + 4 * (kind == Report::sync ? kDiagSlots : seq % kDiagSlots);
     return BAT_OK;
 }
 
@@ -1963,10 +1970,10 @@ void cube_launch_info(const batcube::CubePlan &C, const bat::CubeParams &K, int 
 }
 
 // Queue the sweep (and its reduction) on `stream`; K's result pointers set.
-// No event is recorded: the kernels report their clocks themselves (four
-// event records took a third of a small call's time).
+// No event is recorded where the kernels can report their clocks themselves
+// (four event records took a third of a small call's time).
 int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, int waves, bool jit, bool grad,
-               const DeviceInfo &D, hipStream_t stream, bool sync)
+               const DeviceInfo &D, hipStream_t stream, Report kind)
 {
     hipFunction_t fn = nullptr;
     double jit_ms = 0.0;
@@ -1976,9 +1983,17 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
         if (rc) return rc;
     }
     u64 *slot = nullptr;
-    int rc = diag_next(stream, slot, K.seq, sync);
+    bool captured = false;
+    int rc = diag_next(stream, slot, K.seq, kind, &captured);
     if (rc) return rc;
     K.diag = slot;
+    const bool events = !slot && !captured;
+    if (events) {
+        rc = events_ready();
+        if (rc) return rc;
+        HIPCHK(hipEventRecord(t_state.ev[0], stream));
+        HIPCHK(hipEventRecord(t_state.ev[1], stream));
+    }
     if (jit) {
         void *args[] = {&K};
         HIPCHK(hipModuleLaunchKernel(fn, blocks, 1, 1, (unsigned)(waves * bat::kWave), 1, 1, 0, stream, args, nullptr));
@@ -1987,13 +2002,15 @@ int cube_queue(const batcube::CubePlan &C, bat::CubeParams &K, unsigned blocks, 
     } else {
         HIPCHK(batk::cube_sweep(stream, blocks, waves, K));
     }
+    if (events) HIPCHK(hipEventRecord(t_state.ev[2], stream));
     if (grad) HIPCHK(batk::cube_grad_finish(stream, blocks, K));
     else if (!K.fused) HIPCHK(batk::cube_finish(stream, blocks, K));
+    if (events) HIPCHK(hipEventRecord(t_state.ev[3], stream));
     cube_launch_info(C, K, waves);
     t_state.info.specialised = jit ? 1 : 0;
     t_state.info.jit_ms = jit_ms;
     t_state.info.kernel_id = kid;
-    t_state.cube_seq = slot ? K.seq : ~0ull;
+    t_state.cube_seq = slot ? K.seq : captured ? ~0ull : 0ull;
     t_state.cube_slot = slot;
     t_state.cube_stream = stream;
     t_state.cube_dev = D.id;
@@ -2039,7 +2056,7 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     cube_parts(K, blocks, grad, S->dev);
     K.res = (double *)S->host;
     K.count = (u64 *)(S->host + 8 * n);
-    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, true);
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, Report::sync);
     if (!rc) rc = cube_wait(K, stream);
     if (rc) {
         (void)hipStreamSynchronize(stream);
@@ -2076,7 +2093,7 @@ int cube_async(const batcube::CubePlan &C, const double *p_dev, const DeviceInfo
     K.dRdp = dRdp;
     K.T1 = T1;
     K.T0 = T0;
-    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, false);
+    rc = cube_queue(C, K, blocks, waves, jit, grad, D, stream, own || !ws ? Report::async : Report::noalloc);
     if (own) {
         const hipError_t e = hipFreeAsync(own, stream);
         if (!rc) HIPCHK(e);
@@ -2704,7 +2721,7 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
     u64 seq = 0;
-    rc = diag_next(st, K.diag, seq, true);
+    rc = diag_next(st, K.diag, seq, Report::sync);
     if (rc) return rc;
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)std::max<u64>(blocks, 1), 1, 1,
@@ -2897,7 +2914,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     K.part = (double *)(ws + o_part);
     K.pcount = (u64 *)(ws + o_pc);
     u64 seq = 0;
-    rc = diag_next(st, K.diag, seq, true);
+    rc = diag_next(st, K.diag, seq, Report::sync);
     if (rc) return rc;
     void *args[] = {&K};
     HIPCHK(hipModuleLaunchKernel(fn, (unsigned)blocks, 1, 1, (unsigned)(bat::kWave * bat::kMsCubeWaves), 1, 1, 0, st, args,
@@ -3086,7 +3103,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
         K.c_hi = std::min(c_hi, K.root_hi * size_L);
         const u64 blocks = (K.n_items + bat::kWavesPerBlock - 1) / bat::kWavesPerBlock;
         u64 seq = 0;
-        rc = diag_next(st, K.diag, seq, true);
+        rc = diag_next(st, K.diag, seq, Report::sync);
         if (rc) return rc;
         HIPCHK(batk::ms_sweep(st, (unsigned)std::max<u64>(blocks, 1), K));
         rc = ms_finish(st, D, K.part, K.pcount, K.n_items, K.diag, seq, S->host + out_host_off, R_hi, R_lo, count);
@@ -3335,7 +3352,8 @@ int bat_reliability_noalloc(int32_t n, int32_t m, const bat_arc *arcs, const dou
     if (m > 0 && !p_dev) return fail(BAT_EINVAL, "p_dev is NULL");
     Prepared X;
     TuneChoice tc;
-    int rc = prepare(n, m, arcs, nullptr, s, t, false, true, nullptr, X, tc);
+    int rc = validate(n, m, arcs, nullptr, s, t);
+    if (!rc) rc = current_device(X.D);
     if (rc) return rc;
     // set-up on this device's first call: the address of its scratch copy
     char *ws = nullptr;
@@ -3349,6 +3367,8 @@ int bat_reliability_noalloc(int32_t n, int32_t m, const bat_arc *arcs, const dou
             return cube_async(C, p_dev, X.D, st, false, R_dev, (u64 *)count_dev, nullptr, nullptr, nullptr,
                               (int *)status_dev, ws, kNoAllocScratchBytes);
     }
+    rc = prepare(n, m, arcs, nullptr, s, t, false, true, nullptr, X, tc);
+    if (rc) return rc;
     Request rq{};
     rq.n = n; rq.m = m; rq.s = s; rq.t = t; rq.arcs = arcs; rq.p_dev = p_dev;
     rq.c_lo = 0; rq.c_hi = 1ull << m; rq.grad = false;
@@ -3873,7 +3893,7 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
     L.sums = (bat::double2_t *)(S->host + h_sums);
     L.counts = (u64 *)(S->host + h_cnt);
     u64 *slot = nullptr;
-    rc = diag_next(st, slot, L.seq, true);
+    rc = diag_next(st, slot, L.seq, Report::sync);
     if (rc) return rc;
     L.diag = slot;
     u32 *be = (u32 *)S->host;

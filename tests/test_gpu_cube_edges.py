@@ -214,3 +214,28 @@ def test_reports_while_a_stream_is_captured():
         assert 0.0 < li.kernel_ms <= li.total_ms < 1e4, k
         torch.cuda.synchronize()
         assert (float(out[1][0]), int(out[1][1])) == want, k
+
+
+def test_noalloc_on_a_new_thread():
+    """Its first call there, reported through events or the thread's slots."""
+    import threading
+
+    import torch
+    B = _B()
+    net = W.random_connected(12, 24, seed=73)
+    p = torch.tensor(net.p, dtype=torch.float64, device="cuda")
+    R, cnt = torch.zeros((), dtype=torch.float64, device="cuda"), torch.zeros((), dtype=torch.int64, device="cuda")
+    got = []
+
+    def work():
+        for _ in range(2):
+            B.bat_reliability_noalloc(net.n, net.arcs, p.data_ptr(), net.s, net.t, R.data_ptr(), cnt.data_ptr(), None,
+                                      torch.cuda.current_stream().cuda_stream)
+            got.append(B.bat_last_launch())
+    print("noalloc on a thread", flush=True)
+    th = threading.Thread(target=work)
+    th.start()
+    th.join()
+    torch.cuda.synchronize()
+    assert (float(R), int(cnt)) == B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
+    assert len(got) == 2 and all(0.0 < li.kernel_ms <= li.total_ms and li.perm == 5 for li in got)

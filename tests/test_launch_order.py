@@ -127,3 +127,17 @@ result = [li.kernel_ms, li.total_ms, li.perm]
     launch = next(i for i, o in enumerate(ops) if o.kind == "launch")
     assert [o.kind for o in ops[launch + 1:] if o.kind != "launch"] == ["sync"]
     assert ops[-1].stream == ops[launch].stream != 0
+
+
+@pytest.mark.parametrize("m", [8, 14, 30])
+def test_noalloc_allocates_nothing_on_a_threads_first_call(m):
+    """Neither device memory nor pinned host memory; the launch is reported
+    through events then."""
+    times, ops = recorder.run(_ASYNC + f"""
+x = W.random_connected(max(6, {m} // 2), {m}, seed=3)
+B.bat_reliability_noalloc(x.n, x.arcs, at, x.s, x.t, at + 256, at + 264, None, stream.value)
+li = B.bat_last_launch()
+result = [li.kernel_ms, li.perm]
+""")
+    assert times == [1.0, 5]
+    assert [o.kind for o in ops].count("launch") >= 1 and not any(o.kind == "alloc" for o in ops)
