@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(kGradFinishThreads) k_cube_grad_finish(bat::Cu
         bat::dd_add(h[1], l[1], sh[k][2], sh[k][3]);
         cnt += sc[k];
     }
-    const int st = bat::cube_status(P);
+    const int st = P->done[1] ? -1 : 0;
     if (b == 0) {
         bat::cube_store(P, h[0], l[0], cnt, st);
     } else {

@@ -69,7 +69,7 @@ struct CubeParams {
     // [1 + 2 M][blocks] (R, then bit cb down and up)
     double2_t *part;
     u64 *pcount;
-    u32 *done;                // with gradients: finished blocks of the reduction
+    u32 *done;                // with gradients: finished blocks of the reduction, whether p_dev is no probability
     const double *p_dev;      // [m] on the device, or null: p below
     // results: dd and count, or R (with the check of p_dev); null where not wanted
     double *res, *R;
@@ -551,7 +551,8 @@ __device__ __forceinline__ void cube_clock(CubeArgs *P, u32 k)
     if (P->diag) P->diag[k] = wall_clock64();
 }
 
-// 0, or -1 when a p on the device is no probability.
+// 0, or -1 when a p on the device is no probability.  (By the one thread that
+// then writes the outputs, which may lie where p does.)
 __device__ __forceinline__ int cube_status(CubeArgs *P)
 {
     int st = 0;
@@ -1030,11 +1031,16 @@ __device__ __forceinline__ void cube_grad_kernel(CubeArgs *P, CubeSumTables &T, 
 {
     __shared__ u32 next;
     __shared__ u64 sc[UNITS];
-    if (threadIdx.x == 0) {
-        next = 0u;
-        if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) next = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < (u32)kWave) {
+        // p is checked here, not by the finishing kernel, whose blocks write
+        // their outputs at different times: an output may lie where p does
+        const double p = P->p_dev && threadIdx.x < P->m ? P->p_dev[threadIdx.x] : 0.0;
+        const u64 bad = __ballot(!(p >= 0.0 && p <= 1.0));
+        if (threadIdx.x == 0) {
             cube_clock(P, 0);
-            *P->done = 0u;
+            P->done[0] = 0u;
+            P->done[1] = bad ? 1u : 0u;
         }
     }
     cube_tables(P, T);

@@ -239,3 +239,38 @@ def test_noalloc_on_a_new_thread():
     torch.cuda.synchronize()
     assert (float(R), int(cnt)) == B.bat_reliability(net.n, net.arcs, net.p, net.s, net.t)
     assert len(got) == 2 and all(0.0 < li.kernel_ms <= li.total_ms and li.perm == 5 for li in got)
+
+
+@pytest.mark.parametrize("n,m", [(4, 5), (10, 18), (13, 25), (16, 34)])
+def test_outputs_in_the_place_of_p(n, m):
+    """The device forms check p before any output is written: each output in
+    turn overwrites p, with the results of separate buffers; an invalid p is
+    found all the same."""
+    import torch
+    B = _B()
+    net = W.random_connected(n, m, seed=m, p_lo=0.5, p_hi=0.99)
+    st = torch.zeros((), dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def sweep(bad, place):
+        """place: which output lies where p does."""
+        p = torch.tensor(net.p, dtype=torch.float64, device="cuda")
+        if bad:
+            p[m - 1] = 1.5
+        out = {k: torch.zeros(m, dtype=torch.float64, device="cuda") for k in ("R", "d", "T1", "T0")}
+        cnt = torch.zeros((), dtype=torch.int64, device="cuda")
+        if place:
+            out[place] = p
+        B.bat_reliability_grad_async(n, net.arcs, p.data_ptr(), net.s, net.t, out["R"].data_ptr(), cnt.data_ptr(),
+                                     out["d"].data_ptr(), out["T1"].data_ptr(), out["T0"].data_ptr(), st.data_ptr(), stream)
+        assert B.bat_last_launch().perm == 5
+        got = {k: (v[:1] if k == "R" else v).cpu().numpy() for k, v in out.items()}
+        return got, int(cnt), int(st)
+    print("outputs over p", n, m, flush=True)
+    want = sweep(False, None)
+    assert want[2] == 0
+    for place in ("d", "T1", "T0", "R"):
+        got = sweep(False, place)
+        assert got[1:] == want[1:] and all(np.array_equal(got[0][k], want[0][k]) for k in want[0]), place
+        got = sweep(True, place)
+        assert got[2] == B.BAT_EINVAL and all(np.isnan(v).all() for v in got[0].values()), place
