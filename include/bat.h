@@ -172,9 +172,11 @@ int bat_reliability_range_ex(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  *               kept, 64-bit FNV-1a hashes of the arc list and of p's
  *               bytes), the part count, the launch (arc order kind,
  *               work-item size and chain length as bat_last_launch reports
- *               them; for sub-cube sweeps the levels and bits of an item and
- *               a hash of the arcs' counter bits), the parts done, the count, then R and the per-arc T1
- *               and T0 as hexadecimal floating-point pairs (hi lo).
+ *               them; for sub-cube sweeps the levels and bits of an item, how
+ *               items are split, dealt out to blocks and summed, and a hash
+ *               of the arcs' counter bits), the parts done, the count, then R
+ *               and the per-arc T1 and T0 as hexadecimal floating-point pairs
+ *               (hi lo).
  *               The caller owns the file; it is kept after the sweep
  *               ends.
  *   max_chunks  run at most this many chunks in this call (< 0: no limit),

@@ -1787,8 +1787,15 @@ bool cube_chunked(const batcube::CubePlan &C) { return cube_items(C) > kCubeBloc
 // more than grad_units of them.
 constexpr u64 kGradChunks = 65536;
 
+// How a sweep's items are cut (split: units of an item; units: of a block;
+// chunk: units summed in one place): with the plan, the order of its sums.
+struct CubeShape {
+    u32 split = 0, units = 0, chunk = 0;  // 0: by size
+};
+
 int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
-                bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, bool grad, u64 parts = 1, u64 part = 0)
+                bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, bool grad, u64 parts = 1, u64 part = 0,
+                const CubeShape *want = nullptr)
 {
     memset(&K, 0, sizeof K);
     K.m = (u32)C.m;
@@ -1814,6 +1821,7 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     else
         while (split < 4 && K.n_items * split < enough) split *= 2;
     if (C.levels == 1) split = 1;
+    if (want && want->split) split = want->split;
     K.split = (u32)split;
     const u64 w = K.n_items * split;
     waves = (int)std::min<u64>(w, bat::kCubeWaves);
@@ -1825,9 +1833,11 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
         // 524288 units: 20.4 ms in eights, 26 ms in twos)
         u64 per = 1;
         while (w / per > kGradChunks) per *= 2;
+        if (want && want->chunk) per = want->chunk;
         const u64 chunks = (w + per - 1) / per;
         u64 cb = (u64)waves;
         while (cb < (u64)bat::grad_units(C.M) && chunks / (2 * cb) >= (u64)D.cus * 4) cb *= 2;
+        if (want && want->units) cb = want->units;
         K.chunk = (u32)per;
         K.units = (u32)cb;
         blocks = (unsigned)((chunks + cb - 1) / cb);
@@ -1836,8 +1846,10 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     // units per block: as many as leave every CU some 16 blocks
     while (units < bat::kCubeUnits && w / (2 * units) >= (u64)D.cus * 16) units *= 2;
     if (!grad) {
+        if (want && want->units) units = want->units;
         u64 per = 1;
         while (cube_chunked(C) && w / (units * per) > kCubeBlocks) per *= 2;
+        if (want && want->chunk) per = want->chunk;
         K.chunk = (u32)per;
         K.units = (u32)units;
         const u64 nb = (w + units * per - 1) / (units * per);
@@ -1849,6 +1861,19 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
     for (int c = 0; c < C.M; ++c) K.arc_of_bit[c] = (unsigned char)C.arc_of_bit[c];
     if (!jit && !cube_pack(C, K.prog, K.step)) return fail(BAT_EDEVICE, "sub-cube closures of too many steps");
     return BAT_OK;
+}
+
+// Whether a shape that a file names is one this library cuts parts of
+// `n_items` items into.
+bool cube_shape_ok(const batcube::CubePlan &C, bool grad, const CubeShape &H, u64 n_items)
+{
+    if (!H.split) return true;
+    const u32 most = grad ? (u32)bat::grad_units(C.M) : (u32)bat::kCubeUnits;
+    if (H.split > (u32)kCubeSplitMost || (C.levels == 1 && H.split != 1) || H.units < 1 || H.units > most || H.chunk < 1 ||
+        (!grad && !cube_chunked(C) && H.chunk != 1))
+        return false;
+    const u64 w = n_items * H.split, per = (u64)H.units * H.chunk;
+    return (w + per - 1) / per <= (kCubeBlocks * (u64)kCubeSplitMost);
 }
 
 // Whether the plan runs as a graph-specialised kernel: by the rule of the
@@ -2037,8 +2062,9 @@ int cube_wait(const bat::CubeParams &K, hipStream_t stream)
 // A whole sweep over host probabilities (validated); res: R as a
 // double-double, with gradients followed by T0 and T1 of each arc, written
 // by the device into the pinned staging buffer.
+// shape: how to cut the items; set to how they were.
 int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, bool grad, std::vector<double> &res,
-              u64 &count, u64 parts = 1, u64 part = 0)
+              u64 &count, u64 parts = 1, u64 part = 0, CubeShape *shape = nullptr)
 {
     hipStream_t stream;
     int rc = thread_stream(D.id, stream);
@@ -2047,8 +2073,9 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     unsigned blocks = 0;
     int waves = 0;
     const bool jit = cube_jit(C);
-    rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, grad, parts, part);
+    rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, grad, parts, part, shape);
     if (rc) return rc;
+    if (shape) *shape = CubeShape{K.split, K.units, K.chunk};
     Scratch *S = nullptr;
     const size_t n = grad ? 2 + 4 * (size_t)C.m : 2;
     rc = scratch_reserve(D.id, stream, cube_part_bytes(K, blocks, grad), 8 * (n + 1), S);
@@ -2253,8 +2280,10 @@ struct RunningSums {
     // order kind, work-item size (log2 iterations), chain length
     int order = -1, items = -1, chain = -1;
     // order kPermInfluence (sub-cube sweeps): items is 32 levels + the bits
-    // of an item, bits a hash of the arcs' counter bits
+    // of an item, bits a hash of the arcs' counter bits, shape how the items
+    // are cut (0 in files of before it was kept: by size)
     uint64_t bits = 0;
+    CubeShape shape;
     u64 parts = 0;  // chunks: parts of the whole sweep's work items
     u64 done = 0;
     u64 count = 0;
@@ -2325,11 +2354,19 @@ int checkpoint_read(const char *path, const std::string &problem, bool grad, int
     unsigned long long parts = 0, done = 0, cnt = 0, bits = 0;
     int order = -1, items = -1, chain = -1;
     char tail;
-    const int got_launch = sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d bits=%llx %c", &order, &items,
-                                  &chain, &bits, &tail);
+    CubeShape shape;
+    bool cube_line = sscanf(lines[3].c_str(),
+                            "launch order=%d items=%d chain=%d split=%u units=%u chunk=%u bits=%llx %c", &order, &items,
+                            &chain, &shape.split, &shape.units, &shape.chunk, &bits, &tail) == 7 &&
+                     shape.split && shape.units && shape.chunk;
+    if (!cube_line) {  // (a file of before the shape was kept)
+        shape = CubeShape{};
+        cube_line = sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d bits=%llx %c", &order, &items, &chain,
+                           &bits, &tail) == 4;
+    }
     const bool cubes = order == kPermInfluence;
     const bool launch_ok =
-        cubes ? got_launch == 4
+        cubes ? cube_line
               : sscanf(lines[3].c_str(), "launch order=%d items=%d chain=%d %c", &order, &items, &chain, &tail) == 3;
     if (sscanf(lines[2].c_str(), "parts %llu %c", &parts, &tail) != 1 ||
         !launch_ok ||
@@ -2367,6 +2404,7 @@ int checkpoint_read(const char *path, const std::string &problem, bool grad, int
     R.items = items;
     R.chain = chain;
     R.bits = bits;
+    R.shape = shape;
     R.parts = parts;
     R.done = done;
     R.count = cnt;
@@ -2387,8 +2425,10 @@ int checkpoint_write(const char *path, const std::string &problem, bool grad, co
 {
     std::string text = std::string(kCheckpointMagic) + "\n" + problem + "\n";
     char buf[256];
-    char bits[32] = "";
-    if (S.order == kPermInfluence) snprintf(bits, sizeof bits, " bits=%016llx", (unsigned long long)S.bits);
+    char bits[96] = "";
+    if (S.order == kPermInfluence)
+        snprintf(bits, sizeof bits, " split=%u units=%u chunk=%u bits=%016llx", S.shape.split, S.shape.units,
+                 S.shape.chunk, (unsigned long long)S.bits);
     snprintf(buf, sizeof buf, "parts %llu\nlaunch order=%d items=%d chain=%d%s\ndone %llu\ncount %llu\nR %a %a\n",
              (unsigned long long)S.parts, S.order, S.items, S.chain, bits, (unsigned long long)S.done,
              (unsigned long long)S.count, S.R[0], S.R[1]);
@@ -2436,7 +2476,8 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
         batcube::CubePlan C;
         make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C, first ? 0 : S.items / 32);
         uint64_t bits = fnv_bytes(1469598103934665603ull, C.arc_of_bit.data(), sizeof(int) * C.arc_of_bit.size());
-        if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) || !cube_fits(C)))
+        if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) ||
+                       !cube_shape_ok(C, grad, S.shape, cube_items(C) / S.parts) || !cube_fits(C)))
             return fail(BAT_EIO, "the checkpoint's work items are not the ones this library cuts");
         if (cube_fits(C)) {
             if (first) {
@@ -2448,7 +2489,7 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
             }
             u64 c = 0;
             std::vector<double> res;
-            rc = cube_sync(C, p, D, grad, res, c, S.parts, S.done);
+            rc = cube_sync(C, p, D, grad, res, c, S.parts, S.done, &S.shape);
             if (rc) return rc;
             *count = c;
             R_hl[0] = res[0];

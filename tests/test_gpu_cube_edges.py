@@ -274,3 +274,37 @@ def test_outputs_in_the_place_of_p(n, m):
         assert got[1:] == want[1:] and all(np.array_equal(got[0][k], want[0][k]) for k in want[0]), place
         got = sweep(True, place)
         assert got[2] == B.BAT_EINVAL and all(np.isnan(v).all() for v in got[0].values()), place
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("levels,m", [(2, 26), (3, 25)])
+def test_checkpoint_resumed_under_another_split(tmp_path, levels, m, grad):
+    """The file keeps how the items are cut, so that the parts after an
+    interruption are summed as those before it: the same file, bit for bit,
+    whatever the split then set; a cut that the library does not make is
+    refused."""
+    B = _B()
+    net = W.random_connected(13, m, seed=23, p_lo=0.4, p_hi=0.99)
+    args = (net.n, net.arcs, net.p, net.s, net.t, m - 2)
+    whole, cut = str(tmp_path / "whole.ckpt"), str(tmp_path / "cut.ckpt")
+    old = {k: B.bat_get_option(k) for k in ("BAT_CUBES", "BAT_CUBE_LEVELS", "BAT_CUBE_SPLIT")}
+    try:
+        for k, v in {"BAT_CUBES": 1, "BAT_CUBE_LEVELS": levels, "BAT_CUBE_SPLIT": 1}.items():
+            B.bat_set_option(k, v)
+        print("checkpoint split", levels, m, grad, flush=True)
+        B.bat_reliability_checkpointed(*args, whole, grad=grad)
+        assert B.bat_reliability_checkpointed(*args, cut, grad=grad, max_chunks=2) is None
+        B.bat_set_option("BAT_CUBE_SPLIT", 3)
+        lines = open(cut).read().splitlines()
+        for a, b in (("split=1 ", "split=65 "), ("units=", "units=1000"), ("chunk=1 ", "chunk=0 "), ("split=1 ", "")):
+            assert a in lines[3]
+            bad = str(tmp_path / "bad.ckpt")
+            open(bad, "w").write("\n".join(lines[:3] + [lines[3].replace(a, b)] + lines[4:]) + "\n")
+            with pytest.raises(B.BatError) as e:
+                B.bat_reliability_checkpointed(*args, bad, grad=grad)
+            assert e.value.code == B.BAT_EIO
+        B.bat_reliability_checkpointed(*args, cut, grad=grad)
+    finally:
+        for k, v in old.items():
+            B.bat_set_option(k, v)
+    assert open(cut).read() == open(whole).read()
