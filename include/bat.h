@@ -156,7 +156,9 @@ int bat_reliability_range_ex(int32_t n_nodes, int32_t n_arcs, const bat_arc *arc
  * order, the work-item size and the chain length are those the whole
  * sweep would take (tuned, else the defaults; with BAT_FORWARD_ORDER, the
  * forward BAT order of Section 4.2).  The first chunk fixes them, and the
- * checkpoint file keeps them, so a resumed sweep uses them too.  Chunks
+ * checkpoint file keeps them, so a resumed sweep uses them too, whatever the
+ * options then are (also a graph-specialised kernel where only that can run
+ * a sub-cube sweep's items).  Chunks
  * are added in order: R and each T1_i, T0_i as double-doubles, the count
  * exactly.  The result therefore depends on that launch only through
  * rounding, and not at all on how the chunks are spread over calls.

@@ -2072,7 +2072,8 @@ int cube_sync(const batcube::CubePlan &C, const double *p, const DeviceInfo &D, 
     bat::CubeParams K;
     unsigned blocks = 0;
     int waves = 0;
-    const bool jit = cube_jit(C);
+    // (a resumed checkpoint may need the specialised kernel whatever BAT_JIT is)
+    const bool jit = cube_jit(C) || !cube_fits(C, true);
     rc = cube_params(C, p, nullptr, D, K, blocks, waves, jit, grad, parts, part, shape);
     if (rc) return rc;
     if (shape) *shape = CubeShape{K.split, K.units, K.chunk};
@@ -2477,9 +2478,9 @@ int run_part(int32_t n, int32_t m, const bat_arc *arcs, const double *p, int32_t
         make_cubes(n, m, arcs, s, t, (flags & BAT_DIRECTED) != 0, C, first ? 0 : S.items / 32);
         uint64_t bits = fnv_bytes(1469598103934665603ull, C.arc_of_bit.data(), sizeof(int) * C.arc_of_bit.size());
         if (!first && (bits != S.bits || S.items != 32 * C.levels + C.rel_bits() || S.parts > cube_items(C) ||
-                       !cube_shape_ok(C, grad, S.shape, cube_items(C) / S.parts) || !cube_fits(C)))
+                       !cube_shape_ok(C, grad, S.shape, cube_items(C) / S.parts)))
             return fail(BAT_EIO, "the checkpoint's work items are not the ones this library cuts");
-        if (cube_fits(C)) {
+        if (!first || cube_fits(C)) {
             if (first) {
                 S.order = kPermInfluence;
                 S.items = 32 * C.levels + C.rel_bits();

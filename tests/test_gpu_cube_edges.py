@@ -308,3 +308,21 @@ def test_checkpoint_resumed_under_another_split(tmp_path, levels, m, grad):
         for k, v in old.items():
             B.bat_set_option(k, v)
     assert open(cut).read() == open(whole).read()
+
+
+@pytest.mark.parametrize("option,value", [("BAT_JIT", 0), ("BAT_JIT", 1), ("BAT_CUBES", 0), ("BAT_CHUNK_LOG2", 7)])
+def test_checkpoint_resumed_under_other_options(tmp_path, option, value):
+    """A sweep begun by sub-cubes goes on so, whatever is set since."""
+    B = _B()
+    net = W.random_connected(16, 34, seed=24, p_lo=0.6, p_hi=0.99)
+    args = (net.n, net.arcs, net.p, net.s, net.t, net.m - 1)
+    want = B.bat_reliability_checkpointed(*args, None)
+    f = str(tmp_path / "c.ckpt")
+    assert B.bat_reliability_checkpointed(*args, f, max_chunks=1) is None
+    old = B.bat_get_option(option)
+    print("checkpoint", option, value, flush=True)
+    try:
+        B.bat_set_option(option, value)
+        assert B.bat_reliability_checkpointed(*args, f) == want
+    finally:
+        B.bat_set_option(option, old)
