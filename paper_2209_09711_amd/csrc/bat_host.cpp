@@ -3838,6 +3838,7 @@ struct CubeJob {
 constexpr int kCubeBatchOneLevel = 22;
 constexpr int kCubeBatchP = 32;  // most probability vectors of an entry
 constexpr u64 kCubeBatchItems = 256;  // most work items of a block
+constexpr u64 kCubeBatchBlocks = 1ull << 20;
 constexpr size_t kCubeBatchJobs = 1024;  // most entries of a sweep (about 12 KiB of staging each)
 
 // Vectors a lane group of the kernel is made for.
@@ -3913,7 +3914,12 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
         J.n_blocks = (u32)((J.items + J.units - 1) / J.units);
         blocks += J.n_blocks;
     }
-    if (blocks > 0x7fffffffull) return fail(BAT_ETOOBIG, "too many work items (%llu)", (unsigned long long)blocks);
+    // (reached only with one level forced on large graphs: 1024 threads a
+    // block, fewer than 2^32 in a launch)
+    if (blocks > kCubeBatchBlocks) {
+        fits = false;
+        return BAT_OK;
+    }
     // records: the entry, its steps, its probabilities
     const size_t o_step = align_up(sizeof(bat::BatchCube), 64);
     const size_t o_p = o_step + align_up(sizeof(u32) * (bat::kCubeSteps + 4), 64);

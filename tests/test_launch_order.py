@@ -141,3 +141,18 @@ result = [li.kernel_ms, li.perm]
 """)
     assert times == [1.0, 5]
     assert [o.kind for o in ops].count("launch") >= 1 and not any(o.kind == "alloc" for o in ops)
+
+
+def test_batch_of_too_many_blocks_goes_to_the_plain_launch():
+    """One level forced on 512 graphs of 32 arcs: 4 million blocks."""
+    rc, ops = recorder.run("""
+x = W.random_connected(12, 32, seed=8)
+B.bat_set_option("BAT_CUBES", 1)
+B.bat_set_option("BAT_CUBE_LEVELS", 1)
+try:
+    B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t)] * 512, [np.full((2, 32), 0.5)] * 512)
+except B.BatError as e:
+    result = e.code
+""", fail="k_batched_reduce,finish")
+    assert not any(o.failed for o in ops if o.kind == "launch" and "k_cube" in o.args[1])
+    assert any(o.kind == "launch" and "k_batched" in o.args[1] for o in ops)
