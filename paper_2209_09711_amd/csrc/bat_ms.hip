@@ -21,14 +21,24 @@
 // capacities stays feasible with the greatest, so the second test goes on
 // from the first.  A child whose slot has the least capacity has failed its
 // first test already (its parent's), one with the greatest has met its
-// second; at K = 0 those are verdicts.
+// second; at K = 0 those are verdicts.  An undecided cube of slot 0 alone is
+// not split: as a function of one arc's capacity c the maximum flow is
+// min(A + c, B), the smaller of the least cut through the arc and the least
+// one that avoids it, so where it is short of d by x at the least capacity
+// and meets d at the greatest, it meets d from x units more on.  (Split into
+// its states, one test each: 3^15 vectors at demand 4 0.35 ms a call, now
+// 0.29; 16^7 at demand 14 45 ms, now 6.2, against 8.3 ms with a run of
+// vectors per lane.)
 //
 // A wavefront takes 64 cubes of the `L` lowest slots, one per lane, and from
 // there its lanes share one stack of nodes in LDS: a lane whose node is
 // decided takes the next one, so that no lane waits for another's deep cube
 // (lanes run in lockstep: which lane takes which node, and with it the sum,
-// is fixed).  When the stack is nearly full a lane keeps its children to
-// itself and goes through them in order, which needs no memory.
+// is fixed).  A lane that finds no more room on the stack keeps its children
+// to itself and goes through them in order, which needs no memory.  (With
+// room for all 64 lanes' children asked of it, arcs of more than 8 states
+// never shared any: 10^8 vectors at demand 9 30 ms, 3.5 with what room there
+// is.)
 //
 // The flow test pushes augmenting paths found on node bitmasks: a search
 // sweeps the slots in order, adding the far end of every arc with residual
@@ -45,12 +55,12 @@
 // and orders a whole space's slots by distance from the nearer terminal, the
 // farthest lowest: the arcs that rarely matter are free in the cubes.
 //
-// What bounds it: the sweeps' instructions, about 35 steps of 1100 per
-// wavefront at half its lanes on 3^15 vectors and demand 4: 0.36 ms against
-// 1.27 ms with a run of vectors per lane, each tested by itself.  (An item of
-// 64 neighbouring cubes 0.63 ms; one sweep, one way, per step 1.15 ms; slots
-// ordered outward from s leave twice as many cubes undecided.  Demands of 1
-// to 3 run bit-sliced: 3^18 vectors, demand 2, 0.11 against 2.4 ms.)
+// What bounds it: the sweeps' instructions, some 30 steps of 1100 per
+// wavefront at half its lanes on 3^15 vectors and demand 4: 0.26 ms against
+// 1.22 ms with a run of vectors per lane, each tested by itself.  (Before
+// slot 0's bound: an item of 64 neighbouring cubes 0.63 ms against 0.32; one
+// sweep, one way, per step 1.15 ms; slots ordered outward from s leave twice
+// as many cubes undecided.)
 #include <hip/hip_runtime.h>
 
 #include "bat_launch.hpp"
@@ -137,16 +147,28 @@ k_ms_flow(batk::MsParams P)
     int rf[MM], rb[MM];  // residual capacity of each slot's arc, u -> v and v -> u
 #pragma unroll
     for (int i = 0; i < MM; ++i) rf[i] = rb[i] = 0;
-    int total = 0;
-    bool high = false;  // testing the greatest capacities
+    const bool two = sig[0] <= 2;  // slot 0's states are its least and its greatest
+    int total = 0, base = 0;       // the flow; its greatest with the least capacities
+    bool high = false;             // testing the greatest capacities
     u32 reach = 0u, tf = 0u, tb = 0u;
 
     auto state = [&](u32 i) -> u32 {
         return i < (u32)batk::kMsTreeSlots && i < L ? (u32)(node >> (5u * i)) & 31u
                                                     : (u32)roots[wave][(node >> kMsAtRoot) & 63u][i];
     };
-    auto met = [&](u64 nd, u32 k) {  // the cube's weight
+    // the cube's weight (need: only its states of slot 0 of that capacity)
+    auto met = [&](u64 nd, u32 k, int need) {
         double pr = weight[k];
+        u64 number = size[k];
+        if (need > 0) {
+            pr = 0.0;
+            number = 0ull;
+            for (int x = 0; x < sig[0]; ++x) {
+                const bool on = capt[x] >= need;
+                pr += on ? wt[x] : 0.0;
+                number += on ? 1ull : 0ull;
+            }
+        }
 #pragma unroll
         for (u32 i = 0; i < (u32)MM; ++i) {
             const u32 x = i < (u32)batk::kMsTreeSlots && i < L ? (u32)(nd >> (5u * i)) & 31u
@@ -157,7 +179,7 @@ k_ms_flow(batk::MsParams P)
         bat::two_sum(hi, pr, s_, e_);
         hi = s_;
         lo += e_;
-        cnt += size[k];
+        cnt += number;
     };
     // the child of `nd` (of cube k) with state x in slot k - 1
     auto child = [&](u64 nd, u32 k, u32 x) -> u64 {
@@ -184,7 +206,8 @@ k_ms_flow(batk::MsParams P)
             }
             sp -= n;
         }
-        // -1: the test goes on; 0: not met; 1: met; 2: split
+        // -1: the test goes on; 0: not met; 1: met; 2: split; 3: met from
+        // some capacity of slot 0 on
         int out = -1;
         if (fresh) {
             fresh = false;
@@ -197,8 +220,8 @@ k_ms_flow(batk::MsParams P)
             }
             if ((node & kMsLowFails) && K == 0u) out = 0;
             else if ((node & kMsHighMeets) && K == 0u) out = 1;
-            else if ((node & kMsLowFails) && (node & kMsHighMeets)) out = 2;
-            high = (node & kMsLowFails) != 0ull;
+            else if ((node & kMsLowFails) && (node & kMsHighMeets) && (K != 1u || two)) out = K == 1u ? 3 : 2;
+            high = (node & kMsLowFails) && (K != 1u || two);
 #pragma unroll
             for (u32 i = 0; i < (u32)MM; ++i) {
                 const int c = capt[P.off[i] + state(i)];
@@ -232,10 +255,12 @@ k_ms_flow(batk::MsParams P)
                 if (high || K == 0u) {
                     out = 0;
                 } else if (node & kMsHighMeets) {
-                    out = 2;
+                    out = K == 1u ? 3 : 2;
+                    base = total;
                 } else {
                     // the greatest capacities, from this flow and reach
                     high = true;
+                    base = total;
 #pragma unroll
                     for (u32 i = 0; i < (u32)MM; ++i) {
                         const int more = i < K ? P.most[i] - P.least[i] : 0;
@@ -280,14 +305,17 @@ k_ms_flow(batk::MsParams P)
                 total += b;
                 reach = 1u << s;
                 tf = tb = 0u;
-                if (total >= d) out = high ? 2 : 1;
+                if (total >= d) out = !high ? 1 : K == 1u ? 3 : 2;
             }
         }
-        if (out == 1) met(node, K);
-        // the cubes that split: children on the stack while there is room for
-        // every lane's, else the lane goes to the first of its own
+        if (out == 1) met(node, K, 0);
+        if (out == 3) met(node, 1u, two ? most[0] : least[0] + d - base);
+        // the cubes that split: children on the stack while there is room,
+        // else the lane goes to the first of its own
         if (__ballot(out == 2) != 0ull) {
-            const bool room = sp + 64u * P.most_states <= kMsStack;
+            const u64 split = __ballot(out == 2);
+            const u32 rank = __builtin_amdgcn_mbcnt_hi((u32)(split >> 32), __builtin_amdgcn_mbcnt_lo((u32)split, 0u));
+            const bool room = sp + (rank + 1u) * P.most_states <= kMsStack;
             bool more = out == 2;
             if (!room && more) {
                 node = child(node, K, 0u);
@@ -306,7 +334,7 @@ k_ms_flow(batk::MsParams P)
                     push = true;
                     if (K == 1u && (c & (kMsLowFails | kMsHighMeets))) {  // a verdict
                         push = false;
-                        if (!(c & kMsLowFails)) met(c, 0u);
+                        if (!(c & kMsLowFails)) met(c, 0u, 0);
                     }
                 }
                 const u64 w = __ballot(push);

@@ -326,3 +326,40 @@ def test_checkpoint_resumed_under_other_options(tmp_path, option, value):
         assert B.bat_reliability_checkpointed(*args, f) == want
     finally:
         B.bat_set_option(option, old)
+
+
+@pytest.mark.parametrize("run", [0, 1, 40, 1 << 20])
+@pytest.mark.parametrize("states", [2, 3, 5, 9, 12, 32])
+def test_multi_state_flow_of_many_states(states, run):
+    """The flow kernel's cubes over arcs of many states, their capacities in
+    order, in no order, equal for several states: whole spaces and ranges
+    against the oracle.  R: compensated sums of products of at most 13
+    factors, one a sum of up to 32 terms, some 45 roundings of 1.1e-16."""
+    B = _B()
+    rng = np.random.default_rng(2500 + states)
+    m = {2: 13, 3: 9, 5: 6, 9: 4, 12: 4, 32: 3}[states]
+    old = {k: B.bat_get_option(k) for k in ("BAT_MS_RUN", "BAT_MS_BITS")}
+    try:
+        B.bat_set_option("BAT_MS_BITS", 0)
+        B.bat_set_option("BAT_MS_RUN", run)
+        for k in range(6):
+            n = int(rng.integers(3, 7))
+            net = W.random_multigraph(n, m, seed=int(rng.integers(1 << 30)))
+            cap = rng.integers(0, 2 * states if k % 2 else 4, (m, states))
+            if k < 4:
+                cap = np.sort(cap, axis=1)
+            w = rng.uniform(0.0, 1.0, (m, states))
+            args = (net.n, net.arcs, [states] * m, cap, w / w.sum(axis=1, keepdims=True), 0, net.n - 1,
+                    int(rng.integers(1, 3 * states)))
+            N = states ** m
+            lo, hi = sorted(int(x) for x in rng.integers(0, N + 1, 2))
+            print("multi-state flow", states, run, k, net.n, m, args[-1], lo, hi, flush=True)
+            R, cnt = B.bat_ms_reliability(*args, directed=k == 3)
+            r = B.bat_ms_reliability_range(*args, lo, hi, directed=k == 3)
+            o = oracle.ms_reliability(*args, directed=k == 3)
+            p = oracle.ms_reliability_range(*args, lo, hi, directed=k == 3)
+            assert (cnt, r.count) == (o.count, p.count)
+            assert abs(R - o.sum) <= 5e-15 * o.sum and abs(r.R - p.sum) <= 5e-15 * p.sum
+    finally:
+        for k, v in old.items():
+            B.bat_set_option(k, v)
