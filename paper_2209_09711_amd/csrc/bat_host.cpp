@@ -1721,13 +1721,7 @@ bool cubes_wanted()
     return want == 1 || opts().plain_shape_default();
 }
 
-// Levels by size.  One level decides every word of 32 vectors by itself: one
-// closure deep, so the shortest while the device holds its 2^(M - 11)
-// wavefronts (24 arcs: 16 us against 12 us with two levels; 22 arcs: 8 us
-// against 10 us).  Three levels decide less (30 arcs: 42 us against 34 us)
-// but run longer chains of closures per wavefront; they win from 33 arcs on
-// (specialised: 32 arcs 126 us against 94 us, 33 arcs 110 us against 131 us,
-// 35 arcs 0.14 ms against 0.39 ms).
+// The arcs a sub-cube sweep enumerates.
 std::vector<char> cube_arcs(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed)
 {
     std::vector<char> rel = relevance(n, m, arcs, s, t, directed);
@@ -1736,6 +1730,13 @@ std::vector<char> cube_arcs(int32_t n, int32_t m, const bat_arc *arcs, int32_t s
     return rel;
 }
 
+// Levels by size.  One level decides every word of 32 vectors by itself: one
+// closure deep, so the shortest while the device holds its 2^(M - 11)
+// wavefronts (24 arcs: 16 us against 12 us with two levels; 22 arcs: 8 us
+// against 10 us).  Three levels decide less (30 arcs: 42 us against 34 us)
+// but run longer chains of closures per wavefront; they win from 33 arcs on
+// (specialised: 32 arcs 126 us against 94 us, 33 arcs 110 us against 131 us,
+// 35 arcs 0.14 ms against 0.39 ms).
 void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t, bool directed,
                 batcube::CubePlan &C, int levels = 0)
 {
@@ -1747,9 +1748,7 @@ void make_cubes(int32_t n, int32_t m, const bat_arc *arcs, int32_t s, int32_t t,
     batcube::make_cube_plan(n, m, arcs, rel, s, t, directed, levels, C);
 }
 
-// The launch of a cube plan: everything but the result and partial pointers.
-// part j of `parts` (a power of two, at most the items): the items that are
-// j modulo parts.
+// Work items of a whole sweep.
 u64 cube_items(const batcube::CubePlan &C) { return 1ull << std::max(0, C.M - C.rel_bits()); }
 
 // The closures as the ahead-of-time kernels read them.
@@ -1793,6 +1792,9 @@ struct CubeShape {
     u32 split = 0, units = 0, chunk = 0;  // 0: by size
 };
 
+// The launch of a cube plan: everything but the result and partial pointers.
+// part j of `parts` (a power of two, at most the items): the items that are
+// j modulo parts.
 int cube_params(const batcube::CubePlan &C, const double *p_host, const double *p_dev, const DeviceInfo &D,
                 bat::CubeParams &K, unsigned &blocks, int &waves, bool jit, bool grad, u64 parts = 1, u64 part = 0,
                 const CubeShape *want = nullptr)
@@ -2792,9 +2794,9 @@ constexpr u64 kMsWaves = 65536;
 // 3; 3^15 98 us with 177147, 114 us with 19683, a wavefront per CU.
 constexpr u64 kMsCubePrefixes = 32768;
 // Vectors from which the cubes win.  Whole calls, cubes against every word by
-// itself: 3^14 90 and 66 us at demand 1, 90 and 75 us at 2, 91 and 81 us at 3;
-// 3^15 90 and 79, 93 and 111, 181 and 174 us; 3^17 89 and 114, 97 and 295,
-// 455 and 1101 us.
+// itself (10 nodes): 3^14 52 and 34 us at demand 1, 53 and 42 us at 2, 51 and
+// 44 us at 3; 3^15 53 and 44, 56 and 71, 53 and 80 us; 3^17 57 and 74, 67 and
+// 181, 282 and 851 us.
 constexpr u64 ms_cube_vectors(int d) { return 1ull << (d == 1 ? 26 : 23); }
 
 // A whole space with demand <= 3 by cubes (bat_ms_cube.hpp); slots as above,

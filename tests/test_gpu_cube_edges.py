@@ -363,3 +363,27 @@ def test_multi_state_flow_of_many_states(states, run):
     finally:
         for k, v in old.items():
             B.bat_set_option(k, v)
+
+
+@pytest.mark.parametrize("n_pvec", [1, 0])
+def test_ranges_and_single_vectors_to_rounding(n_pvec):
+    """One probability vector per graph, and ranges (n_pvec 0): products of at
+    most 30 factors and compensated sums, as whole sweeps: some 30 roundings
+    of 1.1e-16."""
+    B = _B()
+    rng = np.random.default_rng(2600)
+    nets = [W.random_connected(n, m, seed=m + 7, p_lo=0.2, p_hi=0.99)
+            for n, m in ((4, 5), (6, 9), (7, 11), (8, 13), (9, 16), (11, 18), (12, 20))]
+    print("to rounding", n_pvec, flush=True)
+    if n_pvec:
+        R, cnt = B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t) for x in nets], [x.p[None, :] for x in nets])
+        assert B.bat_last_launch().perm == 5
+    for k, x in enumerate(nets):
+        if n_pvec:
+            got, c, o = R[k, 0], cnt[k], oracle.reliability(x.n, x.arcs, x.p, x.s, x.t)
+        else:
+            lo, hi = sorted(int(v) for v in rng.integers(0, (1 << x.m) + 1, 2))
+            r = B.bat_reliability_range(x.n, x.arcs, x.p, x.s, x.t, lo, hi)
+            assert B.bat_last_launch().perm == 5 or lo == hi
+            got, c, o = r.R, r.count, oracle.reliability_range(x.n, x.arcs, x.p, x.s, x.t, lo, hi)
+        assert c == o.count and abs(got - o.sum) <= 4e-15 * o.sum, (k, got, o.sum)
