@@ -2821,15 +2821,17 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
         c[k].assign(m, 0u);
         word[k].assign(m, 0u);
     }
-    double sum0 = 1.0;
-    std::vector<double> q[2] = {std::vector<double>(32, 0.0), std::vector<double>(32, 0.0)}, tb(2048, 0.0);
-    for (u64 b = 0; b < B0; ++b) q[0][b] = 1.0;
-    for (u64 b = 0; b < B1; ++b) q[1][b] = 1.0;
+    // the tables are rounded once, from extended precision: their errors are
+    // the same for every cube, and do not average out
+    long double sum0 = 1.0L, q[2][32] = {};
+    std::vector<double> q1(32, 0.0), tb(2048, 0.0);
+    for (u64 b = 0; b < B0; ++b) q[0][b] = 1.0L;
+    for (u64 b = 0; b < B1; ++b) q[1][b] = 1.0L;
     u64 stride = 1;
     u32 upair = 0u;
     for (int j = 0; j < m; ++j) {
         int32_t least = capt[off[j]], most = least;
-        double sum = 0.0;
+        long double sum = 0.0L;
         for (u32 x = 0; x < sig[j]; ++x) {
             const int32_t cap = capt[off[j] + x];
             least = std::min(least, cap);
@@ -2857,14 +2859,25 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
             stride *= sig[j];
         }
     }
+    for (u64 b = 0; b < B1; ++b) {
+        q1[b] = (double)q[1][b];
+        q[1][b] *= sum0;
+    }
     for (int level = 0; level < 2; ++level)
-        for (int h = 0; h < 4; ++h)
-            for (int x = 0; x < 256; ++x) {
-                double a = 0.0;
-                for (int i = 0; i < 8; ++i)
-                    if ((x >> i) & 1) a += q[level][8 * h + i];
-                tb[1024 * level + 256 * h + x] = level ? a * sum0 : a;
+        for (int h = 0; h < 4; ++h) {
+            // (bytes of the bits that a word has)
+            const int bits = std::max(0, std::min(8, (int)(level ? B1 : B0) - 8 * h));
+            double *t = &tb[1024 * level + 256 * h];
+            long double acc[256];
+            acc[0] = 0.0L;
+            for (int b = 0; b < bits; ++b) {
+                const long double w = q[level][8 * h + b];
+                for (int x = 0; x < 1 << b; ++x) {
+                    acc[(1 << b) + x] = acc[x] + w;
+                    t[(1 << b) + x] = (double)acc[(1 << b) + x];
+                }
             }
+        }
     // the closure, on slots
     std::vector<bat_arc> sa(m);
     std::vector<int> bit(m);
@@ -2941,7 +2954,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     rc = scratch_reserve(D.id, st, o_pc + sizeof(u64) * n_waves, in_bytes + out_bytes, S);
     if (rc) return rc;
     memcpy(S->host, tb.data(), sizeof(double) * tb.size());
-    memcpy(S->host + o_q1, q[1].data(), sizeof(double) * 32);
+    memcpy(S->host + o_q1, q1.data(), sizeof(double) * 32);
     memcpy(S->host + o_m1, m1.data(), sizeof(u32) * 96);
     memcpy(S->host + o_w, wt.data(), sizeof(double) * wt.size());
     char *ws = S->dev;

@@ -157,7 +157,7 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
         const bool live = prefix < P.n_prefix;
         u64 r = prefix;
         u32 up[3] = {0u, 0u, 0u};
-        double q = 1.0;
+        double q = 1.0, qe = 0.0;
 #pragma unroll
         for (int j = (int)(G::KW + G::KW1); j < (int)G::M; ++j) {
             const u32 x = (u32)(r % G::SIG[j]);
@@ -165,8 +165,9 @@ __device__ void ms_cube_kernel(const MsCubeParams &P, MsCubeLds &L)
             up[0] |= ((G::C1[j] >> x) & 1u) << j;
             up[1] |= ((G::CE1[j] >> x) & 1u) << j;
             up[2] |= ((G::CE12[j] >> x) & 1u) << j;
-            q *= P.w[G::OFF[j] + x];
+            dd_mul(q, qe, P.w[G::OFF[j] + x]);
         }
+        q += qe;
         const u32 most[3] = {up[0] | high[0], up[1] | high[1], up[2] | high[2]};
         const u32 can = ms_meets<G, 1>(most, live ? G::FULL1 : 0u);
         if (__ballot(can != 0u) != 0ull) {
