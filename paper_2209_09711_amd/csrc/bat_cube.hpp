@@ -943,8 +943,10 @@ struct CubeGradSweep {
         wave_lds_sync();
         v = live ? v : 0.0;
         if (__ballot(v != 0.0) == 0ull) return;
-        const double w = qi * v;
-        dd_add(lane_hi, lane_lo, w, __builtin_fma(qi, v, -w));
+        double w = qi * v, e;
+        lane_lo += __builtin_fma(qi, v, -w);
+        two_sum(lane_hi, w, lane_hi, e);
+        lane_lo += e;
         if (rb < M) {
             double h = T.ql[lane] * v, l = 0.0;
             wave_sum_dd(h, l);
@@ -953,8 +955,13 @@ struct CubeGradSweep {
             const u32 x = (u32)(block >> lane) & 1u;
             const double vh = qm * h, vl = __builtin_fma(qm, h, -vh) + qm * l;
             if (lane + rb < M) {
-                if (x) dd_add(sh[1], sl[1], vh, vl);
-                else dd_add(sh[0], sl[0], vh, vl);
+                double s, e;
+                two_sum(x ? sh[1] : sh[0], vh, s, e);
+                e += vl;
+                sh[1] = x ? s : sh[1];
+                sh[0] = x ? sh[0] : s;
+                sl[1] += x ? e : 0.0;
+                sl[0] += x ? 0.0 : e;
             }
         }
     }

@@ -1832,7 +1832,8 @@ int cube_params(const batcube::CubePlan &C, const double *p_host, const double *
         // a chunk's fold of some 50 columns takes as long as several rounds:
         // chunks of several units once they are many (36 arcs, 65536 units:
         // 1.6 ms one by one, 2.6 ms in chunks of 8 of a block of 64; 40 arcs,
-        // 524288 units: 20.4 ms in eights, 26 ms in twos)
+        // 524288 units: 20.4 ms in eights, 26 ms in twos; with columns kept as
+        // double-doubles 21.0 ms in eights)
         u64 per = 1;
         while (w / per > kGradChunks) per *= 2;
         if (want && want->chunk) per = want->chunk;
