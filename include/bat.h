@@ -201,16 +201,19 @@ int bat_reliability_checkpointed(int32_t n_nodes, int32_t n_arcs, const bat_arc 
                                  double *dRdp_out, double *T1_out, double *T0_out);
 
 /*
- * Many networks, many probability vectors, one persistent launch.
+ * Many networks, many probability vectors, together on the device.
  * Graph g has n_nodes[g] nodes and the arcs arcs[arc_offsets[g] ..
  * arc_offsets[g+1]) (arc_offsets has n_graphs + 1 entries, arc_offsets[0]
  * = 0), source s[g], sink t[g].  Each graph has n_pvec probability vectors:
  * p holds, graph after graph, an n_pvec x m_g row-major block (arc fastest),
  * i.e. graph g's block starts at n_pvec * arc_offsets[g].  One connectivity
  * verdict per state vector serves all n_pvec probability vectors of its
- * graph (in groups of up to 32 per pass over the graph's vectors).  Work
- * items (graph, counter range) are queued largest graph first and taken by
- * one persistent block per compute unit.  Outputs: R_out[g * n_pvec + j]
+ * graph (in groups of up to 32 per pass over the graph's vectors).  The
+ * graphs, largest first, are swept by sub-cubes ("BAT_CUBES") in one launch
+ * or two; if one of them has more than 32 arcs on s-t paths, or a knob of the
+ * plain launch is set, all go in the plain launch: work items (graph, counter
+ * range) in a queue, taken by one persistent block per compute unit, and
+ * specialised kernels on side streams.  Outputs: R_out[g * n_pvec + j]
  * and counts_out[g], host pointers.  Limits per graph as above;
  * 1 <= n_pvec <= BAT_MAX_PVEC.  Blocks until done.
  */
@@ -220,7 +223,9 @@ int bat_reliability_batched(int32_t n_graphs, const int32_t *n_nodes, const int3
                             int32_t n_pvec, const double *p, double *R_out, uint64_t *counts_out);
 
 /*
- * Autotuner for the batched launch: runs this batch (same arguments as
+ * Autotuner for the batched launch.  Where the batch goes by sub-cubes, which
+ * have nothing to tune, they are timed and nothing else.  Else it runs this
+ * batch (same arguments as
  * bat_reliability_batched, results discarded) with each candidate number
  * of chained iteration bits (0, 3..6) and per-wavefront segment size
  * (2^4..2^6 iterations), then with graph-specialised kernels for the
