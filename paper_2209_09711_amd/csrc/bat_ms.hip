@@ -21,8 +21,8 @@
 // capacities stays feasible with the greatest, so the second test goes on
 // from the first.  A child whose slot has the least capacity has failed its
 // first test already (its parent's), one with the greatest has met its
-// second; at K = 0 those are verdicts.  An undecided cube of slot 0 alone is
-// not split: as a function of one arc's capacity c the maximum flow is
+// second.  An undecided cube of slot 0 alone is not split (unless the range
+// ends inside it): as a function of one arc's capacity c the maximum flow is
 // min(A + c, B), the smaller of the least cut through the arc and the least
 // one that avoids it, so where it is short of d by x at the least capacity
 // and meets d at the greatest, it meets d from x units more on.  (Split into
@@ -218,9 +218,7 @@ k_ms_flow(batk::MsParams P)
                 if (e <= P.c_lo || c >= P.c_hi) out = 0;
                 else if (c < P.c_lo || e > P.c_hi) out = 2;
             }
-            if ((node & kMsLowFails) && K == 0u) out = 0;
-            else if ((node & kMsHighMeets) && K == 0u) out = 1;
-            else if ((node & kMsLowFails) && (node & kMsHighMeets) && (K != 1u || two)) out = K == 1u ? 3 : 2;
+            if ((node & kMsLowFails) && (node & kMsHighMeets) && (K != 1u || two)) out = K == 1u ? 3 : 2;
             high = (node & kMsLowFails) && (K != 1u || two);
 #pragma unroll
             for (u32 i = 0; i < (u32)MM; ++i) {
@@ -327,19 +325,10 @@ k_ms_flow(batk::MsParams P)
             for (u32 x = 0;; ++x) {
                 more = more && x < (u32)sig[K ? K - 1u : 0u];
                 if (__ballot(more) == 0ull) break;
-                u64 c = 0ull;
-                bool push = false;
-                if (more) {
-                    c = child(node, K, x);
-                    push = true;
-                    if (K == 1u && (c & (kMsLowFails | kMsHighMeets))) {  // a verdict
-                        push = false;
-                        if (!(c & kMsLowFails)) met(c, 0u, 0);
-                    }
-                }
-                const u64 w = __ballot(push);
-                if (push)
-                    stack[sp + __builtin_amdgcn_mbcnt_hi((u32)(w >> 32), __builtin_amdgcn_mbcnt_lo((u32)w, 0u))] = c;
+                const u64 w = __ballot(more);
+                if (more)
+                    stack[sp + __builtin_amdgcn_mbcnt_hi((u32)(w >> 32), __builtin_amdgcn_mbcnt_lo((u32)w, 0u))] =
+                        child(node, K, x);
                 sp += (u32)__popcll(w);
             }
             bat::wave_lds_sync();
