@@ -342,8 +342,10 @@ def main():
     B.bat_reliability(net.n, arcs, net.p, net.s, net.t)
     cold_cached_s = time.perf_counter() - t0
     load_ms = B.bat_last_launch().jit_ms
-    # autotune (one-time, reported separately): work-item size, convergence
-    # test cadence, kernel kind and arc-to-bit order, timed on spread slices
+    # autotune (one-time, reported separately): the plain launch's work-item
+    # size, convergence test cadence, kernel kind and arc-to-bit order, timed
+    # on spread slices; the time per vector is that of the sub-cube sweep,
+    # which runs below
     t0 = time.perf_counter()
     tune_ns = B.bat_autotune(net.n, arcs, net.p, net.s, net.t)
     tune_s = time.perf_counter() - t0
@@ -367,7 +369,7 @@ def main():
     for _ in range(a.steps):
         step()
         li_step = B.bat_last_launch()
-        kern_ms.append(li_step.kernel_ms)   # HIP events on the launch stream
+        kern_ms.append(li_step.kernel_ms)   # the device clock, reported by the kernels
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms_per_step = (t1 - t0) * 1e3 / a.steps
@@ -414,7 +416,7 @@ def main():
     c3 = W.config3()
     grad_c2_ms = None
     if not a.no_extras:
-        # the same sweep with all 40 gradients (the autotuner tuned it too)
+        # the same sweep with all 40 gradients
         B.bat_reliability_grad(net.n, arcs, net.p, net.s, net.t)
         g2 = []
         for _ in range(2):
@@ -441,13 +443,13 @@ def main():
                                   "ratio": min(gr) / min(fw),
                                   "fwd_launch": launch_key(li_f), "grad_launch": launch_key(li_g)}
     if not a.no_extras and not a.no_batched:
-        # batched: one persistent launch vs the plain forward on every
+        # batched: one call vs the forward sweep of every
         # (graph, probability vector) pair of the same workload
         nets, pvs = c3
         graphs = [(g.n, g.arc_array(), g.s, g.t) for g in nets]
         B.bat_reliability_batched(graphs, pvs)
-        # autotune (one-time, reported separately): chain length and
-        # segment size of the batched launch on this batch
+        # autotune (one-time, reported separately): times the sub-cube batch,
+        # which has no knobs
         t0 = time.perf_counter()
         B.bat_autotune_batched(graphs, pvs)
         btune_s = time.perf_counter() - t0
