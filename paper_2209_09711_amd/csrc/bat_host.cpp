@@ -3858,8 +3858,12 @@ struct CubeJob {
 // and 0.71 ms with 3 vectors, 1.64 and 1.74 ms with 32), 20 and 17 slower.
 constexpr int kCubeBatchOneLevel = 22;
 constexpr int kCubeBatchP = 32;  // most probability vectors of an entry
-constexpr u64 kCubeBatchItems = 256;  // most work items of a block
-constexpr u64 kCubeBatchBlocks = 1ull << 20;
+// Most work items of a block: the partials of the largest batch then take
+// some 20 MiB (64 graphs of 28 to 32 arcs x 32 vectors: 11.3 ms; with at most
+// 256 items 11.5 ms and up to 134 MiB), and also with one level forced on
+// 1024 entries of 32 arcs a launch has 2^19 blocks of 1024 threads (HIP: fewer
+// than 2^32 threads).
+constexpr u64 kCubeBatchItems = 4096;
 constexpr size_t kCubeBatchJobs = 1024;  // most entries of a sweep (about 12 KiB of staging each)
 
 // Vectors a lane group of the kernel is made for.
@@ -3934,12 +3938,6 @@ int cube_batch_run(CubeJob *jobs, size_t n, int width, const DeviceInfo &D, std:
         J.first_block = (u32)blocks;
         J.n_blocks = (u32)((J.items + J.units - 1) / J.units);
         blocks += J.n_blocks;
-    }
-    // (reached only with one level forced on large graphs: 1024 threads a
-    // block, fewer than 2^32 in a launch)
-    if (blocks > kCubeBatchBlocks) {
-        fits = false;
-        return BAT_OK;
     }
     // records: the entry, its steps, its probabilities
     const size_t o_step = align_up(sizeof(bat::BatchCube), 64);

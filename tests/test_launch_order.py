@@ -143,16 +143,32 @@ result = [li.kernel_ms, li.perm]
     assert [o.kind for o in ops].count("launch") >= 1 and not any(o.kind == "alloc" for o in ops)
 
 
-def test_batch_of_too_many_blocks_goes_to_the_plain_launch():
-    """One level forced on 512 graphs of 32 arcs: 4 million blocks."""
-    rc, ops = recorder.run("""
+@pytest.mark.parametrize("graphs", [512, 1100])
+def test_batch_with_one_level_forced_is_launched(graphs):
+    """Hundreds of graphs of 32 arcs with one level, 2^21 work items each:
+    under 2^32 threads in a launch."""
+    rc, ops = recorder.run(f"""
 x = W.random_connected(12, 32, seed=8)
 B.bat_set_option("BAT_CUBES", 1)
 B.bat_set_option("BAT_CUBE_LEVELS", 1)
 try:
-    B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t)] * 512, [np.full((2, 32), 0.5)] * 512)
+    B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t)] * {graphs}, [np.full((2, 32), 0.5)] * {graphs})
 except B.BatError as e:
     result = e.code
-""", fail="k_batched_reduce,finish")
-    assert not any(o.failed for o in ops if o.kind == "launch" and "k_cube" in o.args[1])
-    assert any(o.kind == "launch" and "k_batched" in o.args[1] for o in ops)
+""", fail="finish")
+    sweeps = [o for o in ops if o.kind == "launch" and "finish" not in o.args[1]]
+    assert rc == -3 and len(sweeps) == 2 and not any(o.failed for o in sweeps)
+
+
+def test_workspace_of_a_large_batch():
+    """1024 entries of 32 arcs and 32 vectors: the partials that the thread
+    keeps stay within some tens of MiB."""
+    rc, ops = recorder.run("""
+x = W.random_connected(14, 32, seed=8)
+try:
+    B.bat_reliability_batched([(x.n, x.arcs, x.s, x.t)] * 32, [np.full((1024, 32), 0.5)] * 32)
+except B.BatError as e:
+    result = e.code
+""", fail="finish")
+    assert rc == -3 and not any(o.failed for o in ops if o.kind == "launch" and "finish" not in o.args[1])
+    assert sum(int(o.args[1]) for o in ops if o.kind == "alloc" and o.args[0] == "device") < 48 << 20
