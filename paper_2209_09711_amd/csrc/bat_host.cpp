@@ -2788,7 +2788,7 @@ int ms_bits_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::u
 // Most wavefronts of a multi-state launch, so that neither its threads (HIP's
 // limit is 2^32) nor its partials grow with the space: past that each takes
 // several work items, or there are several launches.
-constexpr u64 kMsWaves = 65536;
+constexpr u64 kMsLaunchWaves = 65536;
 
 // Fewest prefixes worth their own wavefronts: 3^16 vectors at demand 3 took 66
 // us with 59049 prefixes and words of 27 cubes, 97 us with 531441 and words of
@@ -2814,7 +2814,7 @@ int ms_cubes_run(int32_t n, int32_t m, const int *su, const int *sv, const bat::
     while (kw + kw1 < m && B1 * sig[kw + kw1] <= 32 && N / (B0 * B1 * sig[kw + kw1]) >= fewest)
         B1 *= sig[kw + kw1++];
     const u64 n_prefix = N / (B0 * B1), n_items = (n_prefix + bat::kWave - 1) / bat::kWave;
-    const u64 n_waves = std::min(n_items, kMsWaves);
+    const u64 n_waves = std::min(n_items, kMsLaunchWaves);
     const u64 blocks = (n_waves + bat::kMsCubeWaves - 1) / bat::kMsCubeWaves;
     auto kinds = [](int32_t c) { return (c >= 1 ? 1u : 0u) | (c == 1 ? 2u : 0u) | (c == 1 || c == 2 ? 4u : 0u); };
     std::vector<u32> c[3], word[3], lo(m, 0u), hi(m, 0u), m1(96, 0u);
@@ -3096,8 +3096,8 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     }
     if (src_only) return fail(BAT_EINVAL, "no bit-sliced kernel for this sweep (it needs demand 1 to 3 and arcs)");
     // cubes of the L lowest slots: as large as leave some 1024 work items of
-    // 64 (3^15 vectors, demand 4: 0.36 ms with 2768 items, 0.46 ms with 923,
-    // 0.50 ms with 8304; option BAT_MS_RUN > 0: of at most that many vectors)
+    // 64 (3^15 vectors, demand 4: 0.28 ms with 2768 items, 0.36 ms with 923,
+    // 0.39 ms with 8304; option BAT_MS_RUN > 0: of at most that many vectors)
     const u64 span = c_hi - c_lo;
     // The first slot already where that leaves 512: a cube of one free slot is
     // decided whole, by one flow and its bound (6^7 vectors, demand 11: 60 us
@@ -3116,14 +3116,15 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
             K.most[j] = std::max(K.most[j], capt[K.off[j] + k]);
             sum += wt[K.off[j] + k];
         }
-        if (j == (int)K.L && j < std::min<int>(m, batk::kMsTreeSlots) && K.size[j] * K.sig[j] <= (j ? most_size : first_size)) {
+        if (j == (int)K.L && j < std::min<int>(m, batk::kMsTreeSlots) &&
+            K.size[j] * K.sig[j] <= (j ? most_size : first_size)) {
             K.size[j + 1] = K.size[j] * K.sig[j];
             K.weight[j + 1] = K.weight[j] * sum;
             K.most_states = std::max(K.most_states, K.sig[j]);
             K.L = (u32)(j + 1);
         }
     }
-    // roots: those cubes.  A launch takes at most kMsWaves work items of 64;
+    // roots: those cubes.  A launch takes at most kMsLaunchWaves work items of 64;
     // longer ranges go in several, one after the other
     const u64 size_L = K.size[K.L], root_end = span ? (c_hi + size_L - 1) / size_L : c_lo / size_L;
     const u64 n_items = (root_end - c_lo / size_L + 63) / 64;
@@ -3138,7 +3139,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     const size_t o_cap = 0;
     const size_t o_w = align_up(o_cap + sizeof(int32_t) * (n_tab + 1), 256);
     const size_t in_bytes = align_up(o_w + sizeof(double) * (n_tab + 1), 256);
-    const u64 items = std::min(std::max<u64>(n_items, 1), kMsWaves);
+    const u64 items = std::min(std::max<u64>(n_items, 1), kMsLaunchWaves);
     const size_t o_part = in_bytes;
     const size_t o_pc = align_up(o_part + sizeof(double) * 2 * items, 256);
     const size_t total = align_up(o_pc + sizeof(u64) * items, 256);
@@ -3160,7 +3161,7 @@ int ms_run(int32_t n, int32_t m, const bat_arc *arcs, const int32_t *sigma, cons
     K.root_hi = c_lo / size_L;
     do {
         K.root_lo = K.root_hi;
-        K.root_hi = std::min(K.root_lo + 64 * kMsWaves, root_end);
+        K.root_hi = std::min(K.root_lo + 64 * kMsLaunchWaves, root_end);
         K.n_items = (K.root_hi - K.root_lo + 63) / 64;
         K.c_lo = std::max(c_lo, K.root_lo * size_L);
         K.c_hi = std::min(c_hi, K.root_hi * size_L);
@@ -3530,6 +3531,7 @@ int bat_last_launch(bat_launch_info *info)
             hipError_t e = t_state.cube_stream ? hipStreamIsCapturing(t_state.cube_stream, &cs) : hipSuccess;
             if (e == hipSuccess && cs == hipStreamCaptureStatusNone) e = hipStreamSynchronize(t_state.cube_stream);
             if (e != hipSuccess) {
+                (void)hipGetLastError();
                 int dev = 0;
                 e = hipGetDevice(&dev);
                 if (e == hipSuccess) e = hipSetDevice(t_state.cube_dev);
